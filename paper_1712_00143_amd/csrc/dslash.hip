@@ -182,11 +182,13 @@ __device__ __forceinline__ void dslash_body(const DslashLaunch &a)
         }
     }
     if constexpr (EPI != EPI_PLAIN) {
-        if (a.red) {
-            publish_compact(part, a.red, tile);
-        } else if (a.fin != FIN_NONE) {
+        if (wave == 0) {
             double mine[1] = {part};
-            publish_partials<1>(mine, a.partials, tile);
+            first_wave_sum<1>(mine);
+            if (lane == 0) {
+                if (a.red) a.red[tile] = mine[0];
+                else if (a.fin != FIN_NONE) a.partials[(size_t)tile * NPART] = mine[0];
+            }
         }
     }
 }

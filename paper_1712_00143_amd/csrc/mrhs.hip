@@ -27,12 +27,36 @@ namespace hisq {
 template <class LT> struct MrhsVec { using type = float; using pair = float2; };
 template <> struct MrhsVec<double> { using type = double; using pair = double2; };
 
+// One gathered colour vector: base (uniform over the wavefront) plus a 32-bit
+// byte offset.  An FP32 vector is 24 bytes at a stride of 24: one 16-byte and
+// one 8-byte load, where three 8-byte loads per vector kept the address and
+// line-lookup path of the L1 busier than the arithmetic (12 instructions per
+// link of four right-hand sides, now 8).
+template <class A> __device__ __forceinline__ void gather3(const char *base, unsigned off, Cx<A> v[3])
+{
+    if constexpr (sizeof(A) == 8) {
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            const double2 t = *reinterpret_cast<const double2 *>(base + off + 16 * c);
+            v[c] = {t.x, t.y};
+        }
+    } else {
+        typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
+        const f4 t = *reinterpret_cast<const f4 *>(base + off);
+        const float2 u = *reinterpret_cast<const float2 *>(base + off + 16);
+        v[0] = {t.x, t.y};
+        v[1] = {t.z, t.w};
+        v[2] = {u.x, u.y};
+    }
+}
+
 template <class LT, int R, int W, int NR, int EPI>
 __global__ void __launch_bounds__(64 * W) k_dslash_mrhs(MrhsLaunch a)
 {
     using A = typename AccOf<LT>::type;
     using V2 = typename MrhsVec<LT>::pair;
     constexpr int DPW = 16 / W;
+    constexpr unsigned VB = 3 * sizeof(V2);   // bytes of a colour vector
     using F = LinkFmt<LT, R>;
     // the wave index is uniform: keep it (and the direction-block bases) scalar
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -46,13 +70,20 @@ __global__ void __launch_bounds__(64 * W) k_dslash_mrhs(MrhsLaunch a)
     const int grp = bt - tile * ng;
     const int r0 = grp * NR;
     bool act[NR];
-    bool any = false;
+    int first = -1;   // first active right-hand side of the group
 #pragma unroll
-    for (int j = 0; j < NR; j++) {
+    for (int j = NR - 1; j >= 0; j--) {
         act[j] = r0 + j < a.nrhs && (a.states ? a.states[r0 + j].status == a.want : true);
-        any |= act[j];
+        if (act[j]) first = r0 + j;
     }
-    if (!any) return;
+    if (first < 0) return;
+    // an inactive right-hand side gathers the vectors of an active one (lines
+    // that are loaded anyway; its result is not stored), so that the gathers
+    // are straight-line code without a branch per right-hand side
+    const char *src[NR];
+#pragma unroll
+    for (int j = 0; j < NR; j++)
+        src[j] = (const char *)a.in + (size_t)(act[j] ? r0 + j : first) * (size_t)a.vstride * VB;
     const int h = pd.h;
     const int i = tile * TILE + lane;
     const bool valid = i < h;
@@ -60,7 +91,6 @@ __global__ void __launch_bounds__(64 * W) k_dslash_mrhs(MrhsLaunch a)
     const LinkSet &ls = pd.ls[a.lslot];
     const char *lbase = (const char *)ls.ptr[par];
     const int L0 = pd.L[0], L1 = pd.L[1], L2 = pd.L[2], L3 = pd.L[3];
-    const V2 *in = (const V2 *)a.in;
 
     Cx<A> acc[NR][3];
 #pragma unroll
@@ -101,14 +131,7 @@ __global__ void __launch_bounds__(64 * W) k_dslash_mrhs(MrhsLaunch a)
 #pragma unroll
             for (int g = 0; g < G; g++)
 #pragma unroll
-                for (int j = 0; j < NR; j++) {
-                    const V2 *p = in + ((long long)(r0 + j) * a.vstride + nb[g]) * 3;
-#pragma unroll
-                    for (int c = 0; c < 3; c++) {
-                        V2 t = act[j] ? p[c] : V2{(A)0, (A)0};
-                        v[g][j][c] = {t.x, t.y};
-                    }
-                }
+                for (int j = 0; j < NR; j++) gather3<A>(src[j], (unsigned)nb[g] * VB, v[g][j]);
 #pragma unroll
             for (int g = 0; g < G; g++) {
                 const int d = wave * DPW + g0 + g;
@@ -134,47 +157,69 @@ __global__ void __launch_bounds__(64 * W) k_dslash_mrhs(MrhsLaunch a)
         }
     }
 
+    // The waves' partial vectors meet in LDS in a fixed order.  Down to PW
+    // waves the upper half hands its vectors to the lower half; then wave w
+    // collects right-hand sides w, w + PW, ... from the others, so that the
+    // epilogue of NR right-hand sides runs in NR waves side by side instead
+    // of in wave 0 while the others wait.  At 24^3x48, FP32 recon-18, with the
+    // wide branch-free gathers: four right-hand sides 105 -> 93-98 us (PLAIN)
+    // and 139 -> 113 us (AX); 48 of them 660 -> 569 us and 989 -> 736 us, the
+    // FP64 residual of 48 976 -> 760 us.  What is left is memory-side traffic
+    // (3.6 GB a launch of 48, vectors refetched across the t hops).
+    constexpr int PW = NR == 1 ? 1 : W < 4 ? W : NR == 2 ? 2 : 4;
     if constexpr (W > 1) {
-        // pairwise tree over the waves (W is a power of two): the upper half
-        // hands its partial vectors to the lower half through LDS, halving
-        // each round, so LDS holds W/2 waves' worth (more blocks per CU than
-        // a single round into wave 0) and the summation order is fixed
-        __shared__ A red[(W / 2) * NR * 6 * 64];
+        constexpr int FOLD = W / 2 >= PW ? W / 2 : 0;   // waves written per folding round, at most
+        constexpr int SLOTS = FOLD > PW ? FOLD : PW > 1 ? PW : FOLD;
+        __shared__ A red[SLOTS * NR * 6 * 64];
+        auto put = [&](int slot, int j) {
 #pragma unroll
-        for (int half = W / 2; half >= 1; half >>= 1) {
-            if (wave >= half && wave < 2 * half) {
-#pragma unroll
-                for (int j = 0; j < NR; j++)
-#pragma unroll
-                    for (int c = 0; c < 3; c++) {
-                        red[(((wave - half) * NR + j) * 6 + 2 * c) * 64 + lane] = acc[j][c].re;
-                        red[(((wave - half) * NR + j) * 6 + 2 * c + 1) * 64 + lane] = acc[j][c].im;
-                    }
+            for (int c = 0; c < 3; c++) {
+                red[((slot * NR + j) * 6 + 2 * c) * 64 + lane] = acc[j][c].re;
+                red[((slot * NR + j) * 6 + 2 * c + 1) * 64 + lane] = acc[j][c].im;
             }
+        };
+        auto take = [&](int slot, int j) {
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+                acc[j][c].re += red[((slot * NR + j) * 6 + 2 * c) * 64 + lane];
+                acc[j][c].im += red[((slot * NR + j) * 6 + 2 * c + 1) * 64 + lane];
+            }
+        };
+#pragma unroll
+        for (int half = W / 2; half >= PW; half >>= 1) {
+            if (wave >= half && wave < 2 * half)
+#pragma unroll
+                for (int j = 0; j < NR; j++) put(wave - half, j);
             __syncthreads();
-            if (wave < half) {
+            if (wave < half)
 #pragma unroll
-                for (int j = 0; j < NR; j++)
-#pragma unroll
-                    for (int c = 0; c < 3; c++) {
-                        acc[j][c].re += red[((wave * NR + j) * 6 + 2 * c) * 64 + lane];
-                        acc[j][c].im += red[((wave * NR + j) * 6 + 2 * c + 1) * 64 + lane];
-                    }
-            }
+                for (int j = 0; j < NR; j++) take(wave, j);
             if (half > 1) __syncthreads();
         }
+        if constexpr (PW > 1) {
+            if (wave < PW)
+#pragma unroll
+                for (int j = 0; j < NR; j++)
+                    if (j % PW != wave) put(wave, j);
+            __syncthreads();
+            if (wave < PW)
+#pragma unroll
+                for (int j = 0; j < NR; j++)
+                    if (j % PW == wave)
+#pragma unroll
+                        for (int w = 0; w < PW; w++)
+                            if (w != wave) take(w, j);
+        }
     }
+    if (wave >= PW) return;   // no barriers below
 
-    double part[NR];
 #pragma unroll
-    for (int j = 0; j < NR; j++) part[j] = 0.0;
-    if (wave == 0 && valid) {
-        V2 *out = (V2 *)a.out;
-#pragma unroll
-        for (int j = 0; j < NR; j++) {
-            if (!act[j]) continue;
+    for (int j = 0; j < NR; j++) {
+        if (j % PW != wave || r0 + j >= a.nrhs) continue;
+        double part = 0.0;
+        if (valid && act[j]) {
             const long long o = (long long)(r0 + j) * a.vstride + i;
-            V2 *po = out + o * 3;
+            V2 *po = (V2 *)a.out + o * 3;
             if constexpr (EPI == EPI_PLAIN) {
 #pragma unroll
                 for (int c = 0; c < 3; c++) po[c] = V2{acc[j][c].re, acc[j][c].im};
@@ -186,7 +231,7 @@ __global__ void __launch_bounds__(64 * W) k_dslash_mrhs(MrhsLaunch a)
                     V2 p = pp[c];
                     A vr = dg * p.x - acc[j][c].re, vi = dg * p.y - acc[j][c].im;
                     po[c] = V2{vr, vi};
-                    part[j] += (double)p.x * (double)vr + (double)p.y * (double)vi;
+                    part += (double)p.x * (double)vr + (double)p.y * (double)vi;
                 }
             } else {  // EPI_RES: out = b - diag x + D in, |out|^2
                 const V2 *px = (const V2 *)a.aux + o * 3;
@@ -198,20 +243,16 @@ __global__ void __launch_bounds__(64 * W) k_dslash_mrhs(MrhsLaunch a)
                     double2 bb = pb[c];
                     A vr = (A)bb.x - dg * x.x + acc[j][c].re, vi = (A)bb.y - dg * x.y + acc[j][c].im;
                     po[c] = V2{vr, vi};
-                    part[j] += (double)vr * (double)vr + (double)vi * (double)vi;
+                    part += (double)vr * (double)vr + (double)vi * (double)vi;
                 }
             }
         }
-    }
-    if constexpr (EPI != EPI_PLAIN) {
-        __shared__ double lds[16 * NR];
-        block_sum<NR>(part, lds);
-        if (threadIdx.x == 0) {
-            const int ntile = pd.ntile;
-            for (int j = 0; j < NR; j++) {
-                if (r0 + j >= a.nrhs) continue;
-                if (a.red) a.red[(size_t)(r0 + j) * ntile + tile] = part[j];
-                else a.partials[((size_t)(r0 + j) * ntile + tile) * NPART] = part[j];
+        if constexpr (EPI != EPI_PLAIN) {
+            part = wave_sum(part);
+            if (lane == 0) {
+                const size_t t = (size_t)(r0 + j) * pd.ntile + tile;
+                if (a.red) a.red[t] = part;
+                else a.partials[t * NPART] = part;
             }
         }
     }

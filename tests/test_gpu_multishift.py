@@ -266,3 +266,12 @@ def test_mrhs_dslash_forced_matrix_core_and_vector_kernels(tmp_path, shape):
                        capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
     assert '"shape": %d' % shape in r.stdout, r.stdout
+
+
+@pytest.mark.parametrize("shape", [2, 8, 16])
+def test_mrhs_dslash_every_block_shape(tmp_path, shape):
+    """The same cases with the vector-ALU kernel at every other block shape:
+    the partial vectors of W waves are folded to at most four waves and then
+    exchanged so that each wave finishes its own right-hand sides, which takes
+    a different path for W = 2, 4, 8 and 16."""
+    test_mrhs_dslash_forced_matrix_core_and_vector_kernels(tmp_path, shape)
