@@ -222,10 +222,11 @@ __global__ void __launch_bounds__(192) k_blas(BlasLaunch a)
     }
 }
 
-// One block per problem: fixed-order sum of the problem's tile partials, then
-// the finisher (FP64 scalar recurrences) on the totals.
+// One block per problem: fixed-order sum of the problem's tile partials (nv
+// values per tile, tiles `stride` doubles apart), then the finisher (FP64
+// scalar recurrences) on the totals.
 __global__ void __launch_bounds__(1024) k_finish(const ProbDesc *probs, SolveState *states, const double *partials,
-                                                int fin, int want, int nv, ShiftState *ms)
+                                                int fin, int want, int nv, ShiftState *ms, int slot, int stride)
 {
     __shared__ double lds[16 * NPART];
     const ProbDesc &pd = probs[blockIdx.x];
@@ -235,18 +236,28 @@ __global__ void __launch_bounds__(1024) k_finish(const ProbDesc *probs, SolveSta
 #pragma unroll
     for (int k = 0; k < NPART; k++) acc[k] = 0.0;
     for (int j = threadIdx.x; j < pd.ntile; j += blockDim.x) {
-        const double *p = partials + (size_t)(pd.tile_begin + j) * NPART;
+        const double *p = partials + (size_t)(pd.tile_begin + j) * stride;
         for (int k = 0; k < nv; k++) acc[k] += p[k];
     }
     block_sum<NPART>(acc, lds);
-    if (threadIdx.x == 0) run_finisher(fin, st_, acc, ms ? &ms[blockIdx.x] : nullptr);
+    if (fin == FIN_MS) {
+        // one wavefront, a shift per lane: the recurrences of twelve shifts in
+        // one thread took longer than the sum
+        __shared__ double tot;
+        if (threadIdx.x == 0) tot = acc[0];
+        __syncthreads();
+        if (threadIdx.x < 64) ms_finish(st_, &ms[blockIdx.x], tot, slot);
+        return;
+    }
+    if (threadIdx.x == 0) run_finisher(fin, st_, acc);
 }
 
 hipError_t launch_finish(const ProbDesc *probs, SolveState *states, const double *partials, int fin, int want,
-                         int nv, int nprob, hipStream_t s, ShiftState *ms)
+                         int nv, int nprob, hipStream_t s, ShiftState *ms, int slot, int stride)
 {
     // 1024 threads: a large problem's tile partials (thousands) in few loads per thread
-    hipLaunchKernelGGL(k_finish, dim3(nprob), dim3(1024), 0, s, probs, states, partials, fin, want, nv, ms);
+    hipLaunchKernelGGL(k_finish, dim3(nprob), dim3(1024), 0, s, probs, states, partials, fin, want, nv, ms,
+                       slot, stride);
     return hipGetLastError();
 }
 
@@ -275,26 +286,29 @@ hipError_t launch_convert(const void *src, int sprec, void *dst, int dprec, long
 
 // Multi-shift vector kernels (FP32 vectors, FP64 scalars).  Problem = one
 // right-hand side; tiles of problem j cover its h sites.
+//
+// The shift updates of an iteration touch every x_k and p_k once (12 shifts of
+// 4 right-hand sides at 24^3x48: 1.5 GB, 180 us of a 440 us iteration) and
+// nothing but the base system's r, so they wait: the residuals of up to MSRING
+// iterations stay in a ring and one flush applies them all, each element in
+// the order the separate updates had (29 us an iteration instead of 180).
 template <int OP>
 __global__ void __launch_bounds__(192) k_ms(BlasLaunch a)
 {
-    __shared__ float lds[192];
     const int tile = blockIdx.x;
     const int prob = a.tile2prob ? a.tile2prob[tile] : 0;
     const ProbDesc &pd = a.probs[prob];
     SolveState *st_ = &a.states[prob];
-    const int stat = st_->status;
-    if (OP == BL_MS_UPDATE ? (stat != ST_RUNNING && stat != ST_MS_LAST) : stat != a.want) return;
-    const ShiftState *ms = &a.ms[prob];
+    if (st_->status != a.want) return;
     const int e = threadIdx.x;
     const long long site0 = (long long)(tile - pd.tile_begin) * TILE;
     const bool ok = site0 * 3 + e < (long long)pd.h * 3;
     const long long f = (pd.voff + site0) * 3 + e;       // this rhs's vectors
     const long long h3 = (long long)pd.h * 3;
-    const int ns = ms->nshift;
+    const int ns = a.ms[prob].nshift;
     const int j = prob;                                   // rhs index
     double part = 0.0;
-    float2 *r = reinterpret_cast<float2 *>(a.v[0]);
+    float2 *r = reinterpret_cast<float2 *>(a.v[0]) + f;   // ring slot 0
     float2 *p = reinterpret_cast<float2 *>(a.v[3]);
     float2 *xs = reinterpret_cast<float2 *>(a.v[2]);
     float2 *ps = reinterpret_cast<float2 *>(a.v[4]);
@@ -303,7 +317,7 @@ __global__ void __launch_bounds__(192) k_ms(BlasLaunch a)
         if (ok) {
             double2 b = reinterpret_cast<const double2 *>(a.v[5])[f];
             float2 bf = make_float2((float)b.x, (float)b.y);
-            r[f] = bf;
+            r[0] = bf;
             p[f] = bf;
             for (int k = 0; k < ns; k++) {
                 ps[fk0 + k * h3] = bf;
@@ -314,37 +328,88 @@ __global__ void __launch_bounds__(192) k_ms(BlasLaunch a)
     } else if constexpr (OP == BL_MS_RUPDATE) {
         const float al = (float)st_->alpha;
         if (ok) {
-            float2 rv = r[f], q = reinterpret_cast<const float2 *>(a.v[1])[f];
+            float2 rv = r[a.slot * a.ring], q = reinterpret_cast<const float2 *>(a.v[1])[f];
             rv.x -= al * q.x;
             rv.y -= al * q.y;
-            r[f] = rv;
+            r[a.slot2 * a.ring] = rv;
             part = (double)rv.x * rv.x + (double)rv.y * rv.y;
         }
-    } else if constexpr (OP == BL_MS_UPDATE) {
+    } else if constexpr (OP == BL_MS_PUPDATE) {
         if (ok) {
-            const float2 rv = r[f];
-            const float2 pv = p[f];
-            for (int k = 0; k < ns; k++) {
-                if (!ms->upd[k]) continue;
-                const float ak = (float)ms->ak[k], bk = (float)ms->bk[k], zk = (float)ms->zeta[k];
-                const long long fk = fk0 + k * h3;
-                float2 pk = ps[fk], xk = xs[fk];
-                xk.x += ak * pk.x;
-                xk.y += ak * pk.y;
-                pk.x = zk * rv.x + bk * pk.x;
-                pk.y = zk * rv.y + bk * pk.y;
-                xs[fk] = xk;
-                ps[fk] = pk;
-            }
+            const float2 rv = r[a.slot * a.ring], pv = p[f];
             const float be = (float)st_->beta;
             p[f] = make_float2(rv.x + be * pv.x, rv.y + be * pv.y);
         }
     }
-    (void)lds;
-    if (a.fin != FIN_NONE) {
-        double mine[1] = {part};
-        publish_partials<1>(mine, a.partials, tile);
+    if (a.fin != FIN_NONE) publish_compact(part, a.red, tile);
+}
+
+// The pending shift updates.  Iteration q wrote the residual its
+// updates use to ring slot q + 1; the last one of a run of a.slot iterations
+// wrote it to slot 0.  A thread owns two complex numbers of every shift of one
+// right-hand side (h is a multiple of 8, so pairs are 16-byte aligned and never
+// straddle the end of a vector) and holds four shifts' loads in flight: with
+// one shift at a time and 8-byte loads a flush of 8 iterations took 463 us for
+// its 1.6 GB.  blockIdx.y: right-hand side.
+__global__ void __launch_bounds__(256) k_ms_flush(BlasLaunch a)
+{
+    const int j = blockIdx.y;
+    const ShiftState *ms = &a.ms[j];
+    const int npend = ms->npend;
+    if (npend == 0) return;
+    const ProbDesc &pd = a.probs[j];
+    const long long n = (long long)pd.h * 3 / 2;   // pairs per vector
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const float4 *r = reinterpret_cast<const float4 *>(a.v[0]) + pd.voff * 3 / 2 + i;
+    const int ns = ms->nshift;
+    float4 *xs = reinterpret_cast<float4 *>(a.v[2]) + (long long)j * ns * n + i;
+    float4 *ps = reinterpret_cast<float4 *>(a.v[4]) + (long long)j * ns * n + i;
+    float4 rv[MSRING];
+#pragma unroll
+    for (int q = 0; q < MSRING; q++)
+        rv[q] = q < npend ? r[(q + 1 == a.slot ? 0 : q + 1) * (a.ring / 2)] : make_float4(0.f, 0.f, 0.f, 0.f);
+    constexpr int KU = 4;
+    for (int k0 = 0; k0 < ns; k0 += KU) {
+        float4 pk[KU], xk[KU];
+        int nu[KU];
+#pragma unroll
+        for (int u = 0; u < KU; u++) {
+            nu[u] = k0 + u < ns ? ms->nupd[k0 + u] : 0;
+            if (nu[u]) {
+                pk[u] = ps[(k0 + u) * n];
+                xk[u] = xs[(k0 + u) * n];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < KU; u++) {
+            if (nu[u] == 0) continue;
+            const int k = k0 + u;
+#pragma unroll
+            for (int q = 0; q < MSRING; q++) {
+                if (q >= nu[u]) continue;
+                const float ak = ms->ak[q][k], bk = ms->bk[q][k], zk = ms->zk[q][k];
+                xk[u].x += ak * pk[u].x;
+                xk[u].y += ak * pk[u].y;
+                xk[u].z += ak * pk[u].z;
+                xk[u].w += ak * pk[u].w;
+                pk[u].x = zk * rv[q].x + bk * pk[u].x;
+                pk[u].y = zk * rv[q].y + bk * pk[u].y;
+                pk[u].z = zk * rv[q].z + bk * pk[u].z;
+                pk[u].w = zk * rv[q].w + bk * pk[u].w;
+            }
+            xs[k * n] = xk[u];
+            ps[k * n] = pk[u];
+        }
     }
+}
+
+// nrhs right-hand sides of h sites each
+hipError_t launch_ms_flush(const BlasLaunch &a, long long h, int nrhs, hipStream_t s)
+{
+    const long long n = h * 3 / 2;
+    hipLaunchKernelGGL(k_ms_flush, dim3((unsigned)((n + 255) / 256), nrhs), dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_ms(int op, const BlasLaunch &a, int ntiles, hipStream_t s)
@@ -353,10 +418,21 @@ hipError_t launch_ms(int op, const BlasLaunch &a, int ntiles, hipStream_t s)
     switch (op) {
     case BL_MS_INIT: hipLaunchKernelGGL(k_ms<BL_MS_INIT>, g, b, 0, s, a); break;
     case BL_MS_RUPDATE: hipLaunchKernelGGL(k_ms<BL_MS_RUPDATE>, g, b, 0, s, a); break;
-    case BL_MS_UPDATE: hipLaunchKernelGGL(k_ms<BL_MS_UPDATE>, g, b, 0, s, a); break;
+    case BL_MS_PUPDATE: hipLaunchKernelGGL(k_ms<BL_MS_PUPDATE>, g, b, 0, s, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+__global__ void k_status_ms(SolveState *states, ShiftState *ms, int nprob)
+{
+    const int p = blockIdx.x;
+    if (p >= nprob) return;
+    for (int k = threadIdx.x; k < ms[p].nshift; k += blockDim.x) ms[p].nupd[k] = 0;
+    if (threadIdx.x == 0) {
+        ms[p].npend = 0;
+        if (states[p].status == ST_MS_LAST) states[p].status = ST_CONVERGED;
+    }
 }
 
 __global__ void k_status(SolveState *states, int nprob, int from, int to)
@@ -400,8 +476,7 @@ static hipError_t launch_m(int op, const BlasLaunch &a, int nt, hipStream_t s)
 hipError_t launch_blas(int op, int prec, const BlasLaunch &a, int ntiles, int nprob, hipStream_t s)
 {
     if (op == BL_STATUS_MS) {
-        hipLaunchKernelGGL(k_status, dim3((nprob + 63) / 64), dim3(64), 0, s, a.states, nprob,
-                           (int)ST_MS_LAST, (int)ST_CONVERGED);
+        hipLaunchKernelGGL(k_status_ms, dim3(nprob), dim3(64), 0, s, a.states, a.ms, nprob);
         return hipGetLastError();
     }
     if (op == BL_STATUS) {

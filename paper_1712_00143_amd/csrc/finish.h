@@ -29,39 +29,44 @@ __device__ __forceinline__ long long dev_clock()
 //                [alpha_i beta_{i-1} (zeta_{i-1} - zeta_i) + zeta_{i-1} alpha_{i-1} (1 + d_k alpha_i)],
 //   alpha_k = alpha_i zeta_{i+1} / zeta_i,  beta_k = beta_i (zeta_{i+1} / zeta_i)^2,
 // d_k = sigma_k - sigma_base.  A shift stops once |zeta_k| |r| <= tol |b|.
-__device__ __forceinline__ void ms_finish(SolveState *st, ShiftState *ms, double rn)
+// The updates of x_k and p_k this iteration asks for are recorded in ring slot
+// `slot` and applied later (launch_ms_flush).  Called by the 64 lanes of one
+// wavefront, one shift (MAXSHIFT = 64) per lane.
+__device__ __forceinline__ void ms_finish(SolveState *st, ShiftState *ms, double rn, int slot)
 {
     const double al = st->alpha, be = rn / st->rr;
-    int any = 0;
-    for (int k = 0; k < ms->nshift; k++) {
-        ms->upd[k] = ms->active[k];
-        if (!ms->active[k]) continue;
+    const int k = threadIdx.x & 63;
+    bool more = false;
+    if (k < ms->nshift && ms->active[k]) {
+        ms->nupd[k] = slot + 1;
         const double z = ms->zeta[k], zo = ms->zeta_old[k];
         const double zn = z * zo * ms->alpha_old /
                           (al * ms->beta_old * (zo - z) + zo * ms->alpha_old * (1.0 + ms->shift[k] * al));
-        ms->ak[k] = al * zn / z;
-        ms->bk[k] = be * (zn / z) * (zn / z);
+        ms->ak[slot][k] = (float)(al * zn / z);
+        ms->bk[slot][k] = (float)(be * (zn / z) * (zn / z));
+        ms->zk[slot][k] = (float)zn;
         ms->zeta_old[k] = z;
         ms->zeta[k] = zn;
         ms->iters[k] += 1;
         if (fabs(zn) * sqrt(rn) <= sqrt(st->tol2 * st->bb)) ms->active[k] = 0;
-        else any = 1;
+        else more = true;
     }
-    ms->alpha_old = al;
-    ms->beta_old = be;
-    st->beta = be;
-    st->rr_old = st->rr;
-    st->rr = rn;
-    st->iter += 1;
-    if (!any || st->iter >= st->maxiter || !isfinite(rn)) st->status = ST_MS_LAST;
+    const bool any = __ballot(more) != 0;
+    if (k == 0) {
+        ms->npend = slot + 1;
+        ms->alpha_old = al;
+        ms->beta_old = be;
+        st->beta = be;
+        st->rr_old = st->rr;
+        st->rr = rn;
+        st->iter += 1;
+        if (!any || st->iter >= st->maxiter || !isfinite(rn)) st->status = ST_MS_LAST;
+    }
 }
 
-__device__ __forceinline__ void run_finisher(int fin, SolveState *st, const double *tot, ShiftState *ms = nullptr)
+__device__ __forceinline__ void run_finisher(int fin, SolveState *st, const double *tot)
 {
     switch (fin) {
-    case FIN_MS:
-        ms_finish(st, ms, tot[0]);
-        break;
     case FIN_FCG_BETA: {
         const double pq = st->pAp;
         st->cplx[2] = -tot[0] / pq;

@@ -14,6 +14,7 @@ namespace hisq {
 constexpr int TILE = 64;        // sites per logical tile (one wavefront)
 constexpr int NPART = 8;        // doubles of reduction partials per tile
 constexpr int MAXSHIFT = 64;
+constexpr int MSRING = 8;       // multi-shift: iterations whose shift updates one pass applies
 constexpr int NDIR = 16;        // 4 mu x {+1 fat, -1 fat, +3 long, -3 long}
 
 // Solver status codes kept per problem in device memory.
@@ -97,15 +98,18 @@ struct SolveState {
 struct ShiftState {
     double zeta[MAXSHIFT];
     double zeta_old[MAXSHIFT];
-    double ak[MAXSHIFT];
-    double bk[MAXSHIFT];
     double shift[MAXSHIFT];   // sigma_k - sigma_base
+    // coefficients of the iterations not yet applied to x_k, p_k: iteration
+    // `slot` of the ring updates shift k < nshift if slot < nupd[k]
+    float ak[MSRING][MAXSHIFT];
+    float bk[MSRING][MAXSHIFT];
+    float zk[MSRING][MAXSHIFT];
+    int nupd[MAXSHIFT];
     int active[MAXSHIFT];
-    int upd[MAXSHIFT];     // shift updated by the current iteration
     int iters[MAXSHIFT];
     double alpha_old, beta_old;
     int nshift;
-    int pad;
+    int npend;             // most pending iterations of any shift
 };
 
 // ---------------------------------------------------------------- geometry

@@ -100,7 +100,8 @@ struct BlasLaunch {
     double coef;
     double *red;   // fused CG ops: compact per-tile sums, [2][ntot]: p.Ap, then |r|^2
     int ntot;      // tiles of the whole set
-    int pad;
+    int slot, slot2;       // multi-shift: ring slots
+    long long ring;        // multi-shift: complex numbers per ring slot
 };
 enum : int {
     BL_RUPDATE = 0,   // r -= alpha Ap; x += alpha p; partial |r|^2; FIN_BETA
@@ -113,23 +114,27 @@ enum : int {
     BL_COPY_D2F = 7,  // v1 (prec) = v0 (FP64)
     BL_COPY_F2D = 8,  // v1 (FP64) = v0 (prec)
     BL_START = 9,     // r_lo = r_hi (v4); p = r_hi; x_lo = 0 (warm start)
-    BL_MS_RUPDATE = 10,  // multi-shift: r -= alpha Ap; partial |r|^2 (FIN_MS)
-    BL_MS_UPDATE = 11,   // multi-shift: x_k += a_k p_k; p_k = z_k r + b_k p_k; p = r + beta p
+    BL_MS_RUPDATE = 10,  // multi-shift: r' = r - alpha Ap (next ring slot); partial |r'|^2 (FIN_MS)
+    // launch_ms_flush: the pending iterations in turn: x_k += a_k p_k; p_k = z_k r' + b_k p_k
     BL_MS_INIT = 12,     // multi-shift: r = p = b (FP32); p_k = b; x_k = 0; partial |b|^2
-    BL_STATUS_MS = 13,   // MS_LAST -> CONVERGED (one thread per problem)
+    BL_STATUS_MS = 13,   // after a flush: nothing pending, MS_LAST -> CONVERGED (one thread per problem)
+    BL_MS_PUPDATE = 16,  // multi-shift: p = r + beta p
     // The CG update with its finishers folded in: every block sums its
     // problem's compact tile sums itself (same order, same bits in every block).
     BL_RUPDATE_F = 14,   // snapshot the state; alpha = rr / sum(p.Ap); r -= alpha Ap; x += alpha p; |r|^2 to red
     BL_PUPDATE_F = 15,   // beta, convergence and reliable trigger from the snapshot; new state; p = r + beta p
 };
-// vector roles for the multi-shift ops: v0 = r, v1 = Ap, v3 = p, v5 = b (FP64),
-// v2 = x_k base, v4 = p_k base ([rhs][shift][h][3] FP32); ms = per-rhs ShiftState
+// vector roles for the multi-shift ops: v0 = r (the ring: MSRING vectors of
+// every right-hand side, slot-major), v1 = Ap, v3 = p, v5 = b (FP64),
+// v2 = x_k base, v4 = p_k base ([rhs][shift][h][3] FP32); ms = per-rhs
+// ShiftState; slot = ring slot the op reads, slot2 = the one RUPDATE writes
 hipError_t launch_stamp(long long *out, hipStream_t s);
 hipError_t launch_finish(const ProbDesc *probs, SolveState *states, const double *partials, int fin, int want,
-                         int nv, int nprob, hipStream_t s, ShiftState *ms = nullptr);
+                         int nv, int nprob, hipStream_t s, ShiftState *ms = nullptr, int slot = 0, int stride = NPART);
 // contiguous complex arrays: FP64 <-> FP32 (prec 0 / 1), n complex numbers
 hipError_t launch_convert(const void *src, int sprec, void *dst, int dprec, long long n, hipStream_t s);
 hipError_t launch_blas(int op, int prec, const BlasLaunch &a, int ntiles, int nprob, hipStream_t s);
 hipError_t launch_ms(int op, const BlasLaunch &a, int ntiles, hipStream_t s);
+hipError_t launch_ms_flush(const BlasLaunch &a, long long h, int nrhs, hipStream_t s);
 
 }  // namespace hisq

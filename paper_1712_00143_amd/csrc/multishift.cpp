@@ -7,8 +7,10 @@
 //   alpha_j = rr_j / (p_j, Ap_j)                                 [k_finish]
 //   r_j -= alpha_j Ap_j                                          [k_ms RUPDATE]
 //   beta_j, zeta_{j,k}, alpha_{j,k}, beta_{j,k}                  [k_finish FIN_MS, FP64]
-//   x_{j,k} += alpha_{j,k} p_{j,k}; p_{j,k} = zeta_{j,k} r_j + beta_{j,k} p_{j,k};
-//   p_j = r_j + beta_j p_j                                       [k_ms UPDATE, one pass]
+//   p_j = r_j + beta_j p_j                                       [k_ms PUPDATE]
+// and once per MSRING iterations, for each of them in turn,
+//   x_{j,k} += alpha_{j,k} p_{j,k}; p_{j,k} = zeta_{j,k} r_j + beta_{j,k} p_{j,k}
+//                                                                [k_ms FLUSH, one pass]
 // Refinement phase: every (j, k) is finished by the batched mixed-precision
 // CG with FP64 reliable updates, warm-started from x_{j,k}, until its FP64
 // true residual || b_j - (A + sigma_k) x || / ||b_j|| reaches tol.
@@ -41,12 +43,12 @@ struct MsWork {
     SolveState *hst = nullptr;
     ShiftState *dms = nullptr;
     ShiftState *hms = nullptr;
-    double *dpart = nullptr;
+    double *dred = nullptr;   // one sum per tile
     void *r = nullptr, *p = nullptr, *Ap = nullptr, *t = nullptr, *xs = nullptr, *ps = nullptr;
     double *b64 = nullptr, *x64 = nullptr;
     void release()
     {
-        for (void *q : {(void *)ddesc, (void *)dt2p, (void *)dst, (void *)dms, (void *)dpart, r, p, Ap, t, xs,
+        for (void *q : {(void *)ddesc, (void *)dt2p, (void *)dst, (void *)dms, (void *)dred, r, p, Ap, t, xs,
                         ps, (void *)b64, (void *)x64})
             if (q) (void)hipFree(q);
         if (hst) (void)hipHostFree(hst);
@@ -114,8 +116,9 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
     HIPCHK(lat, hipHostMalloc(&W.hst, sizeof(SolveState) * nrhs, hipHostMallocDefault));
     HIPCHK(lat, hipMalloc(&W.dms, sizeof(ShiftState) * nrhs));
     HIPCHK(lat, hipHostMalloc(&W.hms, sizeof(ShiftState) * nrhs, hipHostMallocDefault));
-    HIPCHK(lat, hipMalloc(&W.dpart, sizeof(double) * NPART * (size_t)nrhs * ntile));
-    for (void **q : {&W.r, &W.p, &W.Ap, &W.t}) HIPCHK(lat, hipMalloc(q, v32));
+    HIPCHK(lat, hipMalloc(&W.dred, sizeof(double) * (size_t)nrhs * ntile));
+    HIPCHK(lat, hipMalloc(&W.r, v32 * MSRING));
+    for (void **q : {&W.p, &W.Ap, &W.t}) HIPCHK(lat, hipMalloc(q, v32));
     HIPCHK(lat, hipMalloc(&W.xs, v32 * nshift));
     HIPCHK(lat, hipMalloc(&W.ps, v32 * nshift));
     HIPCHK(lat, hipMalloc(&W.b64, v64));
@@ -149,7 +152,8 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
     bl.tile2prob = W.dt2p;
     bl.states = W.dst;
     bl.ms = W.dms;
-    bl.partials = W.dpart;
+    bl.red = W.dred;
+    bl.ring = (long long)nrhs * h * 3;
     bl.v[0] = W.r;
     bl.v[1] = W.Ap;
     bl.v[2] = W.xs;
@@ -162,7 +166,7 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
     bl.want = ST_RUNNING;
     bl.fin = FIN_NORM_B;
     HIPCHK(lat, launch_ms(BL_MS_INIT, bl, ntot, s));
-    HIPCHK(lat, launch_finish(W.ddesc, W.dst, W.dpart, FIN_NORM_B, ST_RUNNING, 1, nrhs, s));
+    HIPCHK(lat, launch_finish(W.ddesc, W.dst, W.dred, FIN_NORM_B, ST_RUNNING, 1, nrhs, s, nullptr, 0, 1));
 
     // tuned shape of the shared-link kernel (tuning runs before any capture)
     const int group = std::min(4, nrhs);
@@ -180,28 +184,44 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
         a.in = in;
         a.out = out;
         a.aux = aux;
-        a.partials = W.dpart;
+        a.red = W.dred;
         a.states = W.dst;
         a.epi = epi;
         a.want = ST_RUNNING;
         return launch_dslash_mrhs(kprec, recon, group, tcm.W, a, ntile, s);
     };
-    auto iterate = [&]() -> hipError_t {
+    // iteration q of a run of m <= MSRING: reads r from ring slot q, writes the
+    // new one to slot q + 1 (the last one to slot 0, where the next run starts)
+    auto iterate = [&](int q, int m) -> hipError_t {
         hipError_t e;
+        bl.slot = q;
+        bl.slot2 = q + 1 == m ? 0 : q + 1;
         if ((e = mrhs(1, EPI_PLAIN, W.p, W.t, nullptr)) != hipSuccess) return e;
         if ((e = mrhs(0, EPI_AX, W.t, W.Ap, W.p)) != hipSuccess) return e;
-        if ((e = launch_finish(W.ddesc, W.dst, W.dpart, FIN_ALPHA, ST_RUNNING, 1, nrhs, s)) != hipSuccess) return e;
+        if ((e = launch_finish(W.ddesc, W.dst, W.dred, FIN_ALPHA, ST_RUNNING, 1, nrhs, s, nullptr, 0, 1)) != hipSuccess)
+            return e;
         bl.want = ST_RUNNING;
         bl.fin = FIN_MS;
         if ((e = launch_ms(BL_MS_RUPDATE, bl, ntot, s)) != hipSuccess) return e;
-        if ((e = launch_finish(W.ddesc, W.dst, W.dpart, FIN_MS, ST_RUNNING, 1, nrhs, s, W.dms)) != hipSuccess)
+        if ((e = launch_finish(W.ddesc, W.dst, W.dred, FIN_MS, ST_RUNNING, 1, nrhs, s, W.dms, q, 1)) != hipSuccess)
             return e;
         bl.fin = FIN_NONE;
-        if ((e = launch_ms(BL_MS_UPDATE, bl, ntot, s)) != hipSuccess) return e;
-        BlasLaunch st;
-        memset(&st, 0, sizeof st);
-        st.states = W.dst;
-        return launch_blas(BL_STATUS_MS, 0, st, 0, nrhs, s);
+        bl.slot = bl.slot2;
+        return launch_ms(BL_MS_PUPDATE, bl, ntot, s);
+    };
+    // n iterations in runs of MSRING, each followed by its shift updates
+    auto iterations = [&](int n) -> hipError_t {
+        while (n > 0) {
+            const int m = std::min(n, MSRING);
+            hipError_t e;
+            for (int q = 0; q < m; q++)
+                if ((e = iterate(q, m)) != hipSuccess) return e;
+            bl.slot = m;
+            if ((e = launch_ms_flush(bl, h, nrhs, s)) != hipSuccess) return e;
+            if ((e = launch_blas(BL_STATUS_MS, 0, bl, 0, nrhs, s)) != hipSuccess) return e;
+            n -= m;
+        }
+        return hipSuccess;
     };
 
     const int kchunk = prm.check_every > 0 ? prm.check_every : 16;
@@ -210,8 +230,7 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
     const bool use_graph = (prm.flags & HISQ_USE_GRAPH) != 0;
     if (use_graph) {
         HIPCHK(lat, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-        hipError_t ce = hipSuccess;
-        for (int q = 0; q < kchunk && ce == hipSuccess; q++) ce = iterate();
+        hipError_t ce = iterations(kchunk);
         hipError_t ee = hipStreamEndCapture(s, &graph);
         if (ce != hipSuccess) return hip_err(lat, ce, "graph capture");
         if (ee != hipSuccess) return hip_err(lat, ee, "hipStreamEndCapture");
@@ -230,7 +249,7 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
     for (;;) {
         if (use_graph) HIPCHK(lat, hipGraphLaunch(gexec, s));
         else
-            for (int q = 0; q < kchunk; q++) HIPCHK(lat, iterate());
+            HIPCHK(lat, iterations(kchunk));
         HIPCHK(lat, hipMemcpyAsync(W.hst, W.dst, sizeof(SolveState) * nrhs, hipMemcpyDeviceToHost, s));
         HIPCHK(lat, hipStreamSynchronize(s));
         bool any = false;

@@ -275,3 +275,33 @@ def test_mrhs_dslash_every_block_shape(tmp_path, shape):
     exchanged so that each wave finishes its own right-hand sides, which takes
     a different path for W = 2, 4, 8 and 16."""
     test_mrhs_dslash_forced_matrix_core_and_vector_kernels(tmp_path, shape)
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_multishift_deferred_updates_do_not_change_the_solve(graph):
+    """The shift updates of up to eight iterations are applied in one pass.
+    check_every = 1 applies each by itself; runs of 3, 8, 11 (8 + 3) and 16
+    (8 + 8) iterations give the same bits, with shifts that stop in the middle
+    of a run."""
+    H = _hisq()
+    dims = (4, 6, 4, 10)
+    fat, lng = synth.make_links(dims, 0.3, 91)
+    b = synth.gaussian_even(dims, 92, 3)
+    shifts = np.array([0.0, 1e-3, 0.02, 0.3, 2.0])
+    lat = H.Lattice(dims)
+    lat.load_links(fat, lng)
+    lat.prepare_links(H.HISQ_F32, 18)
+    want = None
+    for every in (1, 3, 8, 11, 16):
+        prm = H.hisq_default_params(tol=1e-9, sloppy=H.HISQ_F32, check_every=every, flags=H.HISQ_USE_GRAPH if graph else 0)
+        x, infos = lat.multishift_cg(0.05, shifts, b, params=prm)
+        its = [i["iters"] - i["refine_iters"] for i in infos]
+        if want is None:
+            want = (x, its)
+            for j in range(3):
+                for k, s in enumerate(shifts):
+                    assert oracle.true_residual(dims, fat, lng, 0.05, b[j], x[j, k], s) <= 1e-9
+            assert len(set(its)) > 3
+        assert its == want[1], every
+        assert np.array_equal(x, want[0]), every
+    lat.close()
