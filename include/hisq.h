@@ -465,8 +465,8 @@ hisq_status hisq_fermion_force_links(hisq_lattice lat, int n, const double *alph
  * runs through the Naik product, the second fat7 level, the U(3) projection
  * and the first level.  U is smeared first and the result loaded as the
  * lattice's links (as hisq_smear_links with HISQ_LOAD_RESULT would).
- * Workspace: 106 link-direction fields (144 P bytes each, P as for
- * hisq_smear_links: 16.0 GB at 32^4)
+ * Workspace: 104 link-direction fields (144 P bytes each, P as for
+ * hisq_smear_links: 15.7 GB at 32^4)
  * and 2 n V/2 vectors, kept until hisq_destroy.  Errors: HISQ_ERR_ARG, HISQ_ERR_BREAKDOWN (a level-1 link
  * has no U(3) projection; the lattice keeps the links it had),
  * HISQ_ERR_OOM / HISQ_ERR_HIP. */

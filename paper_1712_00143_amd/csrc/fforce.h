@@ -27,32 +27,41 @@ struct OuterArgs {
 };
 hipError_t launch_ff_outer(const SmearGeom &g, const OuterArgs &a, hipStream_t s);
 
-// Adjoint of the staple of M through direction d for output direction mu,
-//   T(x) = sum_s L_s(x) M_s(x+s) L_s(x+mu)^+   (s = +d, -d; L_{+d}(x) = U_d(x),
-//                                              L_{-d}(x) = U_d(x-d)^+),
-// for the gradient G_s of T (each sign its own field, the sum of G[s][0]
-// and, if not null, G[s][1]), scaled by c:
-//   GM[s] (= or +=)  the gradient with respect to M_s (GM[0] may equal GM[1]),
-//   GUd +=           the gradient with respect to the links U_d.
-// Sign index 0 is +d, 1 is -d; M[s] null leaves that sign out; GM[s] and
-// GUd may be null.  With one field for both signs (GM[0] == GM[1]) and Gb
-// not null, that field also receives gb Gb:
-//   GM = (gm_init ? 0 : GM) + gb Gb + c (adjoint),
-// the initial share a gradient field takes directly from G (the one-link
-// and lower staple terms), so that no separate pass writes it.
-struct StapleAdjArgs {
-    const double2 *Ud;
-    const double2 *M[2];
-    const double2 *G[2][2];
-    double2 *GM[2];
-    double2 *GUd;
-    double c;
-    int mu, d, gm_init;
-    int ord[4];
-    const double2 *Gb;
-    double gb;
+// Adjoint of a fat7 level (see smear.h for its fields): for the gradient G of F
+// (four fields), GU (four fields) += the gradient with respect to the links U.
+// T1, T2 (twelve fields, 3 mu + k) and, with a Lepage term, H (twenty-four) are
+// the forward intermediates, GT1, GT2 the gradients of T1, T2.
+//   top    from F_mu's last staples: GT2 and their share of GU;
+//   mid    the 5-link staples: GT1 from GT2 and G, and their share of GU; GT1
+//          may overwrite T2 (read by top only);
+//   split  (with a Lepage term) the gradients of the two signs of the 3-link
+//          staples, Gp over GT1 and Gm over anything else (T1 is free now);
+//   low    the shares of the 3-link staples (Gp = Gm = GT1 without a Lepage
+//          term) and of c1 U.
+struct AdjTopArgs {
+    const double2 *U, *G, *T2, *H;   // H null: no Lepage term
+    double2 *GT2, *GU;
+    double c5, c7, cL;
 };
-hipError_t launch_staple_adjoint(const SmearGeom &g, const StapleAdjArgs &a, hipStream_t s);
+struct AdjMidArgs {
+    const double2 *U, *G, *T1, *GT2;
+    double2 *GT1, *GU;
+    double c3;
+};
+struct AdjSplitArgs {
+    const double2 *U, *G;
+    double2 *Gp, *Gm;
+    double cL;
+};
+struct AdjLowArgs {
+    const double2 *U, *G, *Gp, *Gm;
+    double2 *GU;
+    double c1;
+};
+hipError_t launch_adj_top(const SmearGeom &g, const AdjTopArgs &a, hipStream_t s);
+hipError_t launch_adj_mid(const SmearGeom &g, const AdjMidArgs &a, hipStream_t s);
+hipError_t launch_adj_split(const SmearGeom &g, const AdjSplitArgs &a, hipStream_t s);
+hipError_t launch_adj_low(const SmearGeom &g, const AdjLowArgs &a, hipStream_t s);
 
 // GW += gradient of sum Re Tr(N_mu(x) GN_mu(x)), N_mu(x) = W_mu(x) W_mu(x+mu) W_mu(x+2mu)
 // (four-direction planar fields).

@@ -11,9 +11,9 @@
 // a closed-form adjoint from the Cayley-Hamilton form of (V^+ V)^{-1/2},
 // whose coefficients are symmetric functions of the singular values and
 // stay finite when they coincide.  Every kernel is an FP64 pass over planar
-// fields (one thread per site, except the staple adjoint's four waves per
-// 64 sites), bound by memory traffic and latency.
+// fields, bound by memory traffic and latency.
 #include "fforce.h"
+#include "gforce.h"
 #include "hisq_dev.h"
 #include "su3.h"
 
@@ -94,90 +94,291 @@ __global__ void __launch_bounds__(256) k_ff_outer(SmearGeom g, OuterArgs a)
     }
 }
 
-__device__ __forceinline__ M3 ld_grad(const double2 *const G[2], size_t V, long long s)
+// ---- adjoint of a fat7 level
+//
+// The staple of fields M+ (through +d) and M- (through -d) for output
+// direction mu,
+//   T(x) = U_d(x) M+(x+d) U_d(x+mu)^+ + U_d(x-d)^+ M-(x-d) U_d(x-d+mu),
+// has, for the gradients G+, G- of its two terms, the gather-form adjoint
+//   t+(z) = U_d(z-d+mu)^+ G+(z-d) U_d(z-d)        (with respect to M+)
+//   t-(z) = U_d(z+mu) G-(z+d) U_d(z)^+            (with respect to M-)
+//   u(z)  = M+(z+d) U_d(z+mu)^+ G+(z) + (G+(z-mu) U_d(z-mu) M+(z-mu+d))^+
+//         + (M-(z) U_d(z+mu) G-(z+d))^+ + G-(z-mu+d) U_d(z-mu)^+ M-(z-mu)
+// (with respect to U_d).  The passes below take every (mu, d) of a level at
+// once: a block holds 64 sites of an x-y-z slab and one wave per direction e
+// and walks a run of time slices; a wave gathers what every (mu, e) or (e, mu)
+// adds to its gradient fields in registers, so that each gradient field is read
+// and written once per pass and the four waves share what they gather through
+// L1 / L2.  (One launch per (mu, d) and sign pair, each updating its link
+// gradient in memory, took 108 launches and 27 ms of the force at 32^4.)
+//
+// What bounds them is traffic beyond L2: a site's fields here are 3 to 10 KB,
+// so that the sites 256 CUs hold at once exceed the L2s, and every extra site
+// in flight costs refetched neighbours.  One wave per SIMD with a term's six to
+// ten matrices requested before its first product (loads_first) therefore
+// beats two waves with a few each: mid 1.77 against 2.11 ms at 32^4.
+
+// Positions of the adjoint of (mu, d) at one site.
+struct StapNb {
+    int s, pd, md, pm, mm, md_pm, mm_pd;
+};
+
+__device__ __forceinline__ StapNb stap_nb(const SmearGeom &g, int s, const int x[4], int mu, int d)
 {
-    M3 m = ld(G[0], V, s);
-    if (G[1]) m = add(m, ld(G[1], V, s));
+    StapNb n;
+    const int Sm = pick(g.S, mu), Lm = pick(g.L, mu), xm = pick(x, mu);
+    const int Sd = pick(g.S, d), Ld = pick(g.L, d), xd = pick(x, d);
+    n.s = s;
+    n.pd = shift(s, xd, Sd, Ld, 1);
+    n.md = shift(s, xd, Sd, Ld, -1);
+    n.pm = shift(s, xm, Sm, Lm, 1);
+    n.mm = shift(s, xm, Sm, Lm, -1);
+    n.md_pm = shift(n.md, xm, Sm, Lm, 1);
+    n.mm_pd = shift(n.mm, xd, Sd, Ld, 1);
+    return n;
+}
+
+// The w-th direction other than e, and the index of direction d among those
+// other than mu (fields 3 mu + k hold (mu, d)).
+__device__ __forceinline__ int other_dir(int w, int e) { return w + (w >= e ? 1 : 0); }
+__device__ __forceinline__ int other_idx(int d, int mu) { return d - (d > mu ? 1 : 0); }
+
+// Block index -> tile and time slices of the walk; wave -> direction.
+struct AdjWalk {
+    int e, t0, t1, i;
+    bool valid;
+    int x[4];
+};
+
+__device__ __forceinline__ AdjWalk adj_walk(const SmearGeom &g, int ntile, int tch)
+{
+    AdjWalk w;
+    const int lb = xcd_tile(blockIdx.x, gridDim.x, 1);
+    const int chunk = lb / ntile, tile = brick_tile(lb - chunk * ntile, g);
+    w.e = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    w.i = tile * 64 + (int)(threadIdx.x & 63);
+    w.valid = w.i < g.S[3];
+    unsigned q = w.valid ? (unsigned)w.i : 0u;
+    w.x[0] = (int)(q % (unsigned)g.L[0]);
+    q /= (unsigned)g.L[0];
+    w.x[1] = (int)(q % (unsigned)g.L[1]);
+    w.x[2] = (int)(q / (unsigned)g.L[1]);
+    w.x[3] = 0;
+    w.t0 = chunk * tch;
+    w.t1 = w.t0 + tch < g.L[3] ? w.t0 + tch : g.L[3];
+    return w;
+}
+
+__device__ __forceinline__ M3 scaled(double k, M3 m)
+{
+    scale3(m, k);
     return m;
 }
 
-// A block holds 64 sites and four waves with one share of the work each, so
-// that each carries a short chain of loads and products (one thread doing all
-// of it needs over 200 registers and leaves two waves per SIMD): waves 0 and
-// 1 the + and - staples' gradients with respect to M, waves 2 and 3 their
-// shares of the gradient with respect to U_d, each pair summed through LDS.
-__global__ void __launch_bounds__(256) k_staple_adjoint(SmearGeom g, StapleAdjArgs a)
+// GU(s) += u.
+__device__ __forceinline__ void add_to(double2 *GU, size_t V, int s, const M3 &u)
 {
-    const int lane = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long vi = (long long)xcd_tile(blockIdx.x, gridDim.x, 1) * 64 + lane;
-    const bool valid = vi < g.V;
-    const size_t V = (size_t)g.P;   // plane stride
-    const bool plus = a.M[0] != nullptr, minus = a.M[1] != nullptr;
-    const bool gm = a.GM[0] || a.GM[1], gm_one = a.GM[0] == a.GM[1];
-    long long s = 0, pd = 0, md = 0, pm = 0, mm = 0, md_pm = 0, mm_pd = 0;
-    if (valid) {
-        int c[4];
-        s = walk((unsigned)vi, g, a.ord, c);
-        const int Sm = pick(g.S, a.mu), Lm = pick(g.L, a.mu), xm = coord(c, a.ord, a.mu);
-        const int Sd = pick(g.S, a.d), Ld = pick(g.L, a.d), xd = coord(c, a.ord, a.d);
-        pd = shift(s, xd, Sd, Ld, 1);
-        md = shift(s, xd, Sd, Ld, -1);
-        pm = shift(s, xm, Sm, Lm, 1);
-        mm = shift(s, xm, Sm, Lm, -1);
-        md_pm = shift(md, xm, Sm, Lm, 1);
-        mm_pd = shift(mm, xd, Sd, Ld, 1);
-    }
-    // gradient with respect to M_s(y): the + staple at x = y - d and the -
-    // staple at x = y + d read it.  U_d(z) is the first link of the + staple
-    // at z and of the - staple at z + d, the last link of the + staple at
-    // z - mu and of the - staple at z - mu + d.
-    M3 t = zero3();
-    if (valid) {
-        if (role == 0) {
-            if (plus && a.GM[0]) t = mul_nn(mul_an(ld(a.Ud, V, md_pm), ld_grad(a.G[0], V, md)), ld(a.Ud, V, md));
-        } else if (role == 1) {
-            if (minus && a.GM[1]) t = mul_na(mul_nn(ld(a.Ud, V, pm), ld_grad(a.G[1], V, pd)), ld(a.Ud, V, s));
-        } else if (role == 2) {
-            if (plus && a.GUd) {
-                t = mul_nn(mul_na(ld(a.M[0], V, pd), ld(a.Ud, V, pm)), ld_grad(a.G[0], V, s));
-                t = add(t, dag(mul_nn(mul_nn(ld_grad(a.G[0], V, mm), ld(a.Ud, V, mm)), ld(a.M[0], V, mm_pd))));
+    stb(GU, V, s, add(ldb_nt(GU, V, s), u));
+}
+
+#define ADJ_KERNEL __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+
+// The last staples of a level: F_mu holds the staple through d of
+// c7 T2_(mu,d) + cL H+-_(mu,d) (the 7-link and, at level 2, the Lepage
+// staples: one transported field, one set of products) and c5 T2_(mu,d).
+// Wave: link direction e = d, every mu in turn.
+template <bool LEP>
+ADJ_KERNEL k_adj_top(SmearGeom g, AdjTopArgs a, int ntile, int tch)
+{
+    AdjWalk w = adj_walk(g, ntile, tch);
+    if (!w.valid) return;
+    const size_t V = (size_t)g.P, fsz = 9 * V;
+    const int e = w.e;
+    const double2 *U = a.U + e * fsz;
+#pragma unroll 1
+    for (int t = w.t0; t < w.t1; t++) {
+        w.x[3] = t;
+        const int s = w.i + t * g.S[3];
+        M3 u = zero3();
+#pragma unroll 1
+        for (int k = 0; k < 3; k++) {
+            const int mu = other_dir(k, e), f = 3 * mu + other_idx(e, mu);
+            const double2 *G = a.G + mu * fsz, *T2 = a.T2 + f * fsz;
+            const double2 *Hp = LEP ? a.H + 2 * f * fsz : nullptr, *Hm = LEP ? Hp + fsz : nullptr;
+            const StapNb n = stap_nb(g, s, w.x, mu, e);
+            // c7 T2 + cL H, from loads already issued
+            auto field = [&](M3 t2, const M3 &h) {
+                scale3(t2, a.c7);
+                if constexpr (LEP) axpy(t2, a.cL, h);
+                return t2;
+            };
+            auto half = [&](const double2 *h, int y) { return LEP ? ldb(h, V, y) : M3(); };
+            const M3 Gs = ldb(G, V, s);
+            {
+                const M3 Upm = ldb(U, V, n.pm), Gpd = ldb(G, V, n.pd), T2s = ldb(T2, V, s), Hs = half(Hm, s);
+                const M3 Us = ldb(U, V, s), Udp = ldb(U, V, n.md_pm), Gmd = ldb(G, V, n.md), Umd = ldb(U, V, n.md);
+                loads_first();
+                const M3 Q = mul_nn(Upm, Gpd);
+                u = add(u, dag(mul_nn(field(T2s, Hs), Q)));
+                const M3 tm = mul_na(Q, Us);
+                const M3 tp = mul_nn(mul_an(Udp, Gmd), Umd);
+                M3 gt = scaled(a.c5, Gs);
+                axpy(gt, a.c7, add(tp, tm));
+                stb(a.GT2 + f * fsz, V, s, gt);
             }
-        } else {
-            if (minus && a.GUd) {
-                t = dag(mul_nn(mul_nn(ld(a.M[1], V, s), ld(a.Ud, V, pm)), ld_grad(a.G[1], V, pd)));
-                t = add(t, mul_nn(mul_na(ld_grad(a.G[1], V, mm_pd), ld(a.Ud, V, mm)), ld(a.M[1], V, mm)));
+            loads_first();
+            {
+                const M3 Upm = ldb(U, V, n.pm), Tpd = ldb(T2, V, n.pd), Hpd = half(Hp, n.pd);
+                const M3 Gmm = ldb(G, V, n.mm), Umm = ldb(U, V, n.mm), Tmp = ldb(T2, V, n.mm_pd), Hmp = half(Hp, n.mm_pd);
+                const M3 Gmp = ldb(G, V, n.mm_pd), Tmm = ldb(T2, V, n.mm), Hmm = half(Hm, n.mm);
+                loads_first();
+                u = add(u, mul_nn(mul_na(field(Tpd, Hpd), Upm), Gs));
+                u = add(u, dag(mul_nn(mul_nn(Gmm, Umm), field(Tmp, Hmp))));
+                u = add(u, mul_nn(mul_na(Gmp, Umm), field(Tmm, Hmm)));
             }
         }
+        add_to(a.GU + e * fsz, V, s, u);
     }
-    // separate gradient fields per sign: each of waves 0 and 1 writes its own
-    if (valid && gm && !gm_one && role < 2) {
-        double2 *f = a.GM[role];
-        if (f && (role == 0 ? plus : minus)) {
-            M3 out = a.gm_init ? zero3() : ld(f, V, s);
-            axpy(out, a.c, t);
-            st(f, V, s, out);
+}
+
+// t+ and t- of the adjoint of (mu, d) at n, from the fields of G+ and G-.
+__device__ __forceinline__ void adj_halves(const double2 *U, const double2 *Gp, const double2 *Gm, size_t V,
+                                           const StapNb &n, M3 &tp, M3 &tm)
+{
+    const M3 a = ldb(U, V, n.md_pm), p = ldb(Gp, V, n.md), b = ldb(U, V, n.md);
+    const M3 c = ldb(U, V, n.pm), m = ldb(Gm, V, n.pd), d = ldb(U, V, n.s);
+    loads_first();
+    tp = mul_nn(mul_an(a, p), b);
+    tm = mul_na(mul_nn(c, m), d);
+}
+__device__ __forceinline__ M3 adj_field(const double2 *U, const double2 *Gp, const double2 *Gm, size_t V,
+                                        const StapNb &n)
+{
+    M3 tp, tm;
+    adj_halves(U, Gp, Gm, V, n, tp, tm);
+    return add(tp, tm);
+}
+
+// GT1_(mu,j) = c3 G_mu + the adjoints of the two 5-link staples that transport
+// T1_(mu,j): through x of T2_(mu,y) and through y of T2_(mu,x), {x, y} the
+// other two directions.  Wave: mu, every j in turn.
+ADJ_KERNEL k_adj_mid(SmearGeom g, AdjMidArgs a, int ntile, int tch)
+{
+    AdjWalk w = adj_walk(g, ntile, tch);
+    if (!w.valid) return;
+    const size_t V = (size_t)g.P, fsz = 9 * V;
+    const int mu = w.e;
+#pragma unroll 1
+    for (int t = w.t0; t < w.t1; t++) {
+        w.x[3] = t;
+        const int s = w.i + t * g.S[3];
+        const M3 Gs = scaled(a.c3, ldb(a.G + mu * fsz, V, s));
+#pragma unroll 1
+        for (int j = 0; j < 3; j++) {
+            const int kx = j == 0 ? 1 : 0, ky = j == 2 ? 1 : 2;
+            M3 o = Gs;
+#pragma unroll 1
+            for (int q = 0; q < 2; q++) {
+                const int d = other_dir(q ? ky : kx, mu);
+                const double2 *G = a.GT2 + (3 * mu + (q ? kx : ky)) * fsz;
+                o = add(o, adj_field(a.U + d * fsz, G, G, V, stap_nb(g, s, w.x, mu, d)));
+            }
+            stb(a.GT1 + (3 * mu + j) * fsz, V, s, o);
         }
     }
-    __shared__ double2 red[2][9][64];   // the partials of waves 1 and 3
-    if (role & 1)
-#pragma unroll
-        for (int i = 0; i < 9; i++) red[role >> 1][i][lane] = t.e[i];
-    __syncthreads();
-    if (!valid) return;
-    if (role == 0 && gm && gm_one) {
-        M3 out = a.gm_init ? zero3() : ld(a.GM[0], V, s);
-        if (a.Gb) axpy(out, a.gb, ld(a.Gb, V, s));
-#pragma unroll
-        for (int i = 0; i < 9; i++) t.e[i] = make_double2(t.e[i].x + red[0][i][lane].x, t.e[i].y + red[0][i][lane].y);
-        axpy(out, a.c, t);
-        st(a.GM[0], V, s, out);
+}
+
+// With a Lepage term the two signs of the 3-link staple (mu, j) have their own
+// gradients: H+-_(mu,j) is transported through j into F_mu, so they are
+// GT1_(mu,j) + cL t+- of G_mu (the first over GT1, the second to Gm).  Wave:
+// mu, every j in turn.
+ADJ_KERNEL k_adj_split(SmearGeom g, AdjSplitArgs a, int ntile, int tch)
+{
+    AdjWalk w = adj_walk(g, ntile, tch);
+    if (!w.valid) return;
+    const size_t V = (size_t)g.P, fsz = 9 * V;
+    const int mu = w.e;
+    const double2 *G = a.G + mu * fsz;
+#pragma unroll 1
+    for (int t = w.t0; t < w.t1; t++) {
+        w.x[3] = t;
+        const int s = w.i + t * g.S[3];
+#pragma unroll 1
+        for (int j = 0; j < 3; j++) {
+            const int d = other_dir(j, mu);
+            double2 *Gp = a.Gp + (3 * mu + j) * fsz;
+            const M3 o = ldb_nt(Gp, V, s);
+            M3 tp, tm, p = o, m = o;
+            adj_halves(a.U + d * fsz, G, G, V, stap_nb(g, s, w.x, mu, d), tp, tm);
+            axpy(p, a.cL, tp);
+            axpy(m, a.cL, tm);
+            stb(Gp, V, s, p);
+            stb(a.Gm + (3 * mu + j) * fsz, V, s, m);
+        }
     }
-    if (role == 2 && a.GUd) {
-#pragma unroll
-        for (int i = 0; i < 9; i++) t.e[i] = make_double2(t.e[i].x + red[1][i][lane].x, t.e[i].y + red[1][i][lane].y);
-        M3 out = ld(a.GUd, V, s);
-        axpy(out, a.c, t);
-        st(a.GUd, V, s, out);
+}
+
+// u of the adjoint of (mu, d) for M+ = M- = M.
+__device__ __forceinline__ void adj_link(M3 &u, const double2 *U, const double2 *M, const double2 *Gp,
+                                         const double2 *Gm, size_t V, const StapNb &n)
+{
+    const M3 Upm = ldb(U, V, n.pm), Mpd = ldb(M, V, n.pd), Gs = ldb(Gp, V, n.s);
+    const M3 Ms = ldb(M, V, n.s), Gpd = ldb(Gm, V, n.pd);
+    const M3 Umm = ldb(U, V, n.mm), Gmm = ldb(Gp, V, n.mm), Mmp = ldb(M, V, n.mm_pd);
+    const M3 Gmp = ldb(Gm, V, n.mm_pd), Mmm = ldb(M, V, n.mm);
+    loads_first();
+    u = add(u, mul_nn(mul_na(Mpd, Upm), Gs));
+    u = add(u, dag(mul_nn(mul_nn(Ms, Upm), Gpd)));
+    u = add(u, dag(mul_nn(mul_nn(Gmm, Umm), Mmp)));
+    u = add(u, mul_nn(mul_na(Gmp, Umm), Mmm));
+}
+
+// The 5-link staples' share of the gradient of the links of direction e
+// (wave): those through e of every mu in turn.
+ADJ_KERNEL k_adj_mid_links(SmearGeom g, AdjMidArgs a, int ntile, int tch)
+{
+    AdjWalk w = adj_walk(g, ntile, tch);
+    if (!w.valid) return;
+    const size_t V = (size_t)g.P, fsz = 9 * V;
+    const int e = w.e;
+#pragma unroll 1
+    for (int t = w.t0; t < w.t1; t++) {
+        w.x[3] = t;
+        const int s = w.i + t * g.S[3];
+        M3 u = zero3();
+#pragma unroll 1
+        for (int k = 0; k < 6; k++) {
+            const int mu = other_dir(k >> 1, e), ke = other_idx(e, mu);
+            const int ka = ke == 0 ? 1 : 0, kb = ke == 2 ? 1 : 2;
+            const double2 *M = a.T1 + (3 * mu + (k & 1 ? kb : ka)) * fsz, *G = a.GT2 + (3 * mu + (k & 1 ? ka : kb)) * fsz;
+            adj_link(u, a.U + e * fsz, M, G, G, V, stap_nb(g, s, w.x, mu, e));
+        }
+        add_to(a.GU + e * fsz, V, s, u);
+    }
+}
+
+// The rest of the gradient of the links of direction e (wave): for every mu in
+// turn the 3-link staples through e of U_mu and those of U_e through mu, and
+// c1 G_e.
+ADJ_KERNEL k_adj_low(SmearGeom g, AdjLowArgs a, int ntile, int tch)
+{
+    AdjWalk w = adj_walk(g, ntile, tch);
+    if (!w.valid) return;
+    const size_t V = (size_t)g.P, fsz = 9 * V;
+    const int e = w.e;
+#pragma unroll 1
+    for (int t = w.t0; t < w.t1; t++) {
+        w.x[3] = t;
+        const int s = w.i + t * g.S[3];
+        M3 u = scaled(a.c1, ldb(a.G + e * fsz, V, s));
+#pragma unroll 1
+        for (int k = 0; k < 3; k++) {
+            const int mu = other_dir(k, e), f = 3 * mu + other_idx(e, mu), fe = 3 * e + k;
+            u = add(u, adj_field(a.U + mu * fsz, a.Gp + fe * fsz, a.Gm + fe * fsz, V, stap_nb(g, s, w.x, e, mu)));
+            loads_first();
+            adj_link(u, a.U + e * fsz, a.U + mu * fsz, a.Gp + f * fsz, a.Gm + f * fsz, V, stap_nb(g, s, w.x, mu, e));
+        }
+        add_to(a.GU + e * fsz, V, s, u);
     }
 }
 
@@ -352,10 +553,47 @@ hipError_t launch_ff_outer(const SmearGeom &g, const OuterArgs &a, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_staple_adjoint(const SmearGeom &g, const StapleAdjArgs &a, hipStream_t s)
+// Blocks of the adjoint passes: 1024, four per CU one after the other (the
+// force at 32^4: 34.2 ms; 512 34.5, 2048 34.8, 8192 35.3).
+static int adj_grid(const SmearGeom &g, int *ntile, int *tch)
 {
-    if (!a.Ud || (!a.M[0] && !a.M[1]) || (a.M[0] && !a.G[0][0]) || (a.M[1] && !a.G[1][0])) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_staple_adjoint, dim3((unsigned)((g.V + 63) / 64)), dim3(256), 0, s, g, a);
+    int nb;
+    tile_grid(g, 1024, ntile, tch, &nb);
+    return nb;
+}
+
+hipError_t launch_adj_top(const SmearGeom &g, const AdjTopArgs &a, hipStream_t s)
+{
+    if (g.P >= BUF_MAX_P) return hipErrorInvalidValue;
+    int ntile, tch;
+    const int nb = adj_grid(g, &ntile, &tch);
+    if (a.H) hipLaunchKernelGGL((k_adj_top<true>), dim3(nb), dim3(256), 0, s, g, a, ntile, tch);
+    else hipLaunchKernelGGL((k_adj_top<false>), dim3(nb), dim3(256), 0, s, g, a, ntile, tch);
+    return hipGetLastError();
+}
+
+hipError_t launch_adj_mid(const SmearGeom &g, const AdjMidArgs &a, hipStream_t s)
+{
+    int ntile, tch;
+    const int nb = adj_grid(g, &ntile, &tch);
+    hipLaunchKernelGGL(k_adj_mid, dim3(nb), dim3(256), 0, s, g, a, ntile, tch);
+    hipLaunchKernelGGL(k_adj_mid_links, dim3(nb), dim3(256), 0, s, g, a, ntile, tch);
+    return hipGetLastError();
+}
+
+hipError_t launch_adj_split(const SmearGeom &g, const AdjSplitArgs &a, hipStream_t s)
+{
+    int ntile, tch;
+    const int nb = adj_grid(g, &ntile, &tch);
+    hipLaunchKernelGGL(k_adj_split, dim3(nb), dim3(256), 0, s, g, a, ntile, tch);
+    return hipGetLastError();
+}
+
+hipError_t launch_adj_low(const SmearGeom &g, const AdjLowArgs &a, hipStream_t s)
+{
+    int ntile, tch;
+    const int nb = adj_grid(g, &ntile, &tch);
+    hipLaunchKernelGGL(k_adj_low, dim3(nb), dim3(256), 0, s, g, a, ntile, tch);
     return hipGetLastError();
 }
 

@@ -76,9 +76,8 @@ hisq_status get_work(hisq_lattice lat, int nf, Work &w, size_t extra = 0)
 }
 
 // out (4 planar fields) = fat7(U (4 planar fields)): one pass 1 for every
-// direction, with a Lepage term one Lepage pass, then per output direction
-// one pass 2 (its 5-staple sums) and one pass 3 (their c5 share and the
-// 7-staples).  T1all: 12 fields (every direction's 3-staples).  Hall: 24
+// direction, then per output direction one pass 2 (its 5-staple sums) and one
+// pass 3 (their c5 share, the 7-staples and the Lepage term).  T1all: 12 fields (every direction's 3-staples).  Hall: 24
 // fields for the single-sign 3-staples, needed when cL != 0 (and kept for
 // the adjoint).  keep: T2all holds 12 fields and direction mu's 5-staple
 // sums stay in its fields 3 mu .. 3 mu + 2 (for the adjoint); otherwise
@@ -90,16 +89,12 @@ hipError_t run_fat7(const SmearGeom &g, const double2 *U, double2 *out, double2 
     if (lep && !Hall) return hipErrorInvalidValue;
     Pass1Args p1{U, out, need5 ? T1all : nullptr, lep ? Hall : nullptr, c[0], c[1]};
     hipError_t e = launch_smear_pass1(g, p1, s);
-    if (e == hipSuccess && lep) {
-        const LepageArgs la{U, Hall, out, c[4]};
-        e = launch_smear_lepage(g, la, s);
-    }
-    if (e != hipSuccess || !need5) return e;
+    if (e != hipSuccess || !(need5 || lep)) return e;
     for (int mu = 0; mu < 4; mu++) {
-        double2 *T2 = keep ? T2all + (size_t)3 * mu * fsz : T2all;
+        double2 *T2 = !need5 ? nullptr : keep ? T2all + (size_t)3 * mu * fsz : T2all;
         const Pass2Args p2{U, T1all + (size_t)3 * mu * fsz, T2, mu};
-        if ((e = launch_smear_pass2(g, p2, s)) != hipSuccess) return e;
-        const Pass3Args p3{U, T2, out + (size_t)mu * fsz, c[2], c[3], mu};
+        if (need5 && (e = launch_smear_pass2(g, p2, s)) != hipSuccess) return e;
+        const Pass3Args p3{U, T2, lep ? Hall : nullptr, out + (size_t)mu * fsz, c[2], c[3], c[4], mu};
         if ((e = launch_smear_pass3(g, p3, s)) != hipSuccess) return e;
     }
     return hipSuccess;
@@ -298,93 +293,22 @@ hisq_status hisq_gauge_action(hisq_lattice lat, const double *U, double beta, co
 
 namespace {
 
-// Gradient of sum Re Tr(fat7(Ul; c)_mu(x) G_mu(x)) with respect to Ul, added
-// to GU (four planar fields each): every pass is undone by its gather-form
-// adjoint, reading the forward intermediates run_fat7 kept (T1all, T2all:
-// 12 fields each; Hall: the 24 single-sign 3-staples of the Lepage term,
-// needed when cL != 0).  sc: 6 scratch fields.
-hipError_t fat7_adjoint(const SmearGeom &g, const double2 *Ul, const double c[5], const double2 *G, double2 *GU,
-                        const double2 *T1all, const double2 *T2all, const double2 *Hall, double2 *sc, size_t fsz,
-                        hipStream_t s)
+// Gradient of sum Re Tr(fat7(U; c)_mu(x) G_mu(x)) with respect to U, added to
+// GU (four planar fields each), from the forward intermediates run_fat7 kept
+// (T1, T2: 12 fields each, T2 overwritten and, with a Lepage term, T1; H: the
+// 24 single-sign 3-staples, null without a Lepage term).  GT2: 12 scratch
+// fields.
+hipError_t fat7_adjoint(const SmearGeom &g, const double2 *U, const double c[5], const double2 *G, double2 *GU,
+                        double2 *T1, double2 *T2, const double2 *H, double2 *GT2, hipStream_t s)
 {
-    double2 *GT1 = sc, *GT2 = sc + 3 * fsz, *GHp = sc + 4 * fsz, *GHm = sc + 5 * fsz;
-    const bool need5 = c[2] != 0.0 || c[3] != 0.0, lep = c[4] != 0.0;
-    if (lep && !Hall) return hipErrorInvalidValue;
-    hipError_t e;
-    auto U_ = [&](int d) { return Ul + (size_t)d * fsz; };
-    auto GU_ = [&](int d) { return GU + (size_t)d * fsz; };
-    // both signs of the staple through d, one field M, gradient Gin; with Gb,
-    // GM starts from gb Gb (gm_init) or adds it
-    auto adj = [&](int mu, int d, const double2 *M, const double2 *Gin, double2 *GM, double2 *GUd, double coef,
-                   const double2 *Gb = nullptr, double gb = 0.0, int init = 0) {
-        StapleAdjArgs a{U_(d), {M, M}, {{Gin, nullptr}, {Gin, nullptr}}, {GM, GM}, GUd, coef, mu, d, init, {}, Gb, gb};
-        const int f[2] = {d, mu};
-        smear_order(f, 2, a.ord);
-        return launch_staple_adjoint(g, a, s);
-    };
-    for (int mu = 0; mu < 4; mu++) {
-        int perp[3], np = 0;
-        for (int d = 0; d < 4; d++)
-            if (d != mu) perp[np++] = d;
-        const double2 *Gmu = G + (size_t)mu * fsz;
-        // forward intermediates: the kept 3- and 5-staple fields of this
-        // direction (and, for the Lepage term, its single-sign 3-staples)
-        const double2 *T1 = T1all + (size_t)3 * mu * fsz, *T2 = T2all + (size_t)3 * mu * fsz;
-        // reverse.  The direct shares of G_mu (c1 on U_mu, c3 on each T1,
-        // c5 on each T2) enter with the first pass that writes the gradient
-        // field (Gb / gb of the staple adjoint) instead of passes of their own.
-        if (need5) {
-            // the 3-staple gradients GT1_j are first written by the 5-staple
-            // adjoints of k = 0 (j = 1, 2) and k = 1 (j = 0)
-            bool gt1_set[3] = {false, false, false};
-            for (int k = 0; k < 3; k++) {
-                const int sig = perp[k], inu = (k + 1) % 3, irho = (k + 2) % 3;
-                const int nu = perp[inu], rho = perp[irho];
-                if (c[3] != 0.0) {
-                    if ((e = adj(mu, sig, T2 + k * fsz, Gmu, GT2, GU_(sig), c[3], Gmu, c[2], 1)) != hipSuccess) return e;
-                } else if ((e = launch_field_axpby(GT2, 0.0, Gmu, c[2], fsz, s)) != hipSuccess) {
-                    return e;
-                }
-                for (const int j : {inu, irho}) {
-                    // T1_nu is transported through rho and T1_rho through nu
-                    const int dj = j == inu ? rho : nu;
-                    const bool first = !gt1_set[j];
-                    gt1_set[j] = true;
-                    if ((e = adj(mu, dj, T1 + j * fsz, GT2, GT1 + j * fsz, GU_(dj), 1.0, first ? Gmu : nullptr,
-                                 first ? c[1] : 0.0, first ? 1 : 0)) != hipSuccess)
-                        return e;
-                }
-            }
-        } else {
-            for (int k = 0; k < 3; k++)
-                if ((e = launch_field_axpby(GT1 + k * fsz, 0.0, Gmu, c[1], fsz, s)) != hipSuccess) return e;
-        }
-        for (int k = 0; k < 3; k++) {
-            const int nu = perp[k];
-            // the one-link share c1 G_mu joins U_mu's gradient in its first pass
-            const double2 *gb = k == 0 ? Gmu : nullptr;
-            const double cb = k == 0 ? c[0] : 0.0;
-            if (!lep) {
-                if ((e = adj(mu, nu, U_(mu), GT1 + k * fsz, GU_(mu), GU_(nu), 1.0, gb, cb)) != hipSuccess) return e;
-                continue;
-            }
-            // Lepage = S+(H+) + S-(H-), S+- the single-sign staples through nu:
-            // first the gradients of H+- (and the links' share), then every
-            // staple of U_mu through nu at once (its 3-staple gradient GT1 on
-            // both signs, GH+- on one each)
-            const double2 *Hp = Hall + (size_t)(6 * mu + 2 * k) * fsz, *Hm = Hp + fsz;
-            StapleAdjArgs a1{U_(nu), {Hp, Hm}, {{Gmu, nullptr}, {Gmu, nullptr}}, {GHp, GHm}, GU_(nu), c[4], mu, nu, 1,
-                             {}};
-            StapleAdjArgs a2{U_(nu), {U_(mu), U_(mu)}, {{GT1 + k * fsz, GHp}, {GT1 + k * fsz, GHm}},
-                             {GU_(mu), GU_(mu)}, GU_(nu), 1.0, mu, nu, 0, {}, gb, cb};
-            const int f[2] = {nu, mu};
-            smear_order(f, 2, a1.ord);
-            smear_order(f, 2, a2.ord);
-            if ((e = launch_staple_adjoint(g, a1, s)) != hipSuccess) return e;
-            if ((e = launch_staple_adjoint(g, a2, s)) != hipSuccess) return e;
-        }
-    }
-    return hipSuccess;
+    const AdjTopArgs top{U, G, T2, H, GT2, GU, c[2], c[3], c[4]};
+    const AdjMidArgs mid{U, G, T1, GT2, T2, GU, c[1]};
+    const AdjSplitArgs split{U, G, T2, T1, c[4]};
+    const AdjLowArgs low{U, G, T2, H ? T1 : T2, GU, c[0]};
+    hipError_t e = launch_adj_top(g, top, s);
+    if (e == hipSuccess) e = launch_adj_mid(g, mid, s);
+    if (e == hipSuccess && H) e = launch_adj_split(g, split, s);
+    return e == hipSuccess ? launch_adj_low(g, low, s) : e;
 }
 
 hisq_status ff_check(hisq_lattice lat, int n, const double *alpha, const double *X, const void *out)
@@ -465,12 +389,14 @@ hisq_status hisq_fermion_force(hisq_lattice lat, const double *U, int n, const d
     if (!U) return set_err(lat, HISQ_ERR_ARG, "null argument");
     HIPCHK(lat, hipSetDevice(lat->device));
     const size_t vb = (size_t)n * lat->h * 3 * sizeof(double2);
-    // fields: U 0-3, level-1 sum 4-7, W 8-11, level-2 sum then GX 12-15, GN
-    // 16-19, GW 20-23, GU 24-27 (also the input and output staging), the
-    // kept 3- and 5-staples of level 1 28-51 and of level 2 52-75, the
-    // single-sign 3-staples of level 2 76-99, scratch 100-105
+    // fields: U 0-3, level-1 sum 4-7, W 8-11, level-2 sum then GX 12-15, GW
+    // 16-19, GN 20-23, GU 24-27 (also the input and output staging), 28-31
+    // spare, the kept 3- and 5-staples of level 1 32-55 and of level 2 56-79,
+    // the single-sign 3-staples of level 2 80-103.  The gradients of the
+    // 5-staples take 20-31 for level 2 (GN is used up by then) and 56-67 for
+    // level 1.
     Work w;
-    if ((st = get_work(lat, 106, w, 2 * vb + 64 * sizeof(double))) != HISQ_OK) return st;
+    if ((st = get_work(lat, 104, w, 2 * vb + 64 * sizeof(double))) != HISQ_OK) return st;
     const size_t fsz = w.fsz;
     const SmearGeom g = geom_of(lat);
     const bool dev = (flags & HISQ_DEVICE_PTR) != 0;
@@ -479,12 +405,12 @@ hisq_status hisq_fermion_force(hisq_lattice lat, const double *U, int n, const d
     const double2 *src;
     if ((st = stage_in(lat, U, flags, w.field(24), &src)) != HISQ_OK) return st;
     HIPCHK(lat, launch_smear_to_planar(g, src, w.field(0), lat->s));
-    HIPCHK(lat, run_fat7(g, w.field(0), w.field(4), w.field(28), w.field(40), nullptr, LV1, fsz, lat->s, true));
+    HIPCHK(lat, run_fat7(g, w.field(0), w.field(4), w.field(32), w.field(44), nullptr, LV1, fsz, lat->s, true));
     HIPCHK(lat, launch_field_axpby(w.field(8), 0.0, w.field(4), 1.0, 4 * fsz, lat->s));
     HIPCHK(lat, hipMemsetAsync(w.bad, 0, sizeof(int), lat->s));
     HIPCHK(lat, launch_smear_unitarize(g, w.field(8), w.bad, lat->s));
     if ((st = check_projection(lat, w.bad)) != HISQ_OK) return st;
-    HIPCHK(lat, run_fat7(g, w.field(8), w.field(12), w.field(52), w.field(64), w.field(76), LV2, fsz, lat->s, true));
+    HIPCHK(lat, run_fat7(g, w.field(8), w.field(12), w.field(56), w.field(68), w.field(80), LV2, fsz, lat->s, true));
     {
         const size_t bytes = link_array_bytes(lat);
         if (!lat->fat64) HIPCHK(lat, hipMalloc(&lat->fat64, bytes));
@@ -499,16 +425,16 @@ hisq_status hisq_fermion_force(hisq_lattice lat, const double *U, int n, const d
     HIPCHK(lat, hipMemcpyAsync(ad, alpha, n * sizeof(double), hipMemcpyHostToDevice, lat->s));
     if ((st = ff_solutions_odd(lat, n, Xd, Yd)) != HISQ_OK) return st;
     // gradients with respect to the level-2 sum (phases folded) and the Naik product
-    OuterArgs oa{Xd, Yd, ad, n, lat->h, w.field(12), w.field(16), 1, NAIK};
+    OuterArgs oa{Xd, Yd, ad, n, lat->h, w.field(12), w.field(20), 1, NAIK};
     HIPCHK(lat, launch_ff_outer(g, oa, lat->s));
-    HIPCHK(lat, hipMemsetAsync(w.field(20), 0, 4 * fsz * sizeof(double2), lat->s));
-    HIPCHK(lat, launch_ff_naik_adjoint(g, w.field(8), w.field(16), w.field(20), lat->s));
-    HIPCHK(lat, fat7_adjoint(g, w.field(8), LV2, w.field(12), w.field(20), w.field(52), w.field(64), w.field(76),
-                             w.field(100), fsz, lat->s));
-    HIPCHK(lat, launch_ff_unitarize_adjoint(g, w.field(4), w.field(20), lat->s));
+    HIPCHK(lat, hipMemsetAsync(w.field(16), 0, 4 * fsz * sizeof(double2), lat->s));
+    HIPCHK(lat, launch_ff_naik_adjoint(g, w.field(8), w.field(20), w.field(16), lat->s));
+    HIPCHK(lat, fat7_adjoint(g, w.field(8), LV2, w.field(12), w.field(16), w.field(56), w.field(68), w.field(80),
+                             w.field(20), lat->s));
+    HIPCHK(lat, launch_ff_unitarize_adjoint(g, w.field(4), w.field(16), lat->s));
     HIPCHK(lat, hipMemsetAsync(w.field(24), 0, 4 * fsz * sizeof(double2), lat->s));
-    HIPCHK(lat, fat7_adjoint(g, w.field(0), LV1, w.field(20), w.field(24), w.field(28), w.field(40), nullptr,
-                             w.field(100), fsz, lat->s));
+    HIPCHK(lat, fat7_adjoint(g, w.field(0), LV1, w.field(16), w.field(24), w.field(32), w.field(44), nullptr,
+                             w.field(56), lat->s));
     HIPCHK(lat, launch_ff_project(g, w.field(0), w.field(24), w.field(24), lat->s));
     if (dev) {
         HIPCHK(lat, launch_smear_from_planar(g, w.field(24), (double2 *)F, lat->s));

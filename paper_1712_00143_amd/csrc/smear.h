@@ -37,26 +37,19 @@ inline long long plane_stride(long long V)
 //                U_nu(x+mu)^+ and H-_k the -nu staple (nu = nu_k), stored for
 //                pass 2 as T1 field 3 mu + k, and with a Lepage term its
 //                halves as H fields 6 mu + 2 k (H+) and 6 mu + 2 k + 1 (H-);
-//   Lepage       (every mu in one launch) F_mu += cL sum over k of the
-//                staple through nu_k of H+_k (+ sign) and H-_k (- sign): the
-//                two-step staples;
 //   pass 2 (mu)  for each k, sig = nu_k and {nu, rho} the other two:
 //                T2_k = staple of T1_nu through rho + staple of T1_rho
 //                through nu (all 5-link staples whose steps avoid sig);
-//   pass 3 (mu)  F_mu += sum over k of c5 T2_k + c7 (staple of T2_k through
-//                sig) (the 7-link staples through sig).
+//   pass 3 (mu)  F_mu += sum over k of c5 T2_k + (the staple through sig of
+//                c7 T2_k + cL H+_k on the + side, c7 T2_k + cL H-_k on the
+//                - side): the 7-link staples through sig and the two-step
+//                (Lepage) staples.
 struct Pass1Args {
     const double2 *U;
     double2 *F;    // four fields
     double2 *T1;   // twelve fields, or null: not stored
     double2 *H;    // twenty-four fields, or null: not stored
     double c1, c3;
-};
-struct LepageArgs {
-    const double2 *U;
-    const double2 *H;   // the twenty-four H fields of pass 1
-    double2 *F;         // four fields, updated
-    double cL;
 };
 struct Pass2Args {
     const double2 *U;
@@ -66,22 +59,20 @@ struct Pass2Args {
 };
 struct Pass3Args {
     const double2 *U;
-    const double2 *T2;   // three fields
+    const double2 *T2;   // three fields, or null: no 5- and 7-link terms
+    const double2 *H;    // the twenty-four H fields of pass 1, or null: no Lepage term
     double2 *F;          // the field of mu
-    double c5, c7;
+    double c5, c7, cL;
     int mu;
 };
 
 hipError_t launch_smear_pass1(const SmearGeom &g, const Pass1Args &a, hipStream_t s);
-hipError_t launch_smear_lepage(const SmearGeom &g, const LepageArgs &a, hipStream_t s);
 hipError_t launch_smear_pass2(const SmearGeom &g, const Pass2Args &a, hipStream_t s);
 hipError_t launch_smear_pass3(const SmearGeom &g, const Pass3Args &a, hipStream_t s);
 
-// Visiting order x, then the directions of `first` (in that order, skipping
-// x and repeats), then the rest: the order in which the fermion force's
-// staple adjoints visit the sites (the smearing passes instead walk runs of
-// time slices per x-y-z tile).
-void smear_order(const int *first, int n, int ord[4]);
+// Grid of the passes that walk time slices, aimed at `target` blocks: ntile
+// tiles of 64 x-y-z sites times runs of tch time slices.
+void tile_grid(const SmearGeom &g, int target, int *ntile, int *tch, int *nblocks);
 
 // [V][4][3][3] complex (site-major) -> four-direction planar field.
 hipError_t launch_smear_to_planar(const SmearGeom &g, const double2 *aos, double2 *pl, hipStream_t s);

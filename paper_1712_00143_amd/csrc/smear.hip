@@ -24,38 +24,23 @@ namespace {
 // y, whose coordinates along that direction and along mu are yd and ym:
 // P = U(y) M(y+d) U(y+mu)^+, Q = U(y-d)^+ M(y-d) U(y-d+mu).
 __device__ __forceinline__ void staple_halves(const double2 *__restrict__ U, const double2 *__restrict__ M, size_t V,
-                                              long long y, int yd, int S, int L, int ym, int Sm, int Lm, M3 &P, M3 &Q)
+                                              int y, int yd, int S, int L, int ym, int Sm, int Lm, M3 &P, M3 &Q)
 {
-    const long long pd = shift(y, yd, S, L, 1), md = shift(y, yd, S, L, -1);
-    const long long pm = shift(y, ym, Sm, Lm, 1), md_pm = shift(md, ym, Sm, Lm, 1);
-    P = mul_na(mul_nn(ld(U, V, y), ld(M, V, pd)), ld(U, V, pm));
-    Q = mul_nn(mul_an(ld(U, V, md), ld(M, V, md)), ld(U, V, md_pm));
+    const int pd = shift(y, yd, S, L, 1), md = shift(y, yd, S, L, -1);
+    const int pm = shift(y, ym, Sm, Lm, 1), md_pm = shift(md, ym, Sm, Lm, 1);
+    const M3 a = ldb(U, V, y), b = ldb(M, V, pd), c = ldb(U, V, pm);
+    const M3 d = ldb(U, V, md), e = ldb(M, V, md), f = ldb(U, V, md_pm);
+    loads_first();
+    P = mul_na(mul_nn(a, b), c);
+    Q = mul_nn(mul_an(d, e), f);
 }
 
 // The one-step staple P + Q of M through (S, L).
 __device__ __forceinline__ M3 staple_at(const double2 *__restrict__ U, const double2 *__restrict__ M, size_t V,
-                                        long long y, int yd, int S, int L, int ym, int Sm, int Lm)
+                                        int y, int yd, int S, int L, int ym, int Sm, int Lm)
 {
     M3 T, Q;
     staple_halves(U, M, V, y, yd, S, L, ym, Sm, Lm, T, Q);
-#pragma unroll
-    for (int i = 0; i < 9; i++) T.e[i] = make_double2(T.e[i].x + Q.e[i].x, T.e[i].y + Q.e[i].y);
-    return T;
-}
-
-// A staple through (S, L) whose two signs transport different fields:
-// U(y) Mp(y+d) U(y+mu)^+ + U(y-d)^+ Mm(y-d) U(y-d+mu).  With Mp, Mm the
-// single-sign 3-staples of U_mu through d this is the two-step (Lepage)
-// staple U(y) U(y+d) U_mu(y+2d) U(y+d+mu)^+ U(y+mu)^+ + (its -d image).
-// Every element of Mp and Mm is read by one site only: non-temporal loads.
-__device__ __forceinline__ M3 staple_pm(const double2 *__restrict__ U, const double2 *__restrict__ Mp,
-                                        const double2 *__restrict__ Mm, size_t V, long long y, int yd, int S, int L,
-                                        int ym, int Sm, int Lm)
-{
-    const long long pd = shift(y, yd, S, L, 1), md = shift(y, yd, S, L, -1);
-    const long long pm = shift(y, ym, Sm, Lm, 1), md_pm = shift(md, ym, Sm, Lm, 1);
-    M3 T = mul_na(mul_nn(ld(U, V, y), ld_nt(Mp, V, pd)), ld(U, V, pm));
-    const M3 Q = mul_nn(mul_an(ld(U, V, md), ld_nt(Mm, V, md)), ld(U, V, md_pm));
 #pragma unroll
     for (int i = 0; i < 9; i++) T.e[i] = make_double2(T.e[i].x + Q.e[i].x, T.e[i].y + Q.e[i].y);
     return T;
@@ -69,13 +54,18 @@ __device__ __forceinline__ M3 staple_pm(const double2 *__restrict__ U, const dou
 // staples through the three nu != mu, stored as T1[3 mu + k] when WT (and
 // their single-sign halves as H[6 mu + 2 k], H[6 mu + 2 k + 1] when WH), and
 //   F_mu = c1 U_mu + c3 sum_nu T1_nu.
+// All six matrices of a staple pair are requested before its products, one
+// wave per SIMD: at 32^4 0.95 ms (1.13 with two waves of fewer loads each, and
+// 1.05 with four matrices first), with the halves stored 1.47 ms (1.93, 1.84).
 template <bool WT, bool WH>
-__global__ void __launch_bounds__(256) k_smear_pass1(SmearGeom g, Pass1Args a, int ntile, int tch)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) k_smear_pass1(SmearGeom g,
+                                                                                               Pass1Args a, int ntile,
+                                                                                               int tch)
 {
     const int lb = xcd_tile(blockIdx.x, gridDim.x, 1);
     const int chunk = lb / ntile, tile = lb - chunk * ntile;
-    const long long i = (long long)tile * 64 + (threadIdx.x & 63);
-    if (i >= (long long)g.S[3]) return;   // no barriers below
+    const int i = tile * 64 + (threadIdx.x & 63);
+    if (i >= g.S[3]) return;   // no barriers below
     const size_t V = (size_t)g.P;   // plane stride
     const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int x[4];
@@ -92,9 +82,9 @@ __global__ void __launch_bounds__(256) k_smear_pass1(SmearGeom g, Pass1Args a, i
 #pragma unroll 1
     for (int t = t0; t < t1; t++) {
         x[3] = t;
-        const long long s = i + (long long)t * g.S[3];
+        const int s = i + t * g.S[3];
         const int xm = pick(x, mu);
-        M3 F = ld(Umu, V, s);
+        M3 F = ldb(Umu, V, s);
 #pragma unroll
         for (int e = 0; e < 9; e++) F.e[e] = make_double2(a.c1 * F.e[e].x, a.c1 * F.e[e].y);
         // one direction at a time: unrolled, the three staples' loads are all
@@ -108,59 +98,17 @@ __global__ void __launch_bounds__(256) k_smear_pass1(SmearGeom g, Pass1Args a, i
             if constexpr (WH) {
                 M3 Q;
                 staple_halves(Un, Umu, V, s, xn, Sn, Ln, xm, Sm, Lm, T, Q);
-                st(a.H + (size_t)(6 * mu + 2 * k) * 9 * V, V, s, T);
-                st(a.H + (size_t)(6 * mu + 2 * k + 1) * 9 * V, V, s, Q);
+                stb(a.H + (size_t)(6 * mu + 2 * k) * 9 * V, V, s, T);
+                stb(a.H + (size_t)(6 * mu + 2 * k + 1) * 9 * V, V, s, Q);
 #pragma unroll
                 for (int e = 0; e < 9; e++) T.e[e] = make_double2(T.e[e].x + Q.e[e].x, T.e[e].y + Q.e[e].y);
             } else {
                 T = staple_at(Un, Umu, V, s, xn, Sn, Ln, xm, Sm, Lm);
             }
             axpy(F, a.c3, T);
-            if constexpr (WT) st(a.T1 + (size_t)(3 * mu + k) * 9 * V, V, s, T);
+            if constexpr (WT) stb(a.T1 + (size_t)(3 * mu + k) * 9 * V, V, s, T);
         }
-        st(a.F + (size_t)mu * 9 * V, V, s, F);
-    }
-}
-
-// The Lepage term of every output direction, with the block grid of pass 1
-// (its tiles in the brick order of brick_tile, as in passes 2 and 3; pass 1
-// itself is 4 % faster in the plain order):
-//   F_mu += cL sum over nu != mu of staple_pm(U_nu; H+, H-),
-// H+- the single-sign 3-staples of U_mu through nu that pass 1 stored.
-__global__ void __launch_bounds__(256) k_smear_lepage(SmearGeom g, LepageArgs a, int ntile, int tch)
-{
-    const int lb = xcd_tile(blockIdx.x, gridDim.x, 1);
-    const int chunk = lb / ntile, tile = brick_tile(lb - chunk * ntile, g);
-    const long long i = (long long)tile * 64 + (threadIdx.x & 63);
-    if (i >= (long long)g.S[3]) return;   // no barriers below
-    const size_t V = (size_t)g.P;   // plane stride
-    const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int x[4];
-    {
-        unsigned r = (unsigned)i;
-        x[0] = (int)(r % (unsigned)g.L[0]);
-        r /= (unsigned)g.L[0];
-        x[1] = (int)(r % (unsigned)g.L[1]);
-        x[2] = (int)(r / (unsigned)g.L[1]);
-    }
-    const int t0 = chunk * tch, t1 = t0 + tch < g.L[3] ? t0 + tch : g.L[3];
-    const int Sm = pick(g.S, mu), Lm = pick(g.L, mu);
-    double2 *Fmu = a.F + (size_t)mu * 9 * V;
-#pragma unroll 1
-    for (int t = t0; t < t1; t++) {
-        x[3] = t;
-        const long long s = i + (long long)t * g.S[3];
-        const int xm = pick(x, mu);
-        M3 F = ld(Fmu, V, s);
-#pragma unroll 1
-        for (int k = 0; k < 3; k++) {
-            const int nu = k + (k >= mu ? 1 : 0);
-            const double2 *Hp = a.H + (size_t)(6 * mu + 2 * k) * 9 * V;
-            axpy(F, a.cL,
-                 staple_pm(a.U + (size_t)nu * 9 * V, Hp, Hp + 9 * V, V, s, pick(x, nu), pick(g.S, nu), pick(g.L, nu),
-                           xm, Sm, Lm));
-        }
-        st(Fmu, V, s, F);
+        stb(a.F + (size_t)mu * 9 * V, V, s, F);
     }
 }
 
@@ -184,9 +132,9 @@ __global__ void __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(1, 2))
     const int lb = xcd_tile(blockIdx.x, gridDim.x, 1);
     const int chunk = lb / ntile, tile = brick_tile(lb - chunk * ntile, g);
     const int lane = threadIdx.x & 63;
-    const long long i0 = (long long)tile * 64 + lane;
-    const bool valid = i0 < (long long)g.S[3];
-    const long long i = valid ? i0 : 0;
+    const int i0 = tile * 64 + lane;
+    const bool valid = i0 < g.S[3];
+    const int i = valid ? i0 : 0;
     const size_t V = (size_t)g.P;   // plane stride
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), mu = a.mu;
     const int k = w >> 1, second = w & 1;
@@ -209,8 +157,17 @@ __global__ void __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(1, 2))
 #pragma unroll 1
     for (int t = t0; t < t1; t++) {
         x[3] = t;
-        const long long s = i + (long long)t * g.S[3];
-        M3 T = staple_at(Ud, T1j, V, s, pick(x, dir), Sd, Ld, pick(x, mu), Sm, Lm);
+        const int s = i + t * g.S[3];
+        const int yd = pick(x, dir), ym = pick(x, mu);
+        const int pd = shift(s, yd, Sd, Ld, 1), md = shift(s, yd, Sd, Ld, -1);
+        const int pm = shift(s, ym, Sm, Lm, 1), md_pm = shift(md, ym, Sm, Lm, 1);
+        // four matrices in flight, the two last links loaded under the first
+        // products: two waves per SIMD (423 us; all six first 453, the
+        // compiler's own order 489)
+        const M3 ua = ldb(Ud, V, s), ma = ldb(T1j, V, pd), ub = ldb(Ud, V, md), mb = ldb(T1j, V, md);
+        loads_first();
+        M3 T = mul_na(mul_nn(ua, ma), ldb(Ud, V, pm));
+        T = add(T, mul_nn(mul_an(ub, mb), ldb(Ud, V, md_pm)));
         if (second)
 #pragma unroll
             for (int e = 0; e < 9; e++) red[k][e][lane] = T.e[e];
@@ -219,23 +176,33 @@ __global__ void __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(1, 2))
 #pragma unroll
             for (int e = 0; e < 9; e++)
                 T.e[e] = make_double2(T.e[e].x + red[k][e][lane].x, T.e[e].y + red[k][e][lane].y);
-            st(T2, V, s, T);
+            stb(T2, V, s, T);
         }
         __syncthreads();
     }
 }
 
-// Pass 3: F_mu += sum over sig of (c5 T2_k + c7 staple(T2_k through sig)),
-// the 7-link staples being the staples of the 5-link ones; the three waves'
-// terms meet in LDS and wave 0 updates F once, adding them in the order of k.
-__global__ void __launch_bounds__(192) k_smear_pass3(SmearGeom g, Pass3Args a, int ntile, int tch)
+// Pass 3: F_mu += sum over sig of c5 T2_k + the staple through sig whose signs
+// transport c7 T2_k + cL H+_k and c7 T2_k + cL H-_k.  The first term of these
+// gives the 7-link staples (the staples of the 5-link ones); with H+-_k the
+// single-sign 3-staples of U_mu through sig, the second gives the two-step
+// (Lepage) staples U(y) U(y+d) U_mu(y+2d) U(y+d+mu)^+ U(y+mu)^+ + (its -d
+// image).  The staple is linear in what it transports, so one set of products
+// serves both (a Lepage pass of its own took 1.19 ms at 32^4, the two extra
+// fields 0.63 ms here).  T: T2 is read (5- and 7-link terms); H: the Lepage term.
+// The three waves' terms meet in LDS and wave 0 updates F once, adding them in
+// the order of k.
+template <bool T, bool H>
+__global__ void __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(1, 2))) k_smear_pass3(SmearGeom g,
+                                                                                               Pass3Args a, int ntile,
+                                                                                               int tch)
 {
     const int lb = xcd_tile(blockIdx.x, gridDim.x, 1);
     const int chunk = lb / ntile, tile = brick_tile(lb - chunk * ntile, g);
     const int lane = threadIdx.x & 63;
-    const long long i0 = (long long)tile * 64 + lane;
-    const bool valid = i0 < (long long)g.S[3];
-    const long long i = valid ? i0 : 0;
+    const int i0 = tile * 64 + lane;
+    const bool valid = i0 < g.S[3];
+    const int i = valid ? i0 : 0;
     const size_t V = (size_t)g.P;   // plane stride
     const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), mu = a.mu;
     const int sig = other_dir(k, mu);
@@ -248,32 +215,44 @@ __global__ void __launch_bounds__(192) k_smear_pass3(SmearGeom g, Pass3Args a, i
         x[2] = (int)(r / (unsigned)g.L[1]);
     }
     const int Sm = pick(g.S, mu), Lm = pick(g.L, mu), Ss = pick(g.S, sig), Ls = pick(g.L, sig);
-    const double2 *Us = a.U + (size_t)sig * 9 * V, *T2 = a.T2 + (size_t)k * 9 * V;
+    const double2 *Us = a.U + (size_t)sig * 9 * V, *T2 = T ? a.T2 + (size_t)k * 9 * V : nullptr;
+    const double2 *Hk = H ? a.H + (size_t)(6 * mu + 2 * k) * 9 * V : nullptr;
     double2 *F = a.F;
     __shared__ double2 red[2][9][64];
+    // the transported field of sign q (0: +, 1: -) at y
+    auto field = [&](int q, int y) {
+        M3 m = zero3();
+        if constexpr (T) axpy(m, a.c7, ldb(T2, V, y));
+        if constexpr (H) axpy(m, a.cL, ldb_nt(Hk + (size_t)q * 9 * V, V, y));
+        return m;
+    };
     const int t0 = chunk * tch, t1 = t0 + tch < g.L[3] ? t0 + tch : g.L[3];
 #pragma unroll 1
     for (int t = t0; t < t1; t++) {
         x[3] = t;
-        const long long s = i + (long long)t * g.S[3];
-        M3 T = zero3();
+        const int s = i + t * g.S[3];
+        M3 f = zero3();
         if (valid) {
-            axpy(T, a.c5, ld(T2, V, s));
-            axpy(T, a.c7, staple_at(Us, T2, V, s, pick(x, sig), Ss, Ls, pick(x, mu), Sm, Lm));
+            const int xs = pick(x, sig), xm = pick(x, mu);
+            const int pd = shift(s, xs, Ss, Ls, 1), md = shift(s, xs, Ss, Ls, -1);
+            const int pm = shift(s, xm, Sm, Lm, 1), md_pm = shift(md, xm, Sm, Lm, 1);
+            if constexpr (T) axpy(f, a.c5, ldb(T2, V, s));
+            f = add(f, mul_na(mul_nn(ldb(Us, V, s), field(0, pd)), ldb(Us, V, pm)));
+            f = add(f, mul_nn(mul_an(ldb(Us, V, md), field(1, md)), ldb(Us, V, md_pm)));
         }
         if (k > 0)
 #pragma unroll
-            for (int e = 0; e < 9; e++) red[k - 1][e][lane] = T.e[e];
+            for (int e = 0; e < 9; e++) red[k - 1][e][lane] = f.e[e];
         __syncthreads();
         if (k == 0 && valid) {
-            M3 f = ld(F, V, s);
+            M3 o = ldb(F, V, s);
 #pragma unroll
             for (int e = 0; e < 9; e++) {
-                f.e[e] = make_double2(f.e[e].x + T.e[e].x, f.e[e].y + T.e[e].y);
-                f.e[e] = make_double2(f.e[e].x + red[0][e][lane].x, f.e[e].y + red[0][e][lane].y);
-                f.e[e] = make_double2(f.e[e].x + red[1][e][lane].x, f.e[e].y + red[1][e][lane].y);
+                o.e[e] = make_double2(o.e[e].x + f.e[e].x, o.e[e].y + f.e[e].y);
+                o.e[e] = make_double2(o.e[e].x + red[0][e][lane].x, o.e[e].y + red[0][e][lane].y);
+                o.e[e] = make_double2(o.e[e].x + red[1][e][lane].x, o.e[e].y + red[1][e][lane].y);
             }
-            st(F, V, s, f);
+            stb(F, V, s, o);
         }
         __syncthreads();
     }
@@ -399,22 +378,9 @@ __global__ void __launch_bounds__(256) k_smear_unitarize(SmearGeom g, double2 *_
 
 }  // namespace
 
-void smear_order(const int *first, int n, int ord[4])
-{
-    bool used[4] = {true, false, false, false};
-    int k = 0;
-    ord[k++] = 0;
-    for (int i = 0; i < n; i++)
-        if (first[i] > 0 && first[i] < 4 && !used[first[i]]) {
-            used[first[i]] = true;
-            ord[k++] = first[i];
-        }
-    for (int d = 1; d < 4; d++)
-        if (!used[d]) ord[k++] = d;
-}
-
 hipError_t launch_smear_pass1(const SmearGeom &g, const Pass1Args &a, hipStream_t s)
 {
+    if (g.P >= BUF_MAX_P) return hipErrorInvalidValue;
     int ntile, tch, nb;
     gauge_force_grid(g, &ntile, &tch, &nb);
     const dim3 grid((unsigned)nb), blk(256);
@@ -426,19 +392,11 @@ hipError_t launch_smear_pass1(const SmearGeom &g, const Pass1Args &a, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_smear_lepage(const SmearGeom &g, const LepageArgs &a, hipStream_t s)
-{
-    int ntile, tch, nb;
-    gauge_force_grid(g, &ntile, &tch, &nb);
-    hipLaunchKernelGGL(k_smear_lepage, dim3((unsigned)nb), dim3(256), 0, s, g, a, ntile, tch);
-    return hipGetLastError();
-}
-
 // The tile grid of gauge_force_grid aimed at `target` blocks: fewer blocks
 // walk longer runs of time slices.  Passes 2 and 3 take 512 (at 32^4 every
 // block walks the whole time extent: pass 3 310 us against 322 with 2048
 // blocks, pass 2 unchanged).
-static void tile_grid(const SmearGeom &g, int target, int *ntile, int *tch, int *nblocks)
+void tile_grid(const SmearGeom &g, int target, int *ntile, int *tch, int *nblocks)
 {
     const long long nxyz = (long long)g.L[0] * g.L[1] * g.L[2];
     *ntile = (int)((nxyz + 63) / 64);
@@ -461,7 +419,10 @@ hipError_t launch_smear_pass3(const SmearGeom &g, const Pass3Args &a, hipStream_
 {
     int ntile, tch, nb;
     tile_grid(g, 512, &ntile, &tch, &nb);
-    hipLaunchKernelGGL(k_smear_pass3, dim3((unsigned)nb), dim3(192), 0, s, g, a, ntile, tch);
+    const dim3 grid((unsigned)nb), blk(192);
+    if (a.T2 && a.H) hipLaunchKernelGGL((k_smear_pass3<true, true>), grid, blk, 0, s, g, a, ntile, tch);
+    else if (a.T2) hipLaunchKernelGGL((k_smear_pass3<true, false>), grid, blk, 0, s, g, a, ntile, tch);
+    else if (a.H) hipLaunchKernelGGL((k_smear_pass3<false, true>), grid, blk, 0, s, g, a, ntile, tch);
     return hipGetLastError();
 }
 

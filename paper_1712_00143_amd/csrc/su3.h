@@ -50,6 +50,51 @@ __device__ __forceinline__ void st(double2 *__restrict__ f, size_t V, long long 
     }
 }
 
+// The same accesses through buffer resources, for the staple passes: a field's
+// base and the plane offsets live in scalar registers and a lane supplies one
+// 32-bit byte offset per site, where 64-bit per-lane addresses of 9 planes a
+// matrix took a fifth of the vector instructions and, hoisted out of the site
+// loops, enough registers to spill.  `f` must be the same for the whole
+// wavefront.  Two resources per field (planes 0-4 and 5-8) keep the plane
+// offsets below 2^32 up to P = 2^26 sites; the entry points that use these
+// keep at least 51 fields (144 P bytes each), so memory ends first.
+constexpr long long BUF_MAX_P = 1LL << 26;
+
+typedef unsigned int b128 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const double2 *f, size_t V, int half)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(f + (half ? 5 * V : 0)), (short)0, -1, 0x00020000);
+}
+
+template <int AUX> __device__ __forceinline__ M3 ldb_aux(const double2 *f, size_t V, int s)
+{
+    M3 m;
+    const unsigned pb = (unsigned)V * 16u;
+#pragma unroll
+    for (int i = 0; i < 9; i++)
+        m.e[i] = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(
+                                                 plane_rsrc(f, V, i >= 5), (int)((unsigned)s * 16u),
+                                                 (int)((unsigned)(i >= 5 ? i - 5 : i) * pb), AUX));
+    return m;
+}
+__device__ __forceinline__ M3 ldb(const double2 *f, size_t V, int s) { return ldb_aux<0>(f, V, s); }
+__device__ __forceinline__ M3 ldb_nt(const double2 *f, size_t V, int s) { return ldb_aux<2>(f, V, s); }
+
+__device__ __forceinline__ void stb(double2 *f, size_t V, int s, const M3 &m)
+{
+    const unsigned pb = (unsigned)V * 16u;
+#pragma unroll
+    for (int i = 0; i < 9; i++)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(b128, m.e[i]), plane_rsrc(f, V, i >= 5),
+                                               (int)((unsigned)s * 16u), (int)((unsigned)(i >= 5 ? i - 5 : i) * pb), 2);
+}
+
+// The loads written before this are issued before the products after it: the
+// scheduler would otherwise trade them for registers and leave two matrices in
+// flight where six fit.
+__device__ __forceinline__ void loads_first() { __builtin_amdgcn_sched_barrier(0); }
+
 // c = a b
 __device__ __forceinline__ M3 mul_nn(const M3 &a, const M3 &b)
 {
@@ -134,9 +179,9 @@ __device__ __forceinline__ int wrap(int v, int L)
 }
 
 // site x + k * dir, for x's coordinate xd along dir (|k| <= 2 L)
-__device__ __forceinline__ long long shift(long long s, int xd, int S, int L, int k)
+template <class I> __device__ __forceinline__ I shift(I s, int xd, int S, int L, int k)
 {
-    return s + (long long)(wrap(xd + k, L) - xd) * S;
+    return s + (I)(wrap(xd + k, L) - xd) * S;
 }
 
 __device__ __forceinline__ int pick(const int v[4], int d)
@@ -170,29 +215,6 @@ __device__ __forceinline__ M3 zero3()
 #pragma unroll
     for (int i = 0; i < 9; i++) c.e[i] = make_double2(0.0, 0.0);
     return c;
-}
-
-// Sites are visited in the order of the axis permutation o (o[0] = 0, x
-// fastest, so that a wavefront's loads stay contiguous): the host puts the
-// directions a pass steps along right after x, so that a site's neighbours
-// along them are visited, and held in L2 / the Infinity Cache, soon after it.
-// Returns lex(x) for visit index i and the coordinates c[k] along o[k].
-__device__ __forceinline__ long long walk(unsigned i, const SmearGeom &g, const int o[4], int c[4])
-{
-    const unsigned L0 = (unsigned)pick(g.L, o[0]), L1 = (unsigned)pick(g.L, o[1]), L2 = (unsigned)pick(g.L, o[2]);
-    c[0] = (int)(i % L0);
-    i /= L0;
-    c[1] = (int)(i % L1);
-    i /= L1;
-    c[2] = (int)(i % L2);
-    c[3] = (int)(i / L2);
-    return (long long)c[0] * pick(g.S, o[0]) + (long long)c[1] * pick(g.S, o[1]) + (long long)c[2] * pick(g.S, o[2]) +
-           (long long)c[3] * pick(g.S, o[3]);
-}
-
-__device__ __forceinline__ int coord(const int c[4], const int o[4], int d)
-{
-    return o[0] == d ? c[0] : o[1] == d ? c[1] : o[2] == d ? c[2] : c[3];
 }
 
 }  // namespace su3

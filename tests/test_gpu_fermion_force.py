@@ -132,6 +132,32 @@ def test_fermion_force_tiled_and_gauge_rotated(reps):
     lat.close()
 
 
+def test_fermion_force_uneven_time_runs_and_ragged_tile():
+    """(30, 22, 24, 14): the adjoint passes walk runs of 3, 3, 3, 3 and 2 time
+    slices and the last tile of a slab holds 32 of 64 sites.  A (6, 22, 4, 14)
+    field repeated along x and z and rotated by a random gauge transformation."""
+    import torch
+    H = _hisq()
+    small, reps = (6, 22, 4, 14), (5, 1, 6, 1)
+    dims = tuple(a * b for a, b in zip(small, reps))
+    Us = synth.thin_links(small, 0.4, 180)
+    xss = _vectors(small, 181)
+    g = synth.random_su3(synth.volume(dims), 182)
+    U = synth.gauge_transform(synth.tile_field(Us, small, reps), dims, g)
+    evs, ev = synth.even_sites(small), synth.even_sites(dims)
+    xs = []
+    for x in xss:
+        full = np.zeros((synth.volume(small), 3), dtype=np.complex128)
+        full[evs] = x
+        xs.append(np.einsum("sij,sj->si", g[ev], synth.tile_field(full, small, reps)[ev]))
+    ref = g[:, None] @ synth.tile_field(oracle.hisq_fermion_force(small, Us, ALPHAS, xss), small, reps) @ _dag(g)[:, None]
+    lat = H.Lattice(dims)
+    F = lat.fermion_force(torch.from_numpy(U.view(np.float64)).cuda(), ALPHAS,
+                          torch.from_numpy(np.stack(xs).view(np.float64)).cuda())
+    check(_links(F.cpu().numpy().view(np.complex128)), _links(ref), 1e-12, ("force", dims))
+    lat.close()
+
+
 def test_bad_arguments():
     H = _hisq()
     dims = (4, 4, 4, 4)
