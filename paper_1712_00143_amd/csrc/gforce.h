@@ -43,4 +43,8 @@ __device__ __forceinline__ int brick_tile(int tile, const SmearGeom &g)
 
 hipError_t launch_gauge_force(const SmearGeom &g, const GForceArgs &a, int mode, hipStream_t s);
 
+// The force (mode 0) with U and F in parity-split planes (the slots of
+// launch_smear_to_planar's split order), for P < BUF_MAX_P.
+hipError_t launch_gauge_force_even(const SmearGeom &g, const GForceArgs &a, hipStream_t s);
+
 }  // namespace hisq

@@ -6,7 +6,9 @@
 // the force on U_mu(x) is (beta/3) TA[U_mu(x) B^+], B the weighted sum of
 // the paths from x to x+mu that close each loop through the link.
 //
-// One thread per link, the whole staple sum in registers:
+// The force comes from k_gauge_force_even (below).  The action, and the force
+// of lattices beyond its 32-bit offsets, from the direct sum: one thread per
+// link, the whole staple sum in registers:
 // 6 signed transverse steps n, each giving the plaquette and the three
 // rectangles (11 products with the shared prefix and suffix factored out),
 // and 24 parallelograms (b, a, mu, -b, -a), summed over b before the common
@@ -198,6 +200,229 @@ __global__ void __launch_bounds__(256) k_gauge_force(SmearGeom g, GForceArgs a)
     }
 }
 
+// ---- the force around even sites
+//
+// Every loop of the action alternates between even and odd sites.  With the
+// eight legs L_p(y) of a site (L_{+mu}(y) = U_mu(y), L_{-mu}(y) = U_mu(y-mu)^+)
+// the loops that turn (or go straight) from leg s to leg b at an even site c
+// close the path c+s -> c -> c+b along
+//   G_{s,b}(c) = cp L_s(c+b) L_{-b}(c+b+s)
+//              + sum_k w_k L_k(c+b) L_s(c+b+k) L_{-b}(c+b+k+s) L_{-k}(c+s+k)
+// over the six signed directions k other than -s and -b; w_k = cr (a rectangle)
+// where k is s or b or the pair is straight (s = -b, then no plaquette), cg (a
+// parallelogram) otherwise.  Every link has one even end, so
+//   A_b(c) = sum_{s != b} G_{s,b}(c) L_s(c)^+,   G_{b,s} = G_{s,b}^+,
+// is the whole staple sum of the link (c, c+b): the 28 pairs of an even site
+// cost 21 products each and give eight links, 74 products per link instead of
+// the 145 of the direct sum (k_gauge_force), and 98 matrix loads instead of 166.
+//
+// A block holds 64 even sites.  The 28 pairs fall into seven rounds of four
+// disjoint ones, one per wave, so that the waves add into the eight sums in LDS
+// without conflicts: the four straight pairs, then for each of the three ways
+// to pair the axes the two matchings of their legs.  Even and odd sites have
+// their own half of every plane, so that a wavefront's loads stay contiguous.
+// Bound by links fetched past L2 (7 TB/s).
+// (Storing the 28 corners L_s^+ L_b of every even site, 2.1 GB at 32^4, leaves
+// 50 products per link but took 7.4 ms: 98 corner loads a link miss L2.)
+//
+// Leg p: axis p >> 1, negative direction if p & 1; p ^ 1 is the opposite.
+
+// A lane's even site: its lex index and, in LDS (64 lanes apart), the lex
+// offsets of the steps -2 .. 2 along each axis (entry 5 a + k + 2), computed
+// once per block instead of with every load.
+struct EvenSite {
+    int lex;
+    const int *off;
+};
+
+// Block -> tile: the chip takes one run of `slice` tiles (a multiple of 8, about
+// four time slices) after the other, each XCD a contiguous part of it, so that
+// the neighbour links that miss L2 come from the Infinity Cache: with a
+// contiguous eighth of the lattice per XCD the slices in use are all over the
+// lattice (3 % slower at 32^4).
+__device__ __forceinline__ int slice_tile(int b, int nb, int slice)
+{
+    const int g0 = b / slice * slice;
+    return g0 + xcd_tile(b - g0, nb - g0 < slice ? nb - g0 : slice, 1);
+}
+
+// Slot of c + d (d uniform) in the parity-split planes: even sites first.
+__device__ __forceinline__ int split_slot(const SmearGeom &g, const EvenSite &e, const int d[4])
+{
+    int y = e.lex;
+#pragma unroll
+    for (int a = 0; a < 4; a++)
+        if (d[a]) y += e.off[(5 * a + d[a] + 2) * 64];
+    return (y >> 1) + (((d[0] ^ d[1] ^ d[2] ^ d[3]) & 1) ? (int)(g.V >> 1) : 0);
+}
+
+__device__ __forceinline__ void go(int d[4], int p)
+{
+    const int k = p & 1 ? -1 : 1;
+#pragma unroll
+    for (int a = 0; a < 4; a++) d[a] += (p >> 1) == a ? k : 0;
+}
+
+// L_p(c + d); the conjugate transpose is taken by reading the transposed
+// planes and flipping the sign of the imaginary parts.
+__device__ __forceinline__ M3 ld_leg(const SmearGeom &g, const double2 *U, const EvenSite &e, const int d0[4], int p)
+{
+    int d[4] = {d0[0], d0[1], d0[2], d0[3]};
+    const bool neg = p & 1;
+    if (neg) go(d, p);
+    const size_t V = (size_t)g.P;
+    const double2 *f = U + (size_t)(p >> 1) * 9 * V;
+    const unsigned pb = (unsigned)V * 16u, off = (unsigned)split_slot(g, e, d) * 16u, flip = neg ? 0x80000000u : 0u;
+    M3 m;
+#pragma unroll
+    for (int i = 0; i < 9; i++) {
+        const int q = neg ? 3 * (i % 3) + i / 3 : i, hi = q >= 5 ? 1 : 0;
+        b128 v = __builtin_bit_cast(b128, __builtin_amdgcn_raw_buffer_load_b128(plane_rsrc(f, V, hi), (int)off,
+                                                                              (int)((unsigned)(q - 5 * hi) * pb), 0));
+        v.w ^= flip;
+        m.e[i] = __builtin_bit_cast(double2, v);
+    }
+    return m;
+}
+
+// The path c+b -> k -> s -> -b -> -k -> c+s.
+struct Path4 {
+    M3 l[4];
+};
+__device__ __forceinline__ void ld_path(const SmearGeom &g, const double2 *U, const EvenSite &e, int s, int b, int k,
+                                        Path4 &p)
+{
+    int d[4] = {0, 0, 0, 0};
+    go(d, b);
+    p.l[0] = ld_leg(g, U, e, d, k);
+    go(d, k);
+    p.l[1] = ld_leg(g, U, e, d, s);
+    go(d, s);
+    p.l[2] = ld_leg(g, U, e, d, b ^ 1);
+    go(d, b ^ 1);
+    p.l[3] = ld_leg(g, U, e, d, k ^ 1);
+}
+__device__ __forceinline__ M3 product(const Path4 &p)
+{
+    return mul_nn(mul_nn(mul_nn(p.l[0], p.l[1]), p.l[2]), p.l[3]);
+}
+
+// acc (in LDS, 64 lanes apart) = or += m.
+__device__ __forceinline__ void lds_add(double2 *acc, bool first, const M3 &m)
+{
+#pragma unroll
+    for (int i = 0; i < 9; i++) {
+        double2 o = first ? make_double2(0.0, 0.0) : acc[i * 64];
+        acc[i * 64] = make_double2(o.x + m.e[i].x, o.y + m.e[i].y);
+    }
+}
+
+// Two groups of four waves take every other round, each with its own sums in
+// LDS (147 KB, one block per CU), added at the end: with four waves and two
+// blocks per CU the sites in flight, and with them the neighbour links fetched
+// again past L2, double (39 GB a launch at 32^4, 5.1 ms; 27 GB and 3.9 ms so;
+// the direct sum 6.3 ms, 5.9 with its loads first).
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_gauge_force_even(SmearGeom g, GForceArgs a, int slice)
+{
+    __shared__ double2 acc2[2][8 * 9 * 64];
+    __shared__ int off[20 * 64];
+    const int lane = threadIdx.x & 63, w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int half = w8 >> 2, w = w8 & 3;
+    double2 *acc = acc2[half];
+    const int cb0 = slice_tile(blockIdx.x, gridDim.x, slice) * 64 + lane;
+    const bool valid = cb0 < (int)(g.V >> 1);
+    EvenSite e;
+    {
+        int x[4];
+        unsigned q = valid ? 2u * (unsigned)cb0 : 0u;
+        e.lex = (int)q;
+        x[0] = (int)(q % (unsigned)g.L[0]);
+        q /= (unsigned)g.L[0];
+        x[1] = (int)(q % (unsigned)g.L[1]);
+        q /= (unsigned)g.L[1];
+        x[2] = (int)(q % (unsigned)g.L[2]);
+        x[3] = (int)(q / (unsigned)g.L[2]);
+        const int odd = (x[1] + x[2] + x[3]) & 1;
+        x[0] += odd;
+        e.lex += odd;
+        e.off = off + lane;
+        if (w8 < 4)
+#pragma unroll
+            for (int k = -2; k <= 2; k++)
+                off[(5 * w8 + k + 2) * 64 + lane] = shift(0, pick(x, w8), pick(g.S, w8), pick(g.L, w8), k);
+        __syncthreads();
+    }
+    const int zero[4] = {0, 0, 0, 0};
+#pragma unroll 1
+    for (int r0 = 0; r0 < 8; r0 += 2) {
+        const int r = r0 + half;
+        // round 0: the straight pair of axis w; then axes (0, t + 1) in waves 0
+        // and 1 and the other two in waves 2 and 3, legs of equal or of
+        // opposite signs
+        int s = 2 * w, b = 2 * w + 1;
+        const bool straight = r == 0;
+        if (!straight) {
+            const int t = (r - 1) >> 1, x = (r - 1) & 1;
+            const int i = w < 2 ? 0 : (t == 0 ? 2 : 1), j = w < 2 ? t + 1 : (t == 2 ? 2 : 3);
+            s = 2 * i + (w & 1);
+            b = 2 * j + ((w & 1) ^ x);
+        }
+        if (valid && r < 7) {
+            M3 G = zero3();
+            if (!straight) {
+                int d[4] = {0, 0, 0, 0};
+                go(d, b);
+                const M3 p0 = ld_leg(g, a.U, e, d, s);
+                go(d, s);
+                const M3 p1 = ld_leg(g, a.U, e, d, b ^ 1);
+                axpy(G, a.cp, mul_nn(p0, p1));
+            }
+#pragma unroll 1
+            for (int k = 0; k < 8; k++) {
+                if (k == (b ^ 1) || k == (s ^ 1)) continue;
+                const double wk = straight || k == b || k == s ? a.cr : a.cg;
+                if (wk == 0.0) continue;
+                Path4 p;
+                ld_path(g, a.U, e, s, b, k, p);
+                loads_first();
+                axpy(G, wk, product(p));
+            }
+            loads_first();
+            const M3 ls = ld_leg(g, a.U, e, zero, s), lb = ld_leg(g, a.U, e, zero, b);
+            lds_add(acc + b * 9 * 64 + lane, r0 == 0, mul_na(G, ls));
+            lds_add(acc + s * 9 * 64 + lane, r0 == 0, mul_an(G, dag(lb)));
+        }
+        __syncthreads();
+    }
+    if (!valid) return;
+    {
+        const int p = w8;
+        M3 A;
+#pragma unroll
+        for (int i = 0; i < 9; i++) {
+            const double2 u = acc2[0][(p * 9 + i) * 64 + lane], v = acc2[1][(p * 9 + i) * 64 + lane];
+            A.e[i] = make_double2(u.x + v.x, u.y + v.y);
+        }
+        // U_mu(c) A, or for the link U_mu(c-mu) = L_p(c)^+ its product with A^+
+        const M3 l = ld_leg(g, a.U, e, zero, p);
+        const M3 M = p & 1 ? mul_an(l, dag(A)) : mul_nn(l, A);
+        const double im3 = (M.e[0].y + M.e[4].y + M.e[8].y) * (1.0 / 3.0);
+        M3 F;
+#pragma unroll
+        for (int i = 0; i < 3; i++)
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                const double2 u = M.e[3 * i + j], v = M.e[3 * j + i];
+                F.e[3 * i + j] = make_double2(a.scale * 0.5 * (u.x - v.x),
+                                              a.scale * (0.5 * (u.y + v.y) - (i == j ? im3 : 0.0)));
+            }
+        int d[4] = {0, 0, 0, 0};
+        if (p & 1) go(d, p);
+        stb(a.F + (size_t)(p >> 1) * 9 * g.P, (size_t)g.P, split_slot(g, e, d), F);
+    }
+}
+
 }  // namespace
 
 void gauge_force_grid(const SmearGeom &g, int *ntile, int *tch, int *nblocks)
@@ -210,6 +435,14 @@ void gauge_force_grid(const SmearGeom &g, int *ntile, int *tch, int *nblocks)
     *tch = (g.L[3] + nchunk - 1) / nchunk;
     nchunk = (g.L[3] + *tch - 1) / *tch;
     *nblocks = *ntile * nchunk;
+}
+
+hipError_t launch_gauge_force_even(const SmearGeom &g, const GForceArgs &a, hipStream_t s)
+{
+    if (g.P >= BUF_MAX_P) return hipErrorInvalidValue;
+    const int per = (int)((g.S[3] / 2 + 63) / 64), slice = (4 * per + 7) / 8 * 8;
+    hipLaunchKernelGGL(k_gauge_force_even, dim3((unsigned)((g.V / 2 + 63) / 64)), dim3(512), 0, s, g, a, slice);
+    return hipGetLastError();
 }
 
 hipError_t launch_gauge_force(const SmearGeom &g, const GForceArgs &a0, int mode, hipStream_t s)

@@ -74,11 +74,18 @@ hipError_t launch_smear_pass3(const SmearGeom &g, const Pass3Args &a, hipStream_
 // tiles of 64 x-y-z sites times runs of tch time slices.
 void tile_grid(const SmearGeom &g, int target, int *ntile, int *tch, int *nblocks);
 
-// [V][4][3][3] complex (site-major) -> four-direction planar field.
-hipError_t launch_smear_to_planar(const SmearGeom &g, const double2 *aos, double2 *pl, hipStream_t s);
+// The staple passes address planes through buffer resources (su3.h), good for
+// plane strides below this many sites.
+constexpr long long BUF_MAX_P = 1LL << 26;
 
-// Planar four-direction field -> [V][4][3][3].
-hipError_t launch_smear_from_planar(const SmearGeom &g, const double2 *pl, double2 *aos, hipStream_t s);
+// [V][4][3][3] complex (site-major) -> four-direction planar field; split: the
+// even sites first in every plane (slot lex / 2), then the odd ones.
+hipError_t launch_smear_to_planar(const SmearGeom &g, const double2 *aos, double2 *pl, hipStream_t s,
+                                  bool split = false);
+
+// Planar four-direction field (split as above) -> [V][4][3][3].
+hipError_t launch_smear_from_planar(const SmearGeom &g, const double2 *pl, double2 *aos, hipStream_t s,
+                                    bool split = false);
 
 // Unitary polar factor W = V (V^+ V)^{-1/2} of every link of a four-direction
 // planar field, in place; *bad (device int) counts links whose V^+ V is not

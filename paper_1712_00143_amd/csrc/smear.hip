@@ -262,6 +262,19 @@ __global__ void __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(1, 2))
 // array is staged in LDS so that both sides move contiguous segments.
 constexpr int SB = 64;
 
+// Slot of site s in the parity-split planes.
+__device__ __forceinline__ long long split_of(const SmearGeom &g, long long s)
+{
+    unsigned q = (unsigned)s;
+    int par = (int)(q % (unsigned)g.L[0]);
+    q /= (unsigned)g.L[0];
+    par += (int)(q % (unsigned)g.L[1]);
+    q /= (unsigned)g.L[1];
+    par += (int)(q % (unsigned)g.L[2]) + (int)(q / (unsigned)g.L[2]);
+    return (s >> 1) + ((par & 1) ? g.V / 2 : 0);
+}
+
+template <bool SPLIT>
 __global__ void __launch_bounds__(256) k_smear_to_planar(SmearGeom g, const double2 *__restrict__ aos,
                                                          double2 *__restrict__ pl)
 {
@@ -274,12 +287,12 @@ __global__ void __launch_bounds__(256) k_smear_to_planar(SmearGeom g, const doub
     const long long s = s0 + sl;
     if (s >= g.V) return;
     const size_t V = (size_t)g.P;   // plane stride
-    double2 *f = pl + (size_t)d * 9 * V;
+    double2 *f = pl + (size_t)d * 9 * V + (SPLIT ? split_of(g, s) : s);
 #pragma unroll
-    for (int e = 0; e < 9; e++) f[e * V + s] = buf[(sl * 4 + d) * 9 + e];
+    for (int e = 0; e < 9; e++) f[e * V] = buf[(sl * 4 + d) * 9 + e];
 }
 
-template <int MODE>   // 0: plain conversion of X; 1: fat and Naik links with phases
+template <int MODE>   // 0: plain conversion of X (2: from parity-split planes); 1: fat and Naik links with phases
 __global__ void __launch_bounds__(256) k_smear_out(SmearGeom g, const double2 *__restrict__ X,
                                                    const double2 *__restrict__ W, double cN,
                                                    double2 *__restrict__ out0, double2 *__restrict__ out1)
@@ -297,7 +310,7 @@ __global__ void __launch_bounds__(256) k_smear_out(SmearGeom g, const double2 *_
     const int ph = d == 0 ? 0 : d == 1 ? x0 : d == 2 ? x0 + x1 : x0 + x1 + x2;
     const double eta = (MODE == 1 && (ph & 1)) ? -1.0 : 1.0;
     if (valid) {
-        const M3 m = ld(X + (size_t)d * 9 * V, V, s);
+        const M3 m = ld(X + (size_t)d * 9 * V, V, MODE == 2 ? split_of(g, s) : s);
 #pragma unroll
         for (int e = 0; e < 9; e++) buf[(sl * 4 + d) * 9 + e] = make_double2(eta * m.e[e].x, eta * m.e[e].y);
     }
@@ -426,16 +439,20 @@ hipError_t launch_smear_pass3(const SmearGeom &g, const Pass3Args &a, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_smear_to_planar(const SmearGeom &g, const double2 *aos, double2 *pl, hipStream_t s)
+hipError_t launch_smear_to_planar(const SmearGeom &g, const double2 *aos, double2 *pl, hipStream_t s, bool split)
 {
-    hipLaunchKernelGGL(k_smear_to_planar, dim3((unsigned)((g.V + SB - 1) / SB)), dim3(256), 0, s, g, aos, pl);
+    const dim3 grid((unsigned)((g.V + SB - 1) / SB)), blk(256);
+    if (split) hipLaunchKernelGGL(k_smear_to_planar<true>, grid, blk, 0, s, g, aos, pl);
+    else hipLaunchKernelGGL(k_smear_to_planar<false>, grid, blk, 0, s, g, aos, pl);
     return hipGetLastError();
 }
 
-hipError_t launch_smear_from_planar(const SmearGeom &g, const double2 *pl, double2 *aos, hipStream_t s)
+hipError_t launch_smear_from_planar(const SmearGeom &g, const double2 *pl, double2 *aos, hipStream_t s, bool split)
 {
-    hipLaunchKernelGGL((k_smear_out<0>), dim3((unsigned)((g.V + SB - 1) / SB)), dim3(256), 0, s, g, pl,
-                       (const double2 *)nullptr, 0.0, aos, (double2 *)nullptr);
+    const dim3 grid((unsigned)((g.V + SB - 1) / SB)), blk(256);
+    const double2 *none = nullptr;
+    if (split) hipLaunchKernelGGL((k_smear_out<2>), grid, blk, 0, s, g, pl, none, 0.0, aos, (double2 *)nullptr);
+    else hipLaunchKernelGGL((k_smear_out<0>), grid, blk, 0, s, g, pl, none, 0.0, aos, (double2 *)nullptr);
     return hipGetLastError();
 }
 

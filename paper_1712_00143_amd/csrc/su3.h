@@ -57,8 +57,8 @@ __device__ __forceinline__ void st(double2 *__restrict__ f, size_t V, long long 
 // loops, enough registers to spill.  `f` must be the same for the whole
 // wavefront.  Two resources per field (planes 0-4 and 5-8) keep the plane
 // offsets below 2^32 up to P = 2^26 sites; the entry points that use these
-// keep at least 51 fields (144 P bytes each), so memory ends first.
-constexpr long long BUF_MAX_P = 1LL << 26;
+// keep at least 51 fields (144 P bytes each), so memory ends first, or check it
+// (BUF_MAX_P).
 
 typedef unsigned int b128 __attribute__((ext_vector_type(4)));
 

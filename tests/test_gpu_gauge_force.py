@@ -94,3 +94,19 @@ def test_small_extents_are_refused():
     with pytest.raises(H.HisqError):
         lat.gauge_action(U, 6.0, ONE_LOOP)
     lat.close()
+
+
+@pytest.mark.parametrize("coefs", [(1.0, -0.08, -0.01), (0.0, 1.0, 0.0), (0.7, 0.0, 0.2)])
+@pytest.mark.parametrize("dims", [(6, 14, 10, 12), (10, 6, 12, 14), (34, 4, 4, 16), (8, 8, 8, 16), (8, 8, 8, 18)])
+def test_gauge_force_ragged_even_tiles(dims, coefs):
+    """The kernel around even sites takes tiles of 64 even sites in groups of
+    about four time slices; it serves lattices above 8192 sites.  The largest
+    that it does not take and, of those it takes, whole tiles (72, 68) and ragged
+    last ones (78.75), partial last groups, x extents that do not divide a tile, and the
+    loop classes switched off."""
+    H = _hisq()
+    U = synth.thin_links(dims, 0.4, 71)
+    lat = H.Lattice(dims)
+    F = lat.gauge_force(U, 6.5, coefs)
+    check(np.asarray(F).reshape(-1, 9), oracle.gauge_force(dims, U, 6.5, coefs).reshape(-1, 9), 1e-13, (dims, coefs))
+    lat.close()
