@@ -449,11 +449,25 @@ hisq_status hisq_prepare_links(hisq_lattice lat, hisq_prec prec, hisq_recon reco
 
 namespace hisq {
 
-static std::string dslash_tune_key(const hipDeviceProp_t &prop, int prec, int recon, int ntile, int nprob,
+// The architecture name of a device, read once per process: the properties
+// query costs more than a small launch.
+std::string arch_name(int device)
+{
+    static std::mutex mu;
+    static std::map<int, std::string> names;
+    std::lock_guard<std::mutex> lock(mu);
+    auto it = names.find(device);
+    if (it != names.end()) return it->second;
+    hipDeviceProp_t prop;
+    if (hipGetDeviceProperties(&prop, device) != hipSuccess) return std::string();
+    return names[device] = prop.gcnArchName;
+}
+
+static std::string dslash_tune_key(const std::string &arch, int prec, int recon, int ntile, int nprob,
                                    bool streamed = false)
 {
     std::ostringstream ks;
-    ks << (streamed ? "dslash3s:" : "dslash3:") << prop.gcnArchName << ":p" << prec << ":r" << recon << ":t" << ntile << ":n" << nprob;
+    ks << (streamed ? "dslash3s:" : "dslash3:") << arch << ":p" << prec << ":r" << recon << ":t" << ntile << ":n" << nprob;
     std::string key = ks.str();
     for (auto &ch : key)
         if (ch == ' ') ch = '_';
@@ -468,10 +482,10 @@ TuneChoice lookup_shape(hisq_lattice lat, int prec, int recon, int ntile, int np
     def.W = prec == 0 ? 8 : 4;
     def.remap = 1;
     if (Tuner::get().disabled()) return def;
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, lat->device) != hipSuccess) return def;
+    const std::string arch = arch_name(lat->device);
+    if (arch.empty()) return def;
     TuneChoice c;
-    return Tuner::get().lookup(dslash_tune_key(prop, prec, recon, ntile, nprob), c) ? c : def;
+    return Tuner::get().lookup(dslash_tune_key(arch, prec, recon, ntile, nprob), c) ? c : def;
 }
 
 // Default and tuned launch shape of the Dslash for a geometry.  streamed:
@@ -484,12 +498,18 @@ TuneChoice pick_shape(hisq_lattice lat, int prec, int recon, const ProbDesc *dde
     def.W = prec == 0 ? 8 : 4;
     def.remap = 1;
     if (no_tune || Tuner::get().disabled()) return def;
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, lat->device) != hipSuccess) return def;
-    std::string key = dslash_tune_key(prop, prec, recon, ntile, nprob);
-    const std::string skey = dslash_tune_key(prop, prec, recon, ntile, nprob, true);
+    // the lattice's own operator: the choice this handle already looked up
+    TuneChoice *own = nprob == 1 && ntile == lat->ntile ? &lat->shape[prec * 2 + (recon == 12)][streamed] : nullptr;
+    if (own && own->us > 0) return *own;
+    const std::string arch = arch_name(lat->device);
+    if (arch.empty()) return def;
+    std::string key = dslash_tune_key(arch, prec, recon, ntile, nprob);
+    const std::string skey = dslash_tune_key(arch, prec, recon, ntile, nprob, true);
     TuneChoice c;
-    if (Tuner::get().lookup(streamed ? skey : key, c)) return c;
+    if (Tuner::get().lookup(streamed ? skey : key, c)) {
+        if (own) *own = c;
+        return c;
+    }
     DVec in, out;
     if (dvec_alloc(in, prec, nsite) != hipSuccess || dvec_alloc(out, prec, nsite) != hipSuccess) {
         dvec_free(in);
@@ -653,15 +673,17 @@ TuneChoice pick_shape_mrhs(hisq_lattice lat, int prec, int recon, int nr, bool n
     def.W = prec == 0 ? 8 : 4;
     def.remap = 1;
     if (no_tune || Tuner::get().disabled() || nr < 1 || nr > 4) return def;
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, lat->device) != hipSuccess) return def;
+    TuneChoice *own = &lat->mrhs_shape[prec * 2 + (recon == 12)][nr - 1];
+    if (own->us > 0) return *own;
+    const std::string arch = arch_name(lat->device);
+    if (arch.empty()) return def;
     std::ostringstream ks;
-    ks << "mrhs2:" << prop.gcnArchName << ":p" << prec << ":r" << recon << ":t" << lat->ntile << ":nr" << nr;
+    ks << "mrhs2:" << arch << ":p" << prec << ":r" << recon << ":t" << lat->ntile << ":nr" << nr;
     std::string key = ks.str();
     for (auto &ch : key)
         if (ch == ' ') ch = '_';
     TuneChoice c;
-    if (Tuner::get().lookup(key, c)) return c;
+    if (Tuner::get().lookup(key, c)) return *own = c;
     DVec in, out;
     const int vprec = prec == 0 ? 0 : 1;   // FP64 vectors with FP64 links, FP32 otherwise
     if (dvec_alloc(in, vprec, lat->h * nr) != hipSuccess || dvec_alloc(out, vprec, lat->h * nr) != hipSuccess) {

@@ -128,10 +128,10 @@ PtcLaunch base_launch(hisq_lattice lat, int lslot)
 int pick_layer_waves(hisq_lattice lat, int lslot, int prec, int recon, bool w16, const void *w, int cin, int cout,
                      int in_zero, int npar, int batch, hipStream_t stream)
 {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, lat->device) != hipSuccess) return 9;
+    const std::string arch = arch_name(lat->device);
+    if (arch.empty()) return 9;
     char key[256];
-    snprintf(key, sizeof key, "ptc:%s:t%d:p%d:r%d:w%d:%dx%d:z%d:np%d:b%d", prop.gcnArchName, lat->ntile, prec, recon,
+    snprintf(key, sizeof key, "ptc:%s:t%d:p%d:r%d:w%d:%dx%d:z%d:np%d:b%d", arch.c_str(), lat->ntile, prec, recon,
              (int)w16, cin, cout, in_zero, npar, batch);
     std::string k(key);
     for (auto &ch : k)
@@ -305,10 +305,10 @@ hipError_t apply_net(hisq_ptc_s *n, hisq_lattice lat, int lslot, int prec, int r
 int pick_infer_waves(hisq_lattice lat, int lslot, int prec, int recon, const void *w16, int cin, int cout, int ik,
                      int ok, int npar, hipStream_t stream)
 {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, lat->device) != hipSuccess) return 3;
+    const std::string arch = arch_name(lat->device);
+    if (arch.empty()) return 3;
     char key[256];
-    snprintf(key, sizeof key, "ptcinf:%s:t%d:p%d:r%d:%dx%d:k%d%d:np%d", prop.gcnArchName, lat->ntile, prec, recon, cin,
+    snprintf(key, sizeof key, "ptcinf:%s:t%d:p%d:r%d:%dx%d:k%d%d:np%d", arch.c_str(), lat->ntile, prec, recon, cin,
              cout, ik, ok, npar);
     std::string k(key);
     for (auto &ch : k)

@@ -13,6 +13,8 @@ hisq_status adopt_device_links(hisq_lattice lat);
 namespace hisq {
 
 ProbDesc lattice_desc(hisq_lattice lat);
+// The architecture name of a device ("" if it cannot be read), queried once per process.
+std::string arch_name(int device);
 TuneChoice pick_shape(hisq_lattice lat, int prec, int recon, const ProbDesc *ddesc, const int *dt2p,
                       int ntile, long long nsite, int nprob, bool no_tune, bool streamed = false);
 // pick_shape's answer without timing: the cached tuned choice or the default.
