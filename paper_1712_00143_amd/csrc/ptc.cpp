@@ -103,10 +103,10 @@ hipError_t refresh_adjoint(hisq_ptc_s *n, hipStream_t s)
 {
     for (int l = 0; l < n->nlayer; l++) {
         hipError_t e = launch_ptc_adjoint(n->w32 + 2 * n->woff[l], n->chans[l], n->chans[l + 1],
-                                          n->wa32 + 2 * n->woff[l], s);
+                                          n->wa32 + 2 * n->woff[l], n->wa16 + 2 * n->woff[l], s);
         if (e != hipSuccess) return e;
     }
-    return launch_to_half(n->wa32, n->wa16, 2 * n->nw, s);
+    return hipSuccess;
 }
 
 PtcLaunch base_launch(hisq_lattice lat, int lslot)
@@ -118,87 +118,16 @@ PtcLaunch base_launch(hisq_lattice lat, int lslot)
     a.in_zero_par = -1;
     a.out_pstride = 2;
     a.g_pstride = 2;
+    a.batch = a.bper = 1;
     return a;
 }
 
-// Waves per block of the layer kernel (1, 3, 5 or 9, sharing the 9
-// transport paths) for this geometry, channel pair, batch and link format:
-// timed once on scratch activations, then cached.  Must not run under stream
-// capture.
-int pick_layer_waves(hisq_lattice lat, int lslot, int prec, int recon, bool w16, const void *w, int cin, int cout,
-                     int in_zero, int npar, int batch, hipStream_t stream)
+// Batch entries per block or unit: all of them where the nblk blocks of one
+// entry fill the device by themselves (want of them), else as few as do.
+int batch_chunk(long long nblk, int batch, long long want)
 {
-    const std::string arch = arch_name(lat->device);
-    if (arch.empty()) return 9;
-    char key[256];
-    snprintf(key, sizeof key, "ptc:%s:t%d:p%d:r%d:w%d:%dx%d:z%d:np%d:b%d", arch.c_str(), lat->ntile, prec, recon,
-             (int)w16, cin, cout, in_zero, npar, batch);
-    std::string k(key);
-    for (auto &ch : k)
-        if (ch == ' ') ch = '_';
-    TuneChoice c;
-    if (Tuner::get().lookup(k, c)) return c.W;
-    if (Tuner::get().disabled()) return 3;
-    const long long h = lat->h;
-    float *in = nullptr, *out = nullptr;
-    if (hipMalloc(&in, sizeof(float) * (size_t)batch * cin * 2 * h * 6) != hipSuccess ||
-        hipMalloc(&out, sizeof(float) * (size_t)batch * cout * 2 * h * 6) != hipSuccess) {
-        if (in) (void)hipFree(in);
-        return 9;
-    }
-    (void)hipMemsetAsync(in, 0, sizeof(float) * (size_t)batch * cin * 2 * h * 6, stream);
-    PtcLaunch a = base_launch(lat, lslot);
-    a.w = w;
-    a.in = in;
-    a.in_bstride = (long long)cin * 2 * h * 6;
-    a.in_zero_par = in_zero;
-    a.out = out;
-    a.out_bstride = (long long)cout * 2 * h * 6;
-    a.out_pstride = 2;
-    a.out_par0 = 0;
-    a.par_lo = 0;
-    hipEvent_t e0, e1;
-    (void)hipEventCreate(&e0);
-    (void)hipEventCreate(&e1);
-    TuneChoice best;
-    best.W = 9;
-    best.us = 1e30;
-    // three interleaved trials of every shape, each shape's best trial counts
-    // (a single short trial is at the mercy of clock ramps and neighbours)
-    const int Ws[4] = {1, 3, 5, 9};
-    double tbest[4] = {1e30, 1e30, 1e30, 1e30};
-    bool okw[4] = {true, true, true, true};
-    for (int j = 0; j < 4; j++)
-        for (int r = 0; r < 2 && okw[j]; r++)
-            okw[j] = launch_ptc_layer(prec, recon, w16, cin, cout, Ws[j], a, lat->ntile * npar, batch, stream) ==
-                     hipSuccess;
-    for (int trial = 0; trial < 3; trial++)
-        for (int j = 0; j < 4; j++) {
-            if (!okw[j]) continue;
-            const int reps = 10;
-            (void)hipEventRecord(e0, stream);
-            for (int r = 0; r < reps; r++)
-                (void)launch_ptc_layer(prec, recon, w16, cin, cout, Ws[j], a, lat->ntile * npar, batch, stream);
-            (void)hipEventRecord(e1, stream);
-            (void)hipEventSynchronize(e1);
-            float ms = 0;
-            (void)hipEventElapsedTime(&ms, e0, e1);
-            tbest[j] = std::min(tbest[j], 1000.0 * ms / reps);
-        }
-    for (int j = 0; j < 4; j++)
-        if (okw[j]) Tuner::get().note(k, Ws[j], 0, 0, tbest[j]);
-    for (int j = 0; j < 4; j++)
-        if (okw[j] && tbest[j] < best.us) {
-            best.us = tbest[j];
-            best.W = Ws[j];
-        }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    (void)hipFree(in);
-    (void)hipFree(out);
-    (void)hipGetLastError();
-    if (best.us < 1e29) Tuner::get().store(k, best);
-    return best.W;
+    const long long nchunk = std::min<long long>(batch, (want + nblk - 1) / nblk);
+    return (int)((batch + nchunk - 1) / nchunk);
 }
 
 // One layer application over output parities [plo, phi].  fz (may be null):
@@ -209,7 +138,6 @@ hipError_t run_layer(hisq_lattice lat, int lslot, int prec, int recon, bool w16,
                      int plo, int phi, int batch, hipStream_t stream, const PtcFuse *fz = nullptr,
                      const float *addin = nullptr, long long addin_bs = 0)
 {
-    const int W = pick_layer_waves(lat, lslot, prec, recon, w16, w, cin, cout, in_zero, phi - plo + 1, batch, stream);
     PtcLaunch a = base_launch(lat, lslot);
     if (fz) {
         a.gate = fz->gate;
@@ -232,7 +160,9 @@ hipError_t run_layer(hisq_lattice lat, int lslot, int prec, int recon, bool w16,
     a.out_par0 = plo;
     a.par_lo = plo;
     const int nblk = lat->ntile * (phi - plo + 1);
-    return launch_ptc_layer(prec, recon, w16, cin, cout, W, a, nblk, batch, stream);
+    a.batch = batch;
+    a.bper = batch_chunk(nblk, batch, LAYER_BLOCKS);
+    return launch_ptc_layer(prec, recon, w16, cin, cout, a, nblk, stream);
 }
 
 // Weight gradient of one layer application, summed over the output parities
@@ -250,11 +180,13 @@ hipError_t run_wgrad(hisq_ptc_s *n, hisq_lattice lat, int cin, int cout, const f
     a.g_bstride = g_bs;
     a.g_pstride = g_pstride;
     a.partials = n->part;
-    // one partial row per block; enough blocks to fill the device, at most one
-    // per work unit
-    const long long units = (long long)lat->ntile * g_pstride * batch;
+    // enough partial rows to fill the device, at most one per work unit
+    const long long tiles = (long long)lat->ntile * g_pstride;
+    a.batch = batch;
+    a.bper = batch_chunk(tiles, batch, WGRAD_UNITS);
+    const long long units = tiles * ((batch + a.bper - 1) / a.bper);
     const int nrow = (int)(units < WGRAD_ROWS ? units : WGRAD_ROWS);
-    hipError_t e = launch_ptc_wgrad(n->tprec, n->trecon, cin, cout, a, g_pstride, batch, nrow, s);
+    hipError_t e = launch_ptc_wgrad(n->tprec, n->trecon, cin, cout, a, g_pstride, nrow, s);
     if (e != hipSuccess) return e;
     return launch_ptc_wsum(n->part, nrow, cin, cout, gw, accumulate, s);
 }
@@ -1097,16 +1029,22 @@ hisq_status hisq_ptc_train(hisq_ptc n, int steps, int batch, double lr, unsigned
         if (st != HISQ_OK) return st;
         const long long hl = lat->h;
         const long long af = (long long)C * 2 * hl * 6;
-        std::vector<double> ee(batch);
-        for (int b = 0; b < batch; b++) {
-            const int i = (int)(rng() % (unsigned long long)pb.n);
-            HIPCHK(lat0, hipMemcpyAsync(rb + (size_t)b * hl * 6, pb.mem + (size_t)2 * i * hl * 6, hl * 24,
-                                        hipMemcpyDeviceToDevice, s));
-            HIPCHK(lat0, hipMemcpyAsync(eb + (size_t)b * hl * 6, pb.mem + ((size_t)2 * i + 1) * hl * 6, hl * 24,
-                                        hipMemcpyDeviceToDevice, s));
-            ee[b] = n->loss == HISQ_LOSS_ENERGY ? pb.er[i] : pb.ee[i];
+        // the drawn pairs, PTC_PAIRS of them per launch
+        for (int b = 0; b < batch; b += PTC_PAIRS) {
+            PtcPairs pr;
+            memset(&pr, 0, sizeof pr);
+            pr.n = std::min(batch - b, PTC_PAIRS);
+            pr.nv = hl * 3;
+            pr.mem = pb.mem;
+            pr.r = rb + (size_t)b * hl * 6;
+            pr.e = eb + (size_t)b * hl * 6;
+            pr.norm = n->dee + b;
+            for (int j = 0; j < pr.n; j++) {
+                pr.index[j] = (int)(rng() % (unsigned long long)pb.n);
+                pr.norm_of[j] = n->loss == HISQ_LOSS_ENERGY ? pb.er[pr.index[j]] : pb.ee[pr.index[j]];
+            }
+            HIPCHK(lat0, launch_ptc_pairs(pr, s));
         }
-        HIPCHK(lat0, hipMemcpyAsync(n->dee, ee.data(), sizeof(double) * batch, hipMemcpyHostToDevice, s));
         // forward half
         for (int l = 1; l <= nl; l++) {
             const bool first = l == 1;
@@ -1114,18 +1052,17 @@ hisq_status hisq_ptc_train(hisq_ptc n, int steps, int batch, double lr, unsigned
                                    first ? rb : acts[l - 1], first ? hl * 6 : af, first ? 1 : -1, acts[l], af, 2, 0, 1,
                                    batch, s));
         }
-        // adjoint half
+        // adjoint half; its last layer adds r: z = r + b_0
         for (int l = nl; l >= 1; l--) {
             const float *w = n->wa32 + 2 * n->woff[l - 1];
             if (l == 1)
                 HIPCHK(lat0, run_layer(lat, n->tslot(), n->tprec, n->trecon, false, w, n->chans[l], n->chans[l - 1], bs[1], af, -1, zb,
-                                       hl * 6, 1, 0, 0, batch, s));
+                                       hl * 6, 1, 0, 0, batch, s, nullptr, rb, hl * 6));
             else
                 HIPCHK(lat0, run_layer(lat, n->tslot(), n->tprec, n->trecon, false, w, n->chans[l], n->chans[l - 1], bs[l], af, -1, bs[l - 1],
                                        af, 2, 0, 1, batch, s));
         }
-        // z = r + E^+ b_0, then the loss and g_z = g_{b_0}
-        HIPCHK(lat0, launch_add_f32(zb, rb, (long long)batch * hl * 6, s));
+        // the loss and g_z = g_{b_0}
         const bool energy = n->loss == HISQ_LOSS_ENERGY;
         if (energy) {
             // D_eo D_oe z for A z = 4 m^2 z - D_eo D_oe z, on the FP32 operator
@@ -1148,7 +1085,6 @@ hisq_status hisq_ptc_train(hisq_ptc n, int steps, int batch, double lr, unsigned
         la.ee = n->dee;
         la.partials = n->part;
         HIPCHK(lat0, launch_ptc_loss(la, lat->ntile, batch, n->dloss + it, s));
-        HIPCHK(lat0, hipMemsetAsync(n->gw, 0, sizeof(double) * 2 * n->nw, s));
         // backward through the adjoint half
         const float *gcur = g0;
         long long g_bs = hl * 6;

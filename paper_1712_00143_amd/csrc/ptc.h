@@ -16,7 +16,7 @@ struct PtcLaunch {
     int out_pstride;         // parities stored per output channel (1 or 2)
     int out_par0;            // first stored output parity
     int par_lo;              // first output parity computed (grid: npar * ntile blocks)
-    int pad;
+    int batch, bper;         // batch entries, and how many of them one block (layer) or unit (weight gradient) takes
     const float *g;          // weight gradient: output gradient [B][Cout][g_pstride][h][3]
     long long g_bstride;
     int g_pstride, g_par0;
@@ -47,8 +47,14 @@ struct PtcFuse {
     int nt;
 };
 
-hipError_t launch_ptc_layer(int prec, int recon, bool w16, int cin, int cout, int W, const PtcLaunch &a, int nblk,
-                            int batch, hipStream_t s);
+hipError_t launch_ptc_layer(int prec, int recon, bool w16, int cin, int cout, const PtcLaunch &a, int nblk,
+                            hipStream_t s);
+
+// Blocks that a layer launch should have before its batch entries share blocks:
+// one full load of the 256 CUs at the three or four waves per SIMD that the
+// kernels' registers allow (16^4, batch 8: 1024 blocks 57 / 22 / 30 us for
+// 4->4 / 1->4 / 4->1, 2048 blocks 55 / 24 / 30, 4096 blocks 60 / 26 / 33)
+constexpr int LAYER_BLOCKS = 1024;
 
 // Inference layer with FP16 activation storage (ptc_infer.hip): activations
 // [2 parities][h][C][3] half2 plus one FP32 scale per (parity, site).
@@ -75,21 +81,36 @@ struct PtcInferLaunch {
 constexpr int PTC_MFMA = 0x100;
 hipError_t launch_ptc_infer(int prec, int recon, int cin, int cout, int ik, int ok, int W, const PtcInferLaunch &a,
                             int nblk, hipStream_t s);
-constexpr int WGRAD_ROWS = 1024;   // weight-gradient partial rows (blocks) at most
+// Weight-gradient partial rows at most (a multiple of the 8 XCDs): the 9 waves
+// of a row, in blocks of four, load the 256 CUs once at three waves per SIMD.
+// Units wanted before batch entries share one: the rows that take one unit more
+// than others then cost at most a tenth.
+constexpr int WGRAD_ROWS = 336, WGRAD_UNITS = 10 * WGRAD_ROWS;
 
-// Weight-gradient partials of npar output parities x batch entries, reduced
-// into nrow rows (one per block) of [9][cout][cin] complex FP64.
-hipError_t launch_ptc_wgrad(int prec, int recon, int cin, int cout, const PtcLaunch &a, int npar, int batch, int nrow,
+// Weight-gradient partials of npar output parities x a.batch entries, reduced
+// into nrow rows of [9][cout][cin] complex FP64.
+hipError_t launch_ptc_wgrad(int prec, int recon, int cin, int cout, const PtcLaunch &a, int npar, int nrow,
                            hipStream_t s);
 hipError_t launch_ptc_wsum(const double *partials, long long nrow, int cin, int cout, double *gw, int accumulate,
                            hipStream_t s);
+// Gather of drawn training pairs (r, e) and their normalisations.
+constexpr int PTC_PAIRS = 16;   // pairs per launch (their indices travel in the kernel arguments)
+struct PtcPairs {
+    const float *mem;        // pair j: r at 2j nv, e at (2j + 1) nv complex values
+    float *r, *e;            // [n][nv] complex
+    double *norm;            // [n]
+    long long nv;            // complex values of a vector
+    int n;
+    int index[PTC_PAIRS];
+    double norm_of[PTC_PAIRS];
+};
+hipError_t launch_ptc_pairs(const PtcPairs &a, hipStream_t s);
 hipError_t launch_ptc_loss(const PtcLaunch &a, int ntile, int batch, double *loss, hipStream_t s);
 hipError_t launch_adam(float *w, float *m, float *v, const double *g, int n, int step, float lr, __half *w16,
                        hipStream_t s);
-hipError_t launch_ptc_adjoint(const float *w, int cin, int cout, float *wadj, hipStream_t s);
+hipError_t launch_ptc_adjoint(const float *w, int cin, int cout, float *wadj, __half *wadj16, hipStream_t s);
 hipError_t launch_to_half(const float *w, __half *w16, int n, hipStream_t s);
 hipError_t launch_ptc_gadj(const double *gp, int cin_p, int cout_p, double *gw, hipStream_t s);
-hipError_t launch_add_f32(float *z, const float *r, long long n, hipStream_t s);
 
 // flexible CG vector kernels (FP32 vectors, complex FP64 scalars in SolveState::cplx)
 struct FcgLaunch {

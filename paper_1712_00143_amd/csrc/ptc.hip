@@ -19,10 +19,18 @@
 
 namespace hisq {
 
+// Weight idx (uniform over the wavefront) through the scalar cache: no kernel
+// writes the weights that it reads, which the address space tells the compiler
+// (in a loop with stores it would load them per lane otherwise).
 template <class WT> __device__ __forceinline__ float2 ldw(const void *w, int idx)
 {
-    if constexpr (sizeof(WT) == 2) return __half22float2(reinterpret_cast<const __half2 *>(w)[idx]);
-    else return reinterpret_cast<const float2 *>(w)[idx];
+    if constexpr (sizeof(WT) == 2) {
+        const uint32_t t = ((const __attribute__((address_space(4))) uint32_t *)w)[idx];
+        return __half22float2(__builtin_bit_cast(__half2, t));
+    } else {
+        const uint64_t t = ((const __attribute__((address_space(4))) uint64_t *)w)[idx];
+        return __builtin_bit_cast(float2, t);
+    }
 }
 
 // neighbour cb index of (co, lex) along mu by +-1
@@ -44,51 +52,64 @@ __device__ __forceinline__ bool path_live(const PtcLaunch &a, int par, int k)
     return k == 0 ? a.in_zero_par != par : a.in_zero_par != 1 - par;
 }
 
-// The loads of path k at output site (par, i): the input colour vectors of
-// CIN channels at the site (identity) or at its neighbour, and the packed
-// link.  k and par must be uniform over the wavefront (the link block is
-// addressed through a wave-uniform buffer resource).
-template <class LT, int R, int CIN>
-__device__ __forceinline__ void path_load(const ProbDesc &pd, const LinkSet &ls, int par, int i, const Coord &co,
-                                          int lex, int k, const float *in_b, RawLink<LT, R> &raw, float2 sv[CIN][3])
+// packed link direction of hop k: 4mu forward, 4mu + 1 backward
+__device__ __forceinline__ int path_dir(int k) { return 4 * ((k - 1) >> 1) + ((k - 1) & 1); }
+
+// The packed link of path k at output site (par, i); k and par must be uniform
+// over the wavefront (the link block is addressed through a wave-uniform
+// buffer resource).  The fat links are re-read by every layer of every
+// application: cached (temporal) loads.
+template <class LT, int R>
+__device__ __forceinline__ void path_link(const LinkSet &ls, int par, int i, int k, RawLink<LT, R> &raw)
 {
-    const long long h = pd.h;
-    int site = i, sp = par;
-    if (k != 0) {
-        const int mu = (k - 1) >> 1;
-        const bool fwd = ((k - 1) & 1) == 0;
-        site = nb1(co, lex, mu, fwd ? 1 : -1, pd.L[0], pd.L[1], pd.L[2], pd.L[3]);
-        sp = 1 - par;
-        using F = LinkFmt<LT, R>;
-        const int d = 4 * mu + (fwd ? 0 : 1);
-        // the fat links are re-read by every layer of every application: keep
-        // them cached (temporal loads)
-        load_link_raw_wave<LT, R, 1>((const char *)ls.ptr[par] + (size_t)d * ls.hs * F::BYTES, i, ls.hs, raw);
-    }
+    if (k == 0) return;
+    using F = LinkFmt<LT, R>;
+    load_link_raw_wave<LT, R, 1>((const char *)ls.ptr[par] + (size_t)path_dir(k) * ls.hs * F::BYTES, i, ls.hs, raw);
+}
+
+// The site that path k reads (on the other parity, except for the identity).
+__device__ __forceinline__ int path_site(const ProbDesc &pd, int i, const Coord &co, int lex, int k)
+{
+    return k == 0 ? i : nb1(co, lex, (k - 1) >> 1, (k & 1) ? 1 : -1, pd.L[0], pd.L[1], pd.L[2], pd.L[3]);
+}
+
+// NC colour vectors of one site: channel c of parity sp (of np stored ones)
+// starts at base + (c np + sp) h vectors.  A vector is 24 bytes at a stride of
+// 24: one 16-byte and one 8-byte access, with a uniform base per channel.
+typedef float f4a8 __attribute__((ext_vector_type(4), aligned(8)));
+
+template <int NC>
+__device__ __forceinline__ void load_site(const float *base, int np, int sp, long long h, int site, Cx<float> v[NC][3])
+{
 #pragma unroll
-    for (int c = 0; c < CIN; c++) {
-        const float2 *p = reinterpret_cast<const float2 *>(in_b) + ((c * 2 + sp) * h + site) * 3;
-#pragma unroll
-        for (int q = 0; q < 3; q++) sv[c][q] = p[q];
+    for (int c = 0; c < NC; c++) {
+        const char *p = reinterpret_cast<const char *>(base) + (c * np + sp) * h * 24;
+        const f4a8 t = *reinterpret_cast<const f4a8 *>(p + (unsigned)site * 24u);
+        const float2 u = *reinterpret_cast<const float2 *>(p + (unsigned)site * 24u + 16);
+        v[c][0] = {t.x, t.y};
+        v[c][1] = {t.z, t.w};
+        v[c][2] = {u.x, u.y};
     }
 }
 
-// The transported colour vectors v[c] of path k from what path_load fetched.
-template <class LT, int R, int CIN>
-__device__ __forceinline__ void path_apply(const LinkSet &ls, const Coord &co, int k, const RawLink<LT, R> &raw,
-                                           const float2 sv[CIN][3], Cx<float> v[CIN][3])
+__device__ __forceinline__ void store_vec(float2 *p, const Cx<float> v[3])
 {
-    if (k == 0) {
-#pragma unroll
-        for (int c = 0; c < CIN; c++)
-#pragma unroll
-            for (int q = 0; q < 3; q++) v[c][q] = {sv[c][q].x, sv[c][q].y};
-        return;
-    }
-    const int mu = (k - 1) >> 1;
-    const bool fwd = ((k - 1) & 1) == 0;
-    const int d = 4 * mu + (fwd ? 0 : 1);
-    Cx<float> u[3][3];
+    f4a8 t;
+    t.x = v[0].re;
+    t.y = v[0].im;
+    t.z = v[1].re;
+    t.w = v[1].im;
+    *reinterpret_cast<f4a8 *>(p) = t;
+    p[2] = make_float2(v[2].re, v[2].im);
+}
+
+// The matrix of hop k, T_k v = u v, from its packed form: the format's scale,
+// phase and the sign of the stored backward links (-F^+) included.
+template <class LT, int R>
+__device__ __forceinline__ void path_matrix(const LinkSet &ls, const Coord &co, int k, const RawLink<LT, R> &raw,
+                                            Cx<float> u[3][3])
+{
+    const int mu = (k - 1) >> 1, d = path_dir(k);
     decode_link<LT, R, float>(raw, u);
     float coef = 1.f;
     if constexpr (R == 12 || sizeof(LT) == 2) {
@@ -99,117 +120,165 @@ __device__ __forceinline__ void path_apply(const LinkSet &ls, const Coord &co, i
             coef = neg ? -coef : coef;
         }
     }
-    if (!fwd) coef = -coef;   // stored -F^+
+    if (d & 1) coef = -coef;
 #pragma unroll
-    for (int c = 0; c < CIN; c++) {
-        Cx<float> s3[3];
+    for (int r = 0; r < 3; r++)
 #pragma unroll
-        for (int q = 0; q < 3; q++) s3[q] = {sv[c][q].x, sv[c][q].y};
+        for (int c = 0; c < 3; c++) u[r][c] = {coef * u[r][c].re, coef * u[r][c].im};
+}
+
+// acc += w v for one colour vector
+__device__ __forceinline__ void mix_acc(const float2 w, const Cx<float> v[3], Cx<float> acc[3])
+{
 #pragma unroll
-        for (int r = 0; r < 3; r++) v[c][r] = {0.f, 0.f};
-        matvec_acc_scaled(u, s3, coef, v[c]);
+    for (int q = 0; q < 3; q++) {
+        acc[q].re = fmaa(-w.y, v[q].im, fmaa(w.x, v[q].re, acc[q].re));
+        acc[q].im = fmaa(w.y, v[q].re, fmaa(w.x, v[q].im, acc[q].im));
     }
 }
 
-// Forward layer (also the input-gradient layer, given the adjoint weights).
-template <class LT, int R, class WT, int CIN, int COUT, int W>
-__global__ void __launch_bounds__(64 * W) k_ptc_layer(PtcLaunch a)
+// Work unit of block j of n: blocks go round the 8 XCDs in order, so XCD j % 8
+// takes a contiguous eighth of the units, whose neighbours it then finds in
+// its own L2.  The last n % 8 units keep their place.
+__device__ __forceinline__ int xcd_unit(int j, int n)
+{
+    const int per = n >> 3;
+    return j < per * 8 ? (j & 7) * per + (j >> 3) : j;
+}
+
+// Forward layer (also the input-gradient layer, given the adjoint weights) of
+// a.bper batch entries per block of four waves: wave w takes the two hops along
+// direction w and every fourth input channel of the identity path, so that the
+// waves and the four SIMDs are evenly loaded (three waves of three paths each,
+// or nine of one, left a SIMD with half or twice the work of another).
+//
+// Issue of vector instructions bounds it: a 4 -> 4 layer needs 336 FP32
+// multiply-adds per site and hop, and unpacking and scaling the link took as
+// many again as a third of them.  So the links are unpacked once, with their
+// coefficient folded in, and stay in registers over the batch entries.  With
+// fewer outputs than inputs the channels are mixed first and COUT vectors
+// transported (the transport is linear).  The waves' outputs are joined
+// through LDS, channel c by wave c mod 4.
+//
+// 16^4, 8 entries, FP16 recon-12 links: 4 -> 4 70 -> 55 us, 4 -> 1 49 -> 29 us,
+// against one entry per block, three waves of three paths and the link
+// unpacked for each entry.  The matrix cores are no help: FP32 4x4x1 products
+// (nine cycles for what takes four multiply-adds) on the mixing gave 62 us.
+template <class LT, int R, class WT, int CIN, int COUT>
+__global__ void __launch_bounds__(256) k_ptc_layer(PtcLaunch a)
 {
     if (a.gate && a.gate->status != a.gate_want) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const ProbDesc &pd = a.probs[0];
     const int ntile = pd.ntile;
-    const int par = a.par_lo + blockIdx.x / ntile;
-    const int tile = blockIdx.x % ntile;
-    const int b = blockIdx.y;
-    const int i = tile * TILE + lane;
-    const bool valid = i < pd.h;
+    const int npar = gridDim.x / ntile;
+    const int unit = xcd_unit(blockIdx.x, gridDim.x);
+    const int par = a.par_lo + unit % npar, tile = unit / npar;
+    const bool valid = tile * TILE + lane < pd.h;
+    const int i = valid ? tile * TILE + lane : pd.h - 1;   // idle lanes repeat the last site
+    const long long h = pd.h;
     const LinkSet &ls = pd.ls[a.lslot];
-    const float *in_b = a.in + (size_t)b * a.in_bstride;
-    Cx<float> acc[COUT][3];
+    const Coord co = cb_to_coord_pd(i, par, pd);
+    const int lex = 2 * i + (co.x[0] & 1);
+    constexpr int W = 4, G = 8 / W;   // waves, hops of each
+    __shared__ float red[W * COUT * 6 * 64];
+    const bool hops = path_live(a, par, 1), ident = path_live(a, par, 0);
+    Cx<float> u[G][3][3];
+    int site[G];
+    if (hops) {
+        RawLink<LT, R> raw[G];
 #pragma unroll
-    for (int c = 0; c < COUT; c++)
+        for (int g = 0; g < G; g++) {
+            site[g] = path_site(pd, i, co, lex, 1 + wave * G + g);
+            path_link<LT, R>(ls, par, i, 1 + wave * G + g, raw[g]);
+        }
 #pragma unroll
-        for (int q = 0; q < 3; q++) acc[c][q] = {0.f, 0.f};
-    if (valid) {
-        const Coord co = cb_to_coord_pd(i, par, pd);
-        const int lex = 2 * i + (co.x[0] & 1);
-        constexpr int PPW = (9 + W - 1) / W;   // paths of this wave
-        constexpr int G = PPW < 3 ? PPW : 3;    // paths whose loads are in flight together
+        for (int g = 0; g < G; g++) path_matrix<LT, R>(ls, co, 1 + wave * G + g, raw[g], u[g]);
+    }
+    const int b0 = blockIdx.y * a.bper, b1 = b0 + a.bper < a.batch ? b0 + a.bper : a.batch;
+    for (int b = b0; b < b1; b++) {
+        const float *in_b = a.in + (size_t)b * a.in_bstride;
+        Cx<float> acc[COUT][3];
 #pragma unroll
-        for (int k0 = 0; k0 < PPW; k0 += G) {
-            RawLink<LT, R> raw[G];
-            float2 sv[G][CIN][3];
-            bool live[G];
+        for (int c = 0; c < COUT; c++)
 #pragma unroll
-            for (int g = 0; g < G; g++) {
-                const int k = wave * PPW + k0 + g;
-                live[g] = k0 + g < PPW && k < 9 && path_live(a, par, k);
-                if (live[g]) path_load<LT, R, CIN>(pd, ls, par, i, co, lex, k, in_b, raw[g], sv[g]);
+            for (int q = 0; q < 3; q++) acc[c][q] = {0.f, 0.f};
+        if (ident)
+#pragma unroll
+            for (int cp = 0; cp < CIN; cp++) {
+                if (cp % W != wave) continue;
+                Cx<float> v[1][3];
+                load_site<1>(in_b + (size_t)(2 * cp + par) * h * 6, 2, 0, h, i, v);
+#pragma unroll
+                for (int c = 0; c < COUT; c++) mix_acc(ldw<WT>(a.w, (c * CIN + cp) * 9), v[0], acc[c]);
             }
+        if (hops) {
+            Cx<float> sv[G][CIN][3];
+#pragma unroll
+            for (int g = 0; g < G; g++) load_site<CIN>(in_b, 2, 1 - par, h, site[g], sv[g]);
 #pragma unroll
             for (int g = 0; g < G; g++) {
-                if (!live[g]) continue;
-                const int k = wave * PPW + k0 + g;
-                Cx<float> v[CIN][3];
-                path_apply<LT, R, CIN>(ls, co, k, raw[g], sv[g], v);
+                const int k = 1 + wave * G + g;
+                if constexpr (COUT < CIN) {
 #pragma unroll
-                for (int c = 0; c < COUT; c++)
+                    for (int c = 0; c < COUT; c++) {
+                        Cx<float> ph[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+#pragma unroll
+                        for (int cp = 0; cp < CIN; cp++) mix_acc(ldw<WT>(a.w, (c * CIN + cp) * 9 + k), sv[g][cp], ph);
+                        matvec_acc(u[g], ph, acc[c]);
+                    }
+                } else {
 #pragma unroll
                     for (int cp = 0; cp < CIN; cp++) {
-                        const float2 w = ldw<WT>(a.w, (c * CIN + cp) * 9 + k);
+                        Cx<float> t[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+                        matvec_acc(u[g], sv[g][cp], t);
 #pragma unroll
-                        for (int q = 0; q < 3; q++) {
-                            acc[c][q].re += w.x * v[cp][q].re - w.y * v[cp][q].im;
-                            acc[c][q].im += w.x * v[cp][q].im + w.y * v[cp][q].re;
-                        }
+                        for (int c = 0; c < COUT; c++) mix_acc(ldw<WT>(a.w, (c * CIN + cp) * 9 + k), t, acc[c]);
                     }
+                }
             }
         }
-    }
-    if constexpr (W > 1) {
-        __shared__ float red[(W - 1) * COUT * 6 * 64];
-        if (wave > 0)
+        float *mine = red + (size_t)wave * COUT * 6 * 64 + lane;
 #pragma unroll
-            for (int c = 0; c < COUT; c++)
+        for (int c = 0; c < COUT; c++)
+            if (c % W != wave)
 #pragma unroll
                 for (int q = 0; q < 3; q++) {
-                    red[(((wave - 1) * COUT + c) * 6 + 2 * q) * 64 + lane] = acc[c][q].re;
-                    red[(((wave - 1) * COUT + c) * 6 + 2 * q + 1) * 64 + lane] = acc[c][q].im;
+                    mine[(6 * c + 2 * q) * 64] = acc[c][q].re;
+                    mine[(6 * c + 2 * q + 1) * 64] = acc[c][q].im;
                 }
         __syncthreads();
-        if (wave == 0)
-            for (int w = 1; w < W; w++)
 #pragma unroll
-                for (int c = 0; c < COUT; c++)
+        for (int c = 0; c < COUT; c++)
+            if (c % W == wave)
 #pragma unroll
-                    for (int q = 0; q < 3; q++) {
-                        acc[c][q].re += red[(((w - 1) * COUT + c) * 6 + 2 * q) * 64 + lane];
-                        acc[c][q].im += red[(((w - 1) * COUT + c) * 6 + 2 * q + 1) * 64 + lane];
+                for (int q = 0; q < 3; q++) {
+                    Cx<float> t = {0.f, 0.f};
+#pragma unroll
+                    for (int w = 0; w < W; w++) {   // the waves in order
+                        const float *o = red + ((size_t)w * COUT + c) * 6 * 64 + lane;
+                        t.re += w == c % W ? acc[c][q].re : o[2 * q * 64];
+                        t.im += w == c % W ? acc[c][q].im : o[(2 * q + 1) * 64];
                     }
-    }
-    if (wave == 0) {
-        double dr = 0.0, di = 0.0;
-        if (valid) {
-            float *out_b = a.out + (size_t)b * a.out_bstride;
-            const long long h = pd.h;
-#pragma unroll
-            for (int c = 0; c < COUT; c++) {
-                const long long o = ((c * a.out_pstride + (par - a.out_par0)) * h + i) * 3;
-                float2 *p = reinterpret_cast<float2 *>(out_b) + o;
-                if (a.addin) {   // the identity term of M, added in the same rounding as a separate pass
-                    const float2 *ad = reinterpret_cast<const float2 *>(a.addin + (size_t)b * a.addin_bstride) + o;
-#pragma unroll
-                    for (int q = 0; q < 3; q++) {
-                        const float2 t = ad[q];
-                        acc[c][q].re += t.x;
-                        acc[c][q].im += t.y;
-                    }
+                    acc[c][q] = t;
                 }
+        if (b + 1 < b1) __syncthreads();
+        double dr = 0.0, di = 0.0;
 #pragma unroll
-                for (int q = 0; q < 3; q++) p[q] = make_float2(acc[c][q].re, acc[c][q].im);
+        for (int c = 0; c < COUT; c++) {
+            if (c % W != wave || !valid) continue;
+            const long long o = ((c * a.out_pstride + (par - a.out_par0)) * h + i) * 3;
+            if (a.addin) {   // the identity term of M, added in the same rounding as a separate pass
+                const float2 *ad = reinterpret_cast<const float2 *>(a.addin + (size_t)b * a.addin_bstride) + o;
+#pragma unroll
+                for (int q = 0; q < 3; q++) {
+                    const float2 t = ad[q];
+                    acc[c][q].re += t.x;
+                    acc[c][q].im += t.y;
+                }
             }
-            if (a.dotred) {   // (q, out) = sum conj(q) out over this tile (COUT = 1)
+            store_vec(reinterpret_cast<float2 *>(a.out + (size_t)b * a.out_bstride) + o, acc[c]);
+            if (COUT == 1 && a.dotred) {   // (q, out) = sum conj(q) out over this tile
                 const float2 *qv = reinterpret_cast<const float2 *>(a.dotq) + (size_t)i * 3;
 #pragma unroll
                 for (int q = 0; q < 3; q++) {
@@ -219,7 +288,7 @@ __global__ void __launch_bounds__(64 * W) k_ptc_layer(PtcLaunch a)
                 }
             }
         }
-        if (a.dotred) {   // wave 0 covers the whole 64-site tile
+        if (COUT == 1 && a.dotred && wave == 0) {   // wave 0 covers the whole 64-site tile
             dr = wave_sum(dr);
             di = wave_sum(di);
             if (lane == 0) {
@@ -231,61 +300,100 @@ __global__ void __launch_bounds__(64 * W) k_ptc_layer(PtcLaunch a)
 }
 
 // Weight gradient: sums of (T_k in_{c'})(x)^+ g_c(x) over sites and batch
-// entries, one wavefront per path k.  Block j walks the work units (batch
-// entry, output parity, tile) j, j + grid, j + 2 grid, ... accumulating in FP64
-// per lane, and reduces once at the end: partials [block][9][COUT][CIN]
-// complex FP64, in a fixed order for a given grid.
+// entries, one wavefront per path k.  Row j walks the work units (batch chunk,
+// output parity, tile) j, j + nrow, ..., accumulating in FP64 per lane, and
+// reduces once at the end: partials [row][9][COUT][CIN] complex FP64, in a
+// fixed order for a given grid.  A unit unpacks its link once for a.bper batch
+// entries.  The hops of a row are two blocks (blockIdx.y 0, 1) of four waves,
+// one per SIMD; the lighter identity path is taken by further blocks, a row per
+// wave.
+//
+// The vector ALU bounds it (4 -> 4: 144 transport, 192 product and 64
+// conversion or FP64 instructions per site, path and entry); with fewer
+// outputs than inputs the gradient is transported instead,
+// (T_k in)^+ g = in^+ (T_k^+ g).  16^4, 8 entries: 4 -> 4 110 -> 73 us, 4 -> 1
+// 53 -> 42 us, 1 -> 4 40 -> 38 us, against blocks of nine waves, a path each
+// (two or three on a SIMD), that unpacked the link for every entry.
 template <class LT, int R, int CIN, int COUT>
-__global__ void __launch_bounds__(576) k_ptc_wgrad(PtcLaunch a, int npar, int batch)
+__global__ void __launch_bounds__(256) k_ptc_wgrad(PtcLaunch a, int npar, int nrow)
 {
-    const int lane = threadIdx.x & 63, k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int k = blockIdx.y < 2 ? 1 + 4 * blockIdx.y + wave : 0;
+    const int row = blockIdx.y < 2 ? blockIdx.x : 4 * blockIdx.x + wave;
+    if (row >= nrow) return;
     const ProbDesc &pd = a.probs[0];
     const int ntile = pd.ntile;
     const long long h = pd.h;
     const LinkSet &ls = pd.ls[a.lslot];
-    const long long nunit = (long long)batch * npar * ntile;
+    const int nunit = (a.batch + a.bper - 1) / a.bper * npar * ntile;
     double acc[COUT][CIN][2];
 #pragma unroll
     for (int c = 0; c < COUT; c++)
 #pragma unroll
         for (int cp = 0; cp < CIN; cp++) acc[c][cp][0] = acc[c][cp][1] = 0.0;
-    for (long long u = blockIdx.x; u < nunit; u += gridDim.x) {
-        const int b = (int)(u / (npar * ntile));
-        const int rem = (int)(u - (long long)b * npar * ntile);
-        const int par = a.par_lo + rem / ntile;
-        const int tile = rem % ntile;
-        const int i = tile * TILE + lane;
-        if (i >= pd.h) continue;
-        const float *in_b = a.in + (size_t)b * a.in_bstride;
-        const float *g_b = a.g + (size_t)b * a.g_bstride;
+    for (int j = row; j < nunit; j += nrow) {
+        const int u = xcd_unit(j, nunit);
+        const int b0 = u / (npar * ntile) * a.bper;
+        const int b1 = b0 + a.bper < a.batch ? b0 + a.bper : a.batch;
+        const int rem = u % (npar * ntile);
+        const int par = a.par_lo + rem % npar;
+        const int i = rem / npar * TILE + lane;
+        if (i >= pd.h || !path_live(a, par, k)) continue;
         const Coord co = cb_to_coord_pd(i, par, pd);
-        const int lex = 2 * i + (co.x[0] & 1);
-        if (!path_live(a, par, k)) continue;
+        const int site = path_site(pd, i, co, 2 * i + (co.x[0] & 1), k);
         RawLink<LT, R> raw;
-        float2 sv[CIN][3];
-        path_load<LT, R, CIN>(pd, ls, par, i, co, lex, k, in_b, raw, sv);
-        Cx<float> v[CIN][3];
-        path_apply<LT, R, CIN>(ls, co, k, raw, sv, v);
+        path_link<LT, R>(ls, par, i, k, raw);
+        Cx<float> m[3][3];
+        if (k != 0) path_matrix<LT, R>(ls, co, k, raw, m);
+        for (int b = b0; b < b1; b++) {
+            Cx<float> v[CIN][3], g[COUT][3];
+            load_site<CIN>(a.in + (size_t)b * a.in_bstride, 2, k == 0 ? par : 1 - par, h, site, v);
+            load_site<COUT>(a.g + (size_t)b * a.g_bstride, a.g_pstride, par - a.g_par0, h, i, g);
+            if (k != 0) {
+                if constexpr (COUT < CIN) {
 #pragma unroll
-        for (int c = 0; c < COUT; c++) {
-            const float2 *gp = reinterpret_cast<const float2 *>(g_b) + ((c * a.g_pstride + (par - a.g_par0)) * h + i) * 3;
-            const float2 g[3] = {gp[0], gp[1], gp[2]};
+                    for (int c = 0; c < COUT; c++) {
+                        Cx<float> t[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
 #pragma unroll
-            for (int cp = 0; cp < CIN; cp++) {
-                float re = 0.f, im = 0.f;
+                        for (int q = 0; q < 3; q++)
 #pragma unroll
-                for (int q = 0; q < 3; q++) {   // conj(v) g
-                    re = fmaa(v[cp][q].re, g[q].x, re);
-                    re = fmaa(v[cp][q].im, g[q].y, re);
-                    im = fmaa(v[cp][q].re, g[q].y, im);
-                    im = fmaa(-v[cp][q].im, g[q].x, im);
+                            for (int r = 0; r < 3; r++) {   // conj(m) g
+                                t[q].re = fmaa(m[r][q].re, g[c][r].re, t[q].re);
+                                t[q].re = fmaa(m[r][q].im, g[c][r].im, t[q].re);
+                                t[q].im = fmaa(m[r][q].re, g[c][r].im, t[q].im);
+                                t[q].im = fmaa(-m[r][q].im, g[c][r].re, t[q].im);
+                            }
+#pragma unroll
+                        for (int q = 0; q < 3; q++) g[c][q] = t[q];
+                    }
+                } else {
+#pragma unroll
+                    for (int c = 0; c < CIN; c++) {
+                        Cx<float> t[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+                        matvec_acc(m, v[c], t);
+#pragma unroll
+                        for (int q = 0; q < 3; q++) v[c][q] = t[q];
+                    }
                 }
-                acc[c][cp][0] += re;
-                acc[c][cp][1] += im;
             }
+#pragma unroll
+            for (int c = 0; c < COUT; c++)
+#pragma unroll
+                for (int cp = 0; cp < CIN; cp++) {
+                    float re = 0.f, im = 0.f;
+#pragma unroll
+                    for (int q = 0; q < 3; q++) {   // conj(v) g
+                        re = fmaa(v[cp][q].re, g[c][q].re, re);
+                        re = fmaa(v[cp][q].im, g[c][q].im, re);
+                        im = fmaa(v[cp][q].re, g[c][q].im, im);
+                        im = fmaa(-v[cp][q].im, g[c][q].re, im);
+                    }
+                    acc[c][cp][0] += re;
+                    acc[c][cp][1] += im;
+                }
         }
     }
-    double *out = a.partials + ((size_t)blockIdx.x * 9 + k) * (COUT * CIN * 2);
+    double *out = a.partials + ((size_t)row * 9 + k) * (COUT * CIN * 2);
 #pragma unroll
     for (int c = 0; c < COUT; c++)
 #pragma unroll
@@ -315,6 +423,21 @@ __global__ void __launch_bounds__(256) k_ptc_wsum(const double *partials, long l
         const int k = q / (cout * cin), c = (q / cin) % cout, cp = q % cin;
         const int o = ((c * cin + cp) * 9 + k) * 2 + ri;
         gw[o] = accumulate ? gw[o] + s[0] : s[0];
+    }
+}
+
+// Drawn pairs gathered into the batch: one launch per step in place of two
+// copies per pair (about 3 us each, 50 us of a step at a batch of 8).
+__global__ void __launch_bounds__(256) k_ptc_pairs(PtcPairs a)
+{
+    const int j = blockIdx.y;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.norm[j] = a.norm_of[j];
+    const float2 *src = reinterpret_cast<const float2 *>(a.mem) + 2 * a.nv * a.index[j];
+    float2 *r = reinterpret_cast<float2 *>(a.r) + a.nv * j, *e = reinterpret_cast<float2 *>(a.e) + a.nv * j;
+    for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < a.nv; t += (long long)gridDim.x * 256) {
+        const float2 u = src[t], v = src[a.nv + t];
+        r[t] = u;
+        e[t] = v;
     }
 }
 
@@ -428,47 +551,34 @@ __global__ void k_adam(float *w, float *m, float *v, const double *g, int n, int
 
 // ------------------------------------------------------------- launchers
 
-template <class LT, int R, class WT, int CIN, int COUT>
-static hipError_t layer_w(int W, const PtcLaunch &a, dim3 g, hipStream_t s)
-{
-    switch (W) {
-    case 1: hipLaunchKernelGGL((k_ptc_layer<LT, R, WT, CIN, COUT, 1>), g, dim3(64), 0, s, a); break;
-    case 3: hipLaunchKernelGGL((k_ptc_layer<LT, R, WT, CIN, COUT, 3>), g, dim3(192), 0, s, a); break;
-    case 5: hipLaunchKernelGGL((k_ptc_layer<LT, R, WT, CIN, COUT, 5>), g, dim3(320), 0, s, a); break;
-    case 9: hipLaunchKernelGGL((k_ptc_layer<LT, R, WT, CIN, COUT, 9>), g, dim3(576), 0, s, a); break;
-    default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
 template <class LT, int R, class WT>
-static hipError_t layer_c(int cin, int cout, int W, const PtcLaunch &a, dim3 g, hipStream_t s)
+static hipError_t layer_c(int cin, int cout, const PtcLaunch &a, dim3 g, hipStream_t s)
 {
 #define PTC_CASE(I, O) \
-    if (cin == I && cout == O) return layer_w<LT, R, WT, I, O>(W, a, g, s);
+    if (cin == I && cout == O) { hipLaunchKernelGGL((k_ptc_layer<LT, R, WT, I, O>), g, dim3(256), 0, s, a); return hipGetLastError(); }
     PTC_CASE(1, 1) PTC_CASE(1, 4) PTC_CASE(4, 4) PTC_CASE(4, 1) PTC_CASE(1, 2) PTC_CASE(2, 2) PTC_CASE(2, 1)
     PTC_CASE(2, 4) PTC_CASE(4, 2) PTC_CASE(1, 8) PTC_CASE(8, 8) PTC_CASE(8, 1)
 #undef PTC_CASE
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_ptc_layer(int prec, int recon, bool w16, int cin, int cout, int W, const PtcLaunch &a, int nblk,
-                            int batch, hipStream_t s)
+hipError_t launch_ptc_layer(int prec, int recon, bool w16, int cin, int cout, const PtcLaunch &a, int nblk,
+                            hipStream_t s)
 {
-    dim3 g(nblk, batch);
+    dim3 g(nblk, (a.batch + a.bper - 1) / a.bper);
     if (prec == 1 && recon == 18)
-        return w16 ? layer_c<float, 18, __half>(cin, cout, W, a, g, s) : layer_c<float, 18, float>(cin, cout, W, a, g, s);
+        return w16 ? layer_c<float, 18, __half>(cin, cout, a, g, s) : layer_c<float, 18, float>(cin, cout, a, g, s);
     if (prec == 2 && recon == 12)
-        return w16 ? layer_c<__half, 12, __half>(cin, cout, W, a, g, s) : layer_c<__half, 12, float>(cin, cout, W, a, g, s);
+        return w16 ? layer_c<__half, 12, __half>(cin, cout, a, g, s) : layer_c<__half, 12, float>(cin, cout, a, g, s);
     return hipErrorInvalidValue;
 }
 
 template <class LT, int R>
-static hipError_t wgrad_c(int cin, int cout, const PtcLaunch &a, int npar, int batch, dim3 g, hipStream_t s)
+static hipError_t wgrad_c(int cin, int cout, const PtcLaunch &a, int npar, int nrow, hipStream_t s)
 {
-    const dim3 b(576);
+    const dim3 g(nrow, 3), b(256);
 #define WG_CASE(I, O) \
-    if (cin == I && cout == O) { hipLaunchKernelGGL((k_ptc_wgrad<LT, R, I, O>), g, b, 0, s, a, npar, batch); return hipGetLastError(); }
+    if (cin == I && cout == O) { hipLaunchKernelGGL((k_ptc_wgrad<LT, R, I, O>), g, b, 0, s, a, npar, nrow); return hipGetLastError(); }
     WG_CASE(1, 1) WG_CASE(1, 4) WG_CASE(4, 4) WG_CASE(4, 1) WG_CASE(1, 2) WG_CASE(2, 2) WG_CASE(2, 1)
     WG_CASE(2, 4) WG_CASE(4, 2) WG_CASE(1, 8) WG_CASE(8, 8) WG_CASE(8, 1)
 #undef WG_CASE
@@ -476,12 +586,11 @@ static hipError_t wgrad_c(int cin, int cout, const PtcLaunch &a, int npar, int b
 }
 
 // transports on FP32 recon-18 (prec 1) or FP16 recon-12 (prec 2) fat links
-hipError_t launch_ptc_wgrad(int prec, int recon, int cin, int cout, const PtcLaunch &a, int npar, int batch, int nrow,
+hipError_t launch_ptc_wgrad(int prec, int recon, int cin, int cout, const PtcLaunch &a, int npar, int nrow,
                             hipStream_t s)
 {
-    const dim3 g(nrow);
-    if (prec == 1 && recon == 18) return wgrad_c<float, 18>(cin, cout, a, npar, batch, g, s);
-    if (prec == 2 && recon == 12) return wgrad_c<__half, 12>(cin, cout, a, npar, batch, g, s);
+    if (prec == 1 && recon == 18) return wgrad_c<float, 18>(cin, cout, a, npar, nrow, s);
+    if (prec == 2 && recon == 12) return wgrad_c<__half, 12>(cin, cout, a, npar, nrow, s);
     return hipErrorInvalidValue;
 }
 
@@ -490,6 +599,13 @@ hipError_t launch_ptc_wsum(const double *partials, long long nrow, int cin, int 
 {
     const int nv = 9 * cout * cin * 2;
     hipLaunchKernelGGL(k_ptc_wsum, dim3(nv), dim3(256), 0, s, partials, nrow, cin, cout, gw, accumulate);
+    return hipGetLastError();
+}
+
+hipError_t launch_ptc_pairs(const PtcPairs &a, hipStream_t s)
+{
+    const long long nb = (a.nv + 255) / 256;
+    hipLaunchKernelGGL(k_ptc_pairs, dim3((unsigned)(nb < 1024 ? nb : 1024), a.n), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -174,6 +174,54 @@ def test_one_training_step_matches_oracle(loss):
     lat.close()
 
 
+@pytest.mark.parametrize("chans", [(1, 4, 4, 1), (1, 2, 4), (1, 8)])
+def test_training_batch_in_ragged_chunks(chans):
+    """Two steps of a batch whose entries share blocks (two entries per block,
+    one in the last; a ragged last tile; a block count that 8 does not divide)
+    against the oracle.  The first Adam step only shows the signs of the
+    gradient, the second its ratio to the first: an entry of at least a
+    twentieth of the largest is known to 1e-5 / 0.05 of itself, a few 1e-7 of
+    an update of 1e-3."""
+    H = _hisq()
+    dims, B, lr = (6, 6, 6, 10), 37, 1e-3
+    fat, lng = synth.make_links(dims, 0.25, seed=4020)
+    lat = H.Lattice(dims)
+    lat.load_links(fat, lng)
+    net = H.PTC(lat, chans)
+    net.set_transport(H.HISQ_F32, 18)
+    net.set_loss(H.HISQ_LOSS_EUCLIDEAN)
+    net.set_weights(_rand_w(chans, 8, scale=0.2))
+    b = synth.gaussian_even(dims, 4520)
+    assert net.harvest(lat, 0.1, b, every=4, maxpairs=2) == 2
+    pairs = [net.get_pair(i, b.shape[0]) for i in range(2)]
+    ws = [[w.astype(np.complex128) for w in net.get_weights()]]
+    state = {}
+    for step in (1, 2):
+        loss = net.train(1, batch=B, lr=lr, seed=step)[0]
+        # the loss depends on how often each pair was drawn only
+        z = [oracle.ptc_apply(dims, fat, ws[-1], r) for r, _ in pairs]
+        ee = [np.vdot(e, e).real for _, e in pairs]
+        S = [np.vdot(zi, e) / n for zi, (_, e), n in zip(z, pairs, ee)]
+        Q = [np.vdot(zi, zi).real / n for zi, n in zip(z, ee)]
+        want = [1 - abs(k * S[0] + (B - k) * S[1]) ** 2 / (B * (k * Q[0] + (B - k) * Q[1])) for k in range(B + 1)]
+        k = int(np.argmin(np.abs(np.array(want) - loss)))
+        assert abs(want[k] - loss) <= 1e-5 * abs(loss)
+        drawn = [pairs[0]] * k + [pairs[1]] * (B - k)
+        _, grads = oracle.ptc_loss_and_grad(dims, fat, ws[-1], [r for r, _ in drawn], [e for _, e in drawn])
+        got = [w.astype(np.complex128) for w in net.get_weights()]
+        for l, g in enumerate(grads):
+            for part in ("real", "imag"):
+                gp, p0 = getattr(g, part), getattr(ws[-1][l], part)
+                m, v = state.get((l, part), (np.zeros_like(gp), np.zeros_like(gp)))
+                p1, m, v = oracle.adam_step(p0, gp, m, v, step, lr=lr)
+                state[l, part] = m, v
+                big = np.abs(gp) > 0.05 * np.abs(gp).max()
+                assert np.allclose(getattr(got[l], part)[big], p1[big], atol=2e-6, rtol=0), (step, l, part)
+        ws.append(got)
+    net.close()
+    lat.close()
+
+
 def _identity_weights(chans):
     ws = []
     for a, b in zip(chans[:-1], chans[1:]):
