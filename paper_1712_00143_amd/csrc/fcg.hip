@@ -152,43 +152,6 @@ hipError_t launch_fcg(const FcgLaunch &a, int ntile, hipStream_t s)
     return hipGetLastError();
 }
 
-// Adjoint weights of a layer: W'[c'][c][k'] = conj(W[c][c'][k]), k' swaps
-// the +mu and -mu paths (the adjoint of a forward hop is a backward hop).
-__global__ void k_ptc_adjoint(const float *w, int cin, int cout, float *wadj, __half *wadj16)
-{
-    const int t = threadIdx.x;
-    if (t >= cin * cout * 9) return;
-    const int k = t % 9, cp = (t / 9) % cin, c = t / (9 * cin);
-    const int ks = k == 0 ? 0 : (((k - 1) & 1) ? k - 1 : k + 1);
-    const float re = w[2 * t], im = w[2 * t + 1];
-    const int o = (cp * cout + c) * 9 + ks;
-    wadj[2 * o] = re;
-    wadj[2 * o + 1] = -im;
-    wadj16[2 * o] = __float2half_rn(re);
-    wadj16[2 * o + 1] = __float2half_rn(-im);
-}
-
-// A gradient gp with respect to the adjoint weights W' ([cout'][cin'][9]) of
-// an adjoint layer application contributes conj(gp) with the paths reversed
-// to the gradient of W ([cin'][cout'][9]): W' = conj(P W), P the index map.
-// It is the first contribution of a step: every value is set.
-__global__ void k_ptc_gadj(const double *gp, int cin_p, int cout_p, double *gw)
-{
-    const int t = threadIdx.x;
-    if (t >= cin_p * cout_p * 9) return;
-    const int k = t % 9, cp = (t / 9) % cin_p, c = t / (9 * cin_p);
-    const int ks = k == 0 ? 0 : (((k - 1) & 1) ? k - 1 : k + 1);
-    const int o = (cp * cout_p + c) * 9 + ks;
-    gw[2 * o] = gp[2 * t];
-    gw[2 * o + 1] = -gp[2 * t + 1];
-}
-
-hipError_t launch_ptc_gadj(const double *gp, int cin_p, int cout_p, double *gw, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_ptc_gadj, dim3(1), dim3(1024), 0, s, gp, cin_p, cout_p, gw);
-    return hipGetLastError();
-}
-
 __global__ void k_to_half(const float *w, __half *w16, int n)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
@@ -198,12 +161,6 @@ __global__ void k_to_half(const float *w, __half *w16, int n)
 hipError_t launch_to_half(const float *w, __half *w16, int n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_to_half, dim3((n + 255) / 256), dim3(256), 0, s, w, w16, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_ptc_adjoint(const float *w, int cin, int cout, float *wadj, __half *wadj16, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_ptc_adjoint, dim3(1), dim3(1024), 0, s, w, cin, cout, wadj, wadj16);
     return hipGetLastError();
 }
 

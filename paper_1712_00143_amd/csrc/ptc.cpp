@@ -98,15 +98,20 @@ hisq_status ensure_transport_links(const hisq_ptc_s *n, hisq_lattice lat)
     return hisq_prepare_links(lat, (hisq_prec)n->tprec, (hisq_recon)n->trecon);
 }
 
-// adjoint weights (FP32 and FP16) of every layer from the FP32 master
-hipError_t refresh_adjoint(hisq_ptc_s *n, hipStream_t s)
+PtcNet net_desc(const hisq_ptc_s *n)
 {
-    for (int l = 0; l < n->nlayer; l++) {
-        hipError_t e = launch_ptc_adjoint(n->w32 + 2 * n->woff[l], n->chans[l], n->chans[l + 1],
-                                          n->wa32 + 2 * n->woff[l], n->wa16 + 2 * n->woff[l], s);
-        if (e != hipSuccess) return e;
+    PtcNet d;
+    memset(&d, 0, sizeof d);
+    d.w32 = n->w32;
+    d.wa32 = n->wa32;
+    d.w16 = n->w16;
+    d.wa16 = n->wa16;
+    d.nlayer = n->nlayer;
+    for (int l = 0; l <= n->nlayer; l++) {
+        d.chans[l] = n->chans[l];
+        d.woff[l] = l < n->nlayer ? n->woff[l] : n->nw;
     }
-    return hipSuccess;
+    return d;
 }
 
 PtcLaunch base_launch(hisq_lattice lat, int lslot)
@@ -166,11 +171,9 @@ hipError_t run_layer(hisq_lattice lat, int lslot, int prec, int recon, bool w16,
 }
 
 // Weight gradient of one layer application, summed over the output parities
-// where g lives (g_pstride 1: even only), added into gw (FP64, the layer's
-// own [cout][cin][9] layout).
+// where g lives (g_pstride 1: even only), into gw (FP64) as `mode` says.
 hipError_t run_wgrad(hisq_ptc_s *n, hisq_lattice lat, int cin, int cout, const float *in, long long in_bs, int in_zero,
-                     const float *g, long long g_bs, int g_pstride, int batch, double *gw, int accumulate,
-                     hipStream_t s)
+                     const float *g, long long g_bs, int g_pstride, int batch, double *gw, int mode, hipStream_t s)
 {
     PtcLaunch a = base_launch(lat, n->tslot());
     a.in = in;
@@ -188,7 +191,7 @@ hipError_t run_wgrad(hisq_ptc_s *n, hisq_lattice lat, int cin, int cout, const f
     const int nrow = (int)(units < WGRAD_ROWS ? units : WGRAD_ROWS);
     hipError_t e = launch_ptc_wgrad(n->tprec, n->trecon, cin, cout, a, g_pstride, nrow, s);
     if (e != hipSuccess) return e;
-    return launch_ptc_wsum(n->part, nrow, cin, cout, gw, accumulate, s);
+    return launch_ptc_wsum(n->part, nrow, cin, cout, gw, mode, s);
 }
 
 // z = M(r) for `batch` even vectors (FP32 [batch][h][3]); `ws` holds two
@@ -428,7 +431,7 @@ extern "C" {
 
 hisq_status hisq_ptc_create(hisq_lattice lat, int nlayer, const int *chans, hisq_ptc *out)
 {
-    if (!lat || !chans || !out || nlayer < 1 || nlayer > 8) return set_err(lat, HISQ_ERR_ARG, "bad network arguments");
+    if (!lat || !chans || !out || nlayer < 1 || nlayer > PTC_MAX_LAYERS) return set_err(lat, HISQ_ERR_ARG, "bad network arguments");
     if (chans[0] != 1) return set_err(lat, HISQ_ERR_ARG, "the first channel count must be 1");
     for (int l = 0; l <= nlayer; l++)
         if (chans[l] != 1 && chans[l] != 2 && chans[l] != 4 && chans[l] != 8)
@@ -496,7 +499,7 @@ hisq_status hisq_ptc_set_weights(hisq_ptc n, const double *w)
     // the FP16 inference copies are rounded from the FP32 master on the device
     // (round to nearest even), as after every Adam step
     HIPCHK(lat, launch_to_half(n->w32, n->w16, 2 * n->nw, lat->s));
-    HIPCHK(lat, refresh_adjoint(n, lat->s));
+    HIPCHK(lat, launch_ptc_adjoint(net_desc(n), lat->s));
     HIPCHK(lat, hipMemsetAsync(n->m, 0, f.size() * 4, lat->s));
     HIPCHK(lat, hipMemsetAsync(n->v, 0, f.size() * 4, lat->s));
     HIPCHK(lat, hipStreamSynchronize(lat->s));
@@ -665,7 +668,7 @@ hisq_status hisq_ptc_layer_backward(hisq_ptc n, int layer, const void *in, const
             HIPCHK(lat, hipMalloc(&n->part, need * 8));
             n->part_n = need;
         }
-        HIPCHK(lat, run_wgrad(n, lat, cin, cout, (const float *)in, 0, -1, (const float *)gout, 0, 2, 1, n->gtmp, 0, s));
+        HIPCHK(lat, run_wgrad(n, lat, cin, cout, (const float *)in, 0, -1, (const float *)gout, 0, 2, 1, n->gtmp, WSUM_SET, s));
         HIPCHK(lat, hipMemcpyAsync(gw, n->gtmp, sizeof(double) * 2 * 9 * cin * cout, hipMemcpyDeviceToHost, s));
     }
     HIPCHK(lat, hipStreamSynchronize(s));
@@ -876,7 +879,7 @@ hisq_status hisq_ptc_load(hisq_ptc n, const char *path)
     HIPCHK(lat, hipMemcpy(n->m, m.data(), nf * 4, hipMemcpyHostToDevice));
     HIPCHK(lat, hipMemcpy(n->v, v.data(), nf * 4, hipMemcpyHostToDevice));
     HIPCHK(lat, launch_to_half(n->w32, n->w16, (int)nf, lat->s));
-    HIPCHK(lat, refresh_adjoint(n, lat->s));
+    HIPCHK(lat, launch_ptc_adjoint(net_desc(n), lat->s));
     HIPCHK(lat, hipStreamSynchronize(lat->s));
     n->step = hdr[4 + n->nlayer];
     return HISQ_OK;
@@ -1092,8 +1095,8 @@ hisq_status hisq_ptc_train(hisq_ptc n, int steps, int batch, double lr, unsigned
         int k = 0;
         for (int l = 1; l <= nl; l++) {
             const int ci = n->chans[l], co = n->chans[l - 1];   // the adjoint application maps ci -> co
-            HIPCHK(lat0, run_wgrad(n, lat, ci, co, bs[l], af, -1, gcur, g_bs, g_pstride, batch, n->gtmp, 0, s));
-            HIPCHK(lat0, launch_ptc_gadj(n->gtmp, ci, co, n->gw + 2 * n->woff[l - 1], s));
+            HIPCHK(lat0, run_wgrad(n, lat, ci, co, bs[l], af, -1, gcur, g_bs, g_pstride, batch,
+                                   n->gw + 2 * n->woff[l - 1], WSUM_ADJOINT, s));
             HIPCHK(lat0, run_layer(lat, n->tslot(), n->tprec, n->trecon, false, n->w32 + 2 * n->woff[l - 1], co, ci, gcur, g_bs,
                                    g_pstride == 1 ? 1 : -1, gbuf[k], af, 2, 0, 1, batch, s));
             gcur = gbuf[k];
@@ -1106,7 +1109,7 @@ hisq_status hisq_ptc_train(hisq_ptc n, int steps, int batch, double lr, unsigned
             const int ci = n->chans[l - 1], co = n->chans[l];
             const bool first = l == 1;
             HIPCHK(lat0, run_wgrad(n, lat, ci, co, first ? rb : acts[l - 1], first ? hl * 6 : af, first ? 1 : -1, gcur,
-                                   af, 2, batch, n->gw + 2 * n->woff[l - 1], 1, s));
+                                   af, 2, batch, n->gw + 2 * n->woff[l - 1], WSUM_ADD, s));
             if (!first) {
                 HIPCHK(lat0, run_layer(lat, n->tslot(), n->tprec, n->trecon, false, n->wa32 + 2 * n->woff[l - 1], co, ci, gcur, af, -1,
                                        gbuf[k], af, 2, 0, 1, batch, s));
@@ -1115,8 +1118,7 @@ hisq_status hisq_ptc_train(hisq_ptc n, int steps, int batch, double lr, unsigned
             }
         }
         n->step += 1;
-        HIPCHK(lat0, launch_adam(n->w32, n->m, n->v, n->gw, 2 * n->nw, n->step, (float)lr, n->w16, s));
-        HIPCHK(lat0, refresh_adjoint(n, s));
+        HIPCHK(lat0, launch_adam(net_desc(n), n->m, n->v, n->gw, n->step, (float)lr, s));
     }
     if (losses && steps > 0)
         HIPCHK(lat0, hipMemcpyAsync(losses, n->dloss, sizeof(double) * steps, hipMemcpyDeviceToHost, s));

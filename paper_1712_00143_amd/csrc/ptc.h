@@ -91,7 +91,8 @@ constexpr int WGRAD_ROWS = 336, WGRAD_UNITS = 10 * WGRAD_ROWS;
 // into nrow rows of [9][cout][cin] complex FP64.
 hipError_t launch_ptc_wgrad(int prec, int recon, int cin, int cout, const PtcLaunch &a, int npar, int nrow,
                            hipStream_t s);
-hipError_t launch_ptc_wsum(const double *partials, long long nrow, int cin, int cout, double *gw, int accumulate,
+enum : int { WSUM_SET = 0, WSUM_ADD = 1, WSUM_ADJOINT = 2 };
+hipError_t launch_ptc_wsum(const double *partials, long long nrow, int cin, int cout, double *gw, int mode,
                            hipStream_t s);
 // Gather of drawn training pairs (r, e) and their normalisations.
 constexpr int PTC_PAIRS = 16;   // pairs per launch (their indices travel in the kernel arguments)
@@ -106,11 +107,20 @@ struct PtcPairs {
 };
 hipError_t launch_ptc_pairs(const PtcPairs &a, hipStream_t s);
 hipError_t launch_ptc_loss(const PtcLaunch &a, int ntile, int batch, double *loss, hipStream_t s);
-hipError_t launch_adam(float *w, float *m, float *v, const double *g, int n, int step, float lr, __half *w16,
-                       hipStream_t s);
-hipError_t launch_ptc_adjoint(const float *w, int cin, int cout, float *wadj, __half *wadj16, hipStream_t s);
+// A network's weights: layer l has chans[l] inputs, chans[l + 1] outputs and
+// starts at complex weight woff[l] (woff[nlayer]: all of them).
+constexpr int PTC_MAX_LAYERS = 8;
+struct PtcNet {
+    float *w32, *wa32;       // FP32 master weights, their adjoint
+    __half *w16, *wa16;      // FP16 copies
+    int nlayer;
+    int chans[PTC_MAX_LAYERS + 1], woff[PTC_MAX_LAYERS + 1];
+};
+// One Adam step on w32, and the copies it leaves stale; launch_ptc_adjoint
+// refreshes the adjoints alone.
+hipError_t launch_adam(const PtcNet &net, float *m, float *v, const double *g, int step, float lr, hipStream_t s);
+hipError_t launch_ptc_adjoint(const PtcNet &net, hipStream_t s);
 hipError_t launch_to_half(const float *w, __half *w16, int n, hipStream_t s);
-hipError_t launch_ptc_gadj(const double *gp, int cin_p, int cout_p, double *gw, hipStream_t s);
 
 // flexible CG vector kernels (FP32 vectors, complex FP64 scalars in SolveState::cplx)
 struct FcgLaunch {

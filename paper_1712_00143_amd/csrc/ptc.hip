@@ -52,6 +52,13 @@ __device__ __forceinline__ bool path_live(const PtcLaunch &a, int par, int k)
     return k == 0 ? a.in_zero_par != par : a.in_zero_par != 1 - par;
 }
 
+// Index of W[c][c'][k] of a layer with cout outputs in its adjoint W'[c'][c][k'],
+// k' the reversed hop (the adjoint of a forward hop is a backward hop).
+__device__ __forceinline__ int adjoint_index(int c, int cp, int k, int cout)
+{
+    return (cp * cout + c) * 9 + (k == 0 ? 0 : (k & 1) ? k + 1 : k - 1);
+}
+
 // packed link direction of hop k: 4mu forward, 4mu + 1 backward
 __device__ __forceinline__ int path_dir(int k) { return 4 * ((k - 1) >> 1) + ((k - 1) & 1); }
 
@@ -137,15 +144,6 @@ __device__ __forceinline__ void mix_acc(const float2 w, const Cx<float> v[3], Cx
     }
 }
 
-// Work unit of block j of n: blocks go round the 8 XCDs in order, so XCD j % 8
-// takes a contiguous eighth of the units, whose neighbours it then finds in
-// its own L2.  The last n % 8 units keep their place.
-__device__ __forceinline__ int xcd_unit(int j, int n)
-{
-    const int per = n >> 3;
-    return j < per * 8 ? (j & 7) * per + (j >> 3) : j;
-}
-
 // Forward layer (also the input-gradient layer, given the adjoint weights) of
 // a.bper batch entries per block of four waves: wave w takes the two hops along
 // direction w and every fourth input channel of the identity path, so that the
@@ -172,7 +170,7 @@ __global__ void __launch_bounds__(256) k_ptc_layer(PtcLaunch a)
     const ProbDesc &pd = a.probs[0];
     const int ntile = pd.ntile;
     const int npar = gridDim.x / ntile;
-    const int unit = xcd_unit(blockIdx.x, gridDim.x);
+    const int unit = xcd_tile(blockIdx.x, gridDim.x, 1);
     const int par = a.par_lo + unit % npar, tile = unit / npar;
     const bool valid = tile * TILE + lane < pd.h;
     const int i = valid ? tile * TILE + lane : pd.h - 1;   // idle lanes repeat the last site
@@ -332,7 +330,7 @@ __global__ void __launch_bounds__(256) k_ptc_wgrad(PtcLaunch a, int npar, int nr
 #pragma unroll
         for (int cp = 0; cp < CIN; cp++) acc[c][cp][0] = acc[c][cp][1] = 0.0;
     for (int j = row; j < nunit; j += nrow) {
-        const int u = xcd_unit(j, nunit);
+        const int u = xcd_tile(j, nunit, 1);
         const int b0 = u / (npar * ntile) * a.bper;
         const int b1 = b0 + a.bper < a.batch ? b0 + a.bper : a.batch;
         const int rem = u % (npar * ntile);
@@ -408,9 +406,11 @@ __global__ void __launch_bounds__(256) k_ptc_wgrad(PtcLaunch a, int npar, int nr
 
 // g_w[c][c'][k] = sum over the partial rows: one block per value, each thread
 // summing rows t, t + 256, ... in order, then a fixed-order block sum, so the
-// result does not depend on scheduling.
+// result does not depend on scheduling.  WSUM_ADJOINT: the rows are a gradient
+// with respect to adjoint weights W' = conj(P W), P the index map; it is stored
+// as conj of the value at the reversed index, as a gradient of W.
 __global__ void __launch_bounds__(256) k_ptc_wsum(const double *partials, long long nrow, int cin, int cout,
-                                                  double *gw, int accumulate)
+                                                  double *gw, int mode)
 {
     __shared__ double lds[16];
     const int v = blockIdx.x;   // value index in [9][cout][cin][2]
@@ -421,8 +421,12 @@ __global__ void __launch_bounds__(256) k_ptc_wsum(const double *partials, long l
     if (threadIdx.x == 0) {
         const int ri = v & 1, q = v >> 1;
         const int k = q / (cout * cin), c = (q / cin) % cout, cp = q % cin;
-        const int o = ((c * cin + cp) * 9 + k) * 2 + ri;
-        gw[o] = accumulate ? gw[o] + s[0] : s[0];
+        if (mode == WSUM_ADJOINT) {
+            gw[2 * adjoint_index(c, cp, k, cout) + ri] = ri ? -s[0] : s[0];
+        } else {
+            const int o = ((c * cin + cp) * 9 + k) * 2 + ri;
+            gw[o] = mode == WSUM_ADD ? gw[o] + s[0] : s[0];
+        }
     }
 }
 
@@ -530,23 +534,51 @@ __global__ void __launch_bounds__(192) k_ptc_loss_grad(PtcLaunch a, const double
         make_float2(ar * t.x - ai * t.y + bc * zw.x, ar * t.y + ai * t.x + bc * zw.y);
 }
 
-// Adam on the FP32 master weights (complex weights as (re, im) pairs);
-// refreshes the FP32 and FP16 working copies.
-__global__ void k_adam(float *w, float *m, float *v, const double *g, int n, int step, float lr, float b1,
-                       float b2, float eps, __half *w16)
+// The working copies of complex weight j (FP32 master value w): the adjoint's
+// in FP32 and FP16, W'[c'][c][k'] = conj(W[c][c'][k]).
+__device__ __forceinline__ void put_adjoint(const PtcNet &net, int j, float re, float im)
+{
+    int l = 0;
+    while (j >= net.woff[l + 1]) l++;
+    const int cin = net.chans[l], cout = net.chans[l + 1];
+    const int t = j - net.woff[l], k = t % 9, cp = (t / 9) % cin, c = t / (9 * cin);
+    const int o = net.woff[l] + adjoint_index(c, cp, k, cout);
+    net.wa32[2 * o] = re;
+    net.wa32[2 * o + 1] = -im;
+    net.wa16[2 * o] = __float2half_rn(re);
+    net.wa16[2 * o + 1] = __float2half_rn(-im);
+}
+
+__global__ void k_ptc_adjoint(PtcNet net)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    const float gj = (float)g[j];
-    const float mj = b1 * m[j] + (1.f - b1) * gj;
-    const float vj = b2 * v[j] + (1.f - b2) * gj * gj;
-    m[j] = mj;
-    v[j] = vj;
-    const float mh = mj / (1.f - powf(b1, (float)step));
-    const float vh = vj / (1.f - powf(b2, (float)step));
-    const float wj = w[j] - lr * mh / (sqrtf(vh) + eps);
-    w[j] = wj;
-    w16[j] = __float2half_rn(wj);
+    if (j < net.woff[net.nlayer]) put_adjoint(net, j, net.w32[2 * j], net.w32[2 * j + 1]);
+}
+
+// Adam on the FP32 master weights (one complex weight per thread, its parts
+// separate parameters); refreshes the working copies of the weight and of the
+// adjoint (one launch instead of one more per layer, 4.4 us each).
+__global__ void k_adam(PtcNet net, float *m, float *v, const double *g, int step, float lr, float b1, float b2,
+                       float eps)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= net.woff[net.nlayer]) return;
+    float wn[2];
+#pragma unroll
+    for (int ri = 0; ri < 2; ri++) {
+        const int j = 2 * t + ri;
+        const float gj = (float)g[j];
+        const float mj = b1 * m[j] + (1.f - b1) * gj;
+        const float vj = b2 * v[j] + (1.f - b2) * gj * gj;
+        m[j] = mj;
+        v[j] = vj;
+        const float mh = mj / (1.f - powf(b1, (float)step));
+        const float vh = vj / (1.f - powf(b2, (float)step));
+        wn[ri] = net.w32[j] - lr * mh / (sqrtf(vh) + eps);
+        net.w32[j] = wn[ri];
+        net.w16[j] = __float2half_rn(wn[ri]);
+    }
+    put_adjoint(net, t, wn[0], wn[1]);
 }
 
 // ------------------------------------------------------------- launchers
@@ -594,11 +626,11 @@ hipError_t launch_ptc_wgrad(int prec, int recon, int cin, int cout, const PtcLau
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_ptc_wsum(const double *partials, long long nrow, int cin, int cout, double *gw, int accumulate,
+hipError_t launch_ptc_wsum(const double *partials, long long nrow, int cin, int cout, double *gw, int mode,
                            hipStream_t s)
 {
     const int nv = 9 * cout * cin * 2;
-    hipLaunchKernelGGL(k_ptc_wsum, dim3(nv), dim3(256), 0, s, partials, nrow, cin, cout, gw, accumulate);
+    hipLaunchKernelGGL(k_ptc_wsum, dim3(nv), dim3(256), 0, s, partials, nrow, cin, cout, gw, mode);
     return hipGetLastError();
 }
 
@@ -619,11 +651,16 @@ hipError_t launch_ptc_loss(const PtcLaunch &a, int ntile, int batch, double *los
     return hipGetLastError();
 }
 
-hipError_t launch_adam(float *w, float *m, float *v, const double *g, int n, int step, float lr, __half *w16,
-                       hipStream_t s)
+hipError_t launch_adam(const PtcNet &net, float *m, float *v, const double *g, int step, float lr, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_adam, dim3((n + 255) / 256), dim3(256), 0, s, w, m, v, g, n, step, lr, 0.9f, 0.999f,
-                       1e-8f, w16);
+    hipLaunchKernelGGL(k_adam, dim3((net.woff[net.nlayer] + 255) / 256), dim3(256), 0, s, net, m, v, g, step, lr, 0.9f,
+                       0.999f, 1e-8f);
+    return hipGetLastError();
+}
+
+hipError_t launch_ptc_adjoint(const PtcNet &net, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_ptc_adjoint, dim3((net.woff[net.nlayer] + 255) / 256), dim3(256), 0, s, net);
     return hipGetLastError();
 }
 
