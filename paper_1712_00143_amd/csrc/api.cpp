@@ -45,7 +45,13 @@ hipError_t dvec_alloc(DVec &v, int prec, long long sites)
     v.prec = prec;
     v.sites = sites;
     v.n = prec == 2 ? reinterpret_cast<float *>((char *)v.p + (size_t)sites * 12) : nullptr;
-    return hipMemset(v.p, 0, b);
+    return device_zero(v.p, b);
+}
+
+hipError_t device_zero(void *p, size_t bytes)
+{
+    const hipError_t e = hipMemset(p, 0, bytes);
+    return e != hipSuccess ? e : hipStreamSynchronize(nullptr);
 }
 
 void dvec_free(DVec &v)

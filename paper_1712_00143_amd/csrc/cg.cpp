@@ -73,7 +73,7 @@ hisq_status build_set(hisq_lattice lat0, SolveSet &S, const std::vector<hisq_lat
         HIPCHK(lat0, hipHostMalloc(&S.hst, sizeof(SolveState) * n, hipHostMallocDefault));
         HIPCHK(lat0, hipMalloc(&S.dpart, sizeof(double) * NPART * ntile));
         HIPCHK(lat0, hipMalloc(&S.dred, sizeof(double) * 2 * ntile));
-        HIPCHK(lat0, hipMemset(S.dst, 0, sizeof(SolveState) * n));
+        HIPCHK(lat0, device_zero(S.dst, sizeof(SolveState) * n));
     }
     // the tile -> problem map depends on the order of the problems, not only
     // on the totals compared above

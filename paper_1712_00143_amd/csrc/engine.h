@@ -24,6 +24,10 @@ struct DVec {
 
 size_t vec_bytes(int prec, long long sites);
 hipError_t dvec_alloc(DVec &v, int prec, long long sites);
+// Clears new device memory before the call returns.  hipMemset alone is queued
+// on the null stream, which the lattices' non-blocking streams do not wait for:
+// it could clear what the first kernel or copy on such a stream had written.
+hipError_t device_zero(void *p, size_t bytes);
 void dvec_free(DVec &v);
 
 // Work set of one (possibly batched) solve: concatenated parity vectors of

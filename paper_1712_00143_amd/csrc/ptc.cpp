@@ -464,10 +464,10 @@ hisq_status hisq_ptc_create(hisq_lattice lat, int nlayer, const int *chans, hisq
         hisq_ptc_destroy(n);
         return set_err(lat, HISQ_ERR_OOM, "network allocation failed");
     }
-    for (void *p : {(void *)n->w32, (void *)n->m, (void *)n->v, (void *)n->wa32}) (void)hipMemset(p, 0, nf * 4);
-    (void)hipMemset(n->w16, 0, nf * 2);
-    (void)hipMemset(n->wa16, 0, nf * 2);
-    (void)hipMemset(n->gw, 0, nf * 8);
+    for (void *p : {(void *)n->w32, (void *)n->m, (void *)n->v, (void *)n->wa32}) (void)device_zero(p, nf * 4);
+    (void)device_zero(n->w16, nf * 2);
+    (void)device_zero(n->wa16, nf * 2);
+    (void)device_zero(n->gw, nf * 8);
     *out = n;
     return HISQ_OK;
 }
@@ -810,6 +810,7 @@ hisq_status hisq_ptc_harvest(hisq_ptc n, hisq_lattice lat, double mass, const do
         pb.ee[keep] = pb.ee[i];
         pb.er[keep++] = pb.er[i];
     }
+    HIPCHK(lat, hipStreamSynchronize(nullptr));   // copies within the device are only queued
     pb.n = keep;
     pb.ee.resize(keep);
     pb.er.resize(keep);
