@@ -72,8 +72,8 @@ hipError_t launch_ff_naik_adjoint(const SmearGeom &g, const double2 *W, const do
 // four-direction planar fields.
 hipError_t launch_ff_unitarize_adjoint(const SmearGeom &g, const double2 *V, double2 *G, hipStream_t s);
 
-// out = a * out + b * in over n double2 (a = 0: out = b * in, out not read).
-hipError_t launch_field_axpby(double2 *out, double a, const double2 *in, double b, size_t n, hipStream_t s);
+// out = in over n double2.
+hipError_t launch_field_copy(double2 *out, const double2 *in, size_t n, hipStream_t s);
 
 // F_mu(x) = TA[U_mu(x) G_mu(x)] (four-direction planar fields; F may alias G).
 hipError_t launch_ff_project(const SmearGeom &g, const double2 *U, const double2 *G, double2 *F, hipStream_t s);

@@ -513,17 +513,10 @@ __global__ void __launch_bounds__(256) k_ff_unitarize_adjoint(SmearGeom g, const
     st(gf, V, s, add(mul_nn(Mx, G), mul_na(Kh, Vm)));
 }
 
-__global__ void k_field_axpby(double2 *out, double a, const double2 *in, double b, size_t n)
+__global__ void k_field_copy(double2 *out, const double2 *in, size_t n)
 {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const double2 v = in[i];
-        if (a == 0.0) {   // out may hold anything (never read)
-            out[i] = make_double2(b * v.x, b * v.y);
-        } else {
-            const double2 o = out[i];
-            out[i] = make_double2(a * o.x + b * v.x, a * o.y + b * v.y);
-        }
-    }
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+        out[i] = in[i];
 }
 
 __global__ void __launch_bounds__(256) k_ff_project(SmearGeom g, const double2 *U, const double2 *G, double2 *F)
@@ -610,11 +603,10 @@ hipError_t launch_ff_unitarize_adjoint(const SmearGeom &g, const double2 *V, dou
     return hipGetLastError();
 }
 
-hipError_t launch_field_axpby(double2 *out, double a, const double2 *in, double b, size_t n, hipStream_t s)
+hipError_t launch_field_copy(double2 *out, const double2 *in, size_t n, hipStream_t s)
 {
     const size_t blocks = (n + 255) / 256;
-    hipLaunchKernelGGL(k_field_axpby, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, s, out, a, in, b,
-                       n);
+    hipLaunchKernelGGL(k_field_copy, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, s, out, in, n);
     return hipGetLastError();
 }
 

@@ -412,7 +412,7 @@ hisq_status hisq_fermion_force(hisq_lattice lat, const double *U, int n, const d
     if ((st = stage_in(lat, U, flags, w.field(24), &src)) != HISQ_OK) return st;
     HIPCHK(lat, launch_smear_to_planar(g, src, w.field(0), lat->s));
     HIPCHK(lat, run_fat7(g, w.field(0), w.field(4), w.field(32), w.field(44), nullptr, LV1, fsz, lat->s, true));
-    HIPCHK(lat, launch_field_axpby(w.field(8), 0.0, w.field(4), 1.0, 4 * fsz, lat->s));
+    HIPCHK(lat, launch_field_copy(w.field(8), w.field(4), 4 * fsz, lat->s));
     HIPCHK(lat, hipMemsetAsync(w.bad, 0, sizeof(int), lat->s));
     HIPCHK(lat, launch_smear_unitarize(g, w.field(8), w.bad, lat->s));
     if ((st = check_projection(lat, w.bad)) != HISQ_OK) return st;

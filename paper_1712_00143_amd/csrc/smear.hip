@@ -4,11 +4,11 @@
 // The smearing (the link construction of the HISQ action, Follana et al.,
 // hep-lat/0610092; the paper's run-time breakdown in Section 2 lists it
 // beside the two forces) is a sum of path products of 3x3 matrices.  The
-// 5- and 7-link staples are staples of staples, so one kernel, the staple of
-// a field M through one direction, builds all of them: the host walks
-// nu -> rho -> sigma and every pass reads the previous pass's output (see
-// smear.cpp).  Each pass touches a handful of planar fields once, so it is
-// bound by HBM traffic (about 1.1 flop per byte), not by the FP64 units.
+// 5- and 7-link staples are staples of staples, so one operation, the staple of
+// a field M through one direction, builds all of them: three passes, each
+// reading the previous pass's fields (see smear.cpp).  A pass does a few flops
+// per byte of its planar fields, so traffic and load latency bound it, not the
+// FP64 units.
 #include "gforce.h"
 #include "hisq_dev.h"
 #include "smear.h"
