@@ -562,7 +562,7 @@ def run_smear(args):
     print(json.dumps({"smear_32^4": smear_summary(args)}), flush=True)
 
 
-GF_FLOP_PER_LINK = 145 * 198 + 60   # 3x3 complex products per link (see gforce.hip) and the projection
+GF_FLOP_PER_LINK = 74 * 198 + 60   # 3x3 complex products per link (see gforce.hip) and the projection
 
 
 def one_loop_coefs(u0):
