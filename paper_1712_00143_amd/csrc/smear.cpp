@@ -247,7 +247,7 @@ hisq_status hisq_gauge_force(hisq_lattice lat, const double *U, double beta, con
     // The kernel around even sites does half the work (12^4 137 us against 204
     // with the direct sum, 32^4 4.35 ms against 6.64, conversions included).  Up
     // to about 8^4 either takes the latency of one block, 112 us against 110;
-    // from 2^26 sites on its plane offsets overflow.
+    // from 53.7 million sites on its byte offsets overflow (su3.h).
     const bool even = g.V > 8192 && g.P < BUF_MAX_P;
     const double2 *src;
     if ((st = stage_in(lat, U, flags, w.field(8), &src)) != HISQ_OK) return st;

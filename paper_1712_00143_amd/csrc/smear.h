@@ -74,9 +74,10 @@ hipError_t launch_smear_pass3(const SmearGeom &g, const Pass3Args &a, hipStream_
 // tiles of 64 x-y-z sites times runs of tch time slices.
 void tile_grid(const SmearGeom &g, int target, int *ntile, int *tch, int *nblocks);
 
-// The staple passes address planes through buffer resources (su3.h), good for
-// plane strides below this many sites.
-constexpr long long BUF_MAX_P = 1LL << 26;
+// The staple passes address planes through buffer resources (su3.h) that hold
+// five planes of 16-byte elements in 2^32 - 1 bytes: good for plane strides
+// below this many sites (53.7 million).
+constexpr long long BUF_MAX_P = 0xffffffffLL / 80;
 
 // [V][4][3][3] complex (site-major) -> four-direction planar field; split: the
 // even sites first in every plane (slot lex / 2), then the odd ones.

@@ -42,10 +42,13 @@ __device__ __forceinline__ void st(double2 *__restrict__ f, size_t V, long long 
 // 32-bit byte offset per site, where 64-bit per-lane addresses of 9 planes a
 // matrix took a fifth of the vector instructions and, hoisted out of the site
 // loops, enough registers to spill.  `f` must be the same for the whole
-// wavefront.  Two resources per field (planes 0-4 and 5-8) keep the plane
-// offsets below 2^32 up to P = 2^26 sites; the entry points that use these
-// keep at least 51 fields (144 P bytes each), so memory ends first, or check it
-// (BUF_MAX_P).
+// wavefront.  Two resources per field, planes 0-4 and 5-8, of 2^32 - 1 bytes:
+// the last plane of the first starts 64 P bytes into it and a lane adds up to
+// 16 P, so P has to stay below 2^32 / 80 sites (BUF_MAX_P; the range check may
+// count the scalar plane offset with the lane's, and would then drop what lies
+// beyond).  The entry points that use these keep at least 51 fields (144 P
+// bytes each), so memory ends first, or check P.
+static_assert(5 * 16 * BUF_MAX_P <= 0xffffffffLL, "planes 0-4 of a field lie in one resource");
 
 typedef unsigned int b128 __attribute__((ext_vector_type(4)));
 
