@@ -214,6 +214,10 @@ hisq_status hisq_cg_noalloc(hisq_lattice lat, double mass, const double *b, doub
  * whose FP64 true residual is above tol are then refined with mixed CG
  * (all nrhs*nshift refinements advance together, sharing link reads; their
  * status is checked every min(check_every, 4) iterations).
+ * Workspace during the call: 24 nrhs V/2 bytes for each of 3 + 2 nshift
+ * vectors and of min(check_every, 8) residuals (down to one, at some speed, if
+ * the device has no room for more), 48 nrhs V/2 for each of 1 + nshift FP64
+ * vectors; the refinement's own set is kept until hisq_destroy.
  * info: nrhs*nshift entries (or NULL). */
 hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nshift, const double *shifts,
                                int nrhs, const double *b, double *x,

@@ -8,9 +8,10 @@
 //   r_j -= alpha_j Ap_j                                          [k_ms RUPDATE]
 //   beta_j, zeta_{j,k}, alpha_{j,k}, beta_{j,k}                  [k_finish FIN_MS, FP64]
 //   p_j = r_j + beta_j p_j                                       [k_ms PUPDATE]
-// and once per MSRING iterations, for each of them in turn,
+// and once per MSRING iterations (fewer if check_every or the memory for their
+// residuals is), for each of them in turn,
 //   x_{j,k} += alpha_{j,k} p_{j,k}; p_{j,k} = zeta_{j,k} r_j + beta_{j,k} p_{j,k}
-//                                                                [k_ms FLUSH, one pass]
+//                                                                [k_ms_flush, one pass]
 // Refinement phase: every (j, k) is finished by the batched mixed-precision
 // CG with FP64 reliable updates, warm-started from x_{j,k}, until its FP64
 // true residual || b_j - (A + sigma_k) x || / ||b_j|| reaches tol.
@@ -117,12 +118,27 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
     HIPCHK(lat, hipMalloc(&W.dms, sizeof(ShiftState) * nrhs));
     HIPCHK(lat, hipHostMalloc(&W.hms, sizeof(ShiftState) * nrhs, hipHostMallocDefault));
     HIPCHK(lat, hipMalloc(&W.dred, sizeof(double) * (size_t)nrhs * ntile));
-    HIPCHK(lat, hipMalloc(&W.r, v32 * MSRING));
     for (void **q : {&W.p, &W.Ap, &W.t}) HIPCHK(lat, hipMalloc(q, v32));
     HIPCHK(lat, hipMalloc(&W.xs, v32 * nshift));
     HIPCHK(lat, hipMalloc(&W.ps, v32 * nshift));
     HIPCHK(lat, hipMalloc(&W.b64, v64));
     HIPCHK(lat, hipMalloc(&W.x64, v64 * nshift));
+
+    // tuned shape of the shared-link kernel (tuning runs before any capture)
+    const int group = std::min(4, nrhs);
+    const TuneChoice tcm = pick_shape_mrhs(lat, kprec, recon, group, (prm.flags & HISQ_NO_TUNE) != 0);
+
+    // The ring of residuals, after everything that the solve cannot do without:
+    // one slot is enough, and no chunk needs more than its iterations.
+    const int kchunk = prm.check_every > 0 ? prm.check_every : 16;
+    int ring = std::min(MSRING, kchunk);
+    for (;; ring /= 2) {
+        const hipError_t e = hipMalloc(&W.r, v32 * ring);
+        if (e == hipSuccess) break;
+        W.r = nullptr;
+        if (e != hipErrorOutOfMemory || ring == 1) return hip_err(lat, e, "hipMalloc(residuals)");
+        (void)hipGetLastError();
+    }
     HIPCHK(lat, hipMemcpyAsync(W.ddesc, hd.data(), sizeof(ProbDesc) * nrhs, hipMemcpyHostToDevice, s));
     HIPCHK(lat, hipMemcpyAsync(W.dt2p, t2p.data(), sizeof(int) * t2p.size(), hipMemcpyHostToDevice, s));
     HIPCHK(lat, hipMemcpyAsync(W.b64, b, v64, dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
@@ -168,9 +184,6 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
     HIPCHK(lat, launch_ms(BL_MS_INIT, bl, ntot, s));
     HIPCHK(lat, launch_finish(W.ddesc, W.dst, W.dred, FIN_NORM_B, ST_RUNNING, 1, nrhs, s, nullptr, 0, 1));
 
-    // tuned shape of the shared-link kernel (tuning runs before any capture)
-    const int group = std::min(4, nrhs);
-    const TuneChoice tcm = pick_shape_mrhs(lat, kprec, recon, group, (prm.flags & HISQ_NO_TUNE) != 0);
     auto mrhs = [&](int out_par, int epi, const void *in, void *out, const void *aux) -> hipError_t {
         MrhsLaunch a;
         memset(&a, 0, sizeof a);
@@ -190,7 +203,7 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
         a.want = ST_RUNNING;
         return launch_dslash_mrhs(kprec, recon, group, tcm.W, a, ntile, s);
     };
-    // iteration q of a run of m <= MSRING: reads r from ring slot q, writes the
+    // iteration q of a run of m <= ring: reads r from ring slot q, writes the
     // new one to slot q + 1 (the last one to slot 0, where the next run starts)
     auto iterate = [&](int q, int m) -> hipError_t {
         hipError_t e;
@@ -209,10 +222,10 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
         bl.slot = bl.slot2;
         return launch_ms(BL_MS_PUPDATE, bl, ntot, s);
     };
-    // n iterations in runs of MSRING, each followed by its shift updates
+    // n iterations in runs of `ring`, each followed by its shift updates
     auto iterations = [&](int n) -> hipError_t {
         while (n > 0) {
-            const int m = std::min(n, MSRING);
+            const int m = std::min(n, ring);
             hipError_t e;
             for (int q = 0; q < m; q++)
                 if ((e = iterate(q, m)) != hipSuccess) return e;
@@ -224,7 +237,6 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
         return hipSuccess;
     };
 
-    const int kchunk = prm.check_every > 0 ? prm.check_every : 16;
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     const bool use_graph = (prm.flags & HISQ_USE_GRAPH) != 0;
@@ -261,6 +273,8 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
     // x_{j,k} to FP64 for the refinement
     HIPCHK(lat, launch_convert(W.xs, 1, W.x64, 0, (long long)nrhs * nshift * h * 3, s));
     HIPCHK(lat, hipStreamSynchronize(s));
+    HIPCHK(lat, hipFree(W.r));   // the refinement may need the ring's memory
+    W.r = nullptr;
     const double t_krylov = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
 
     // refinement: one batched mixed CG over all (j, k), warm start.  The
