@@ -350,7 +350,9 @@ __global__ void __launch_bounds__(192) k_ms(BlasLaunch a)
 // right-hand side (h is a multiple of 8, so pairs are 16-byte aligned and never
 // straddle the end of a vector) and holds four shifts' loads in flight: with
 // one shift at a time and 8-byte loads a flush of 8 iterations took 463 us for
-// its 1.6 GB.  blockIdx.y: right-hand side.
+// its 1.6 GB.  A right-hand side that goes on has p = r + beta p of the run's
+// last iteration here too (a launch of its own otherwise, which check_every = 1
+// would pay on every iteration).  blockIdx.y: right-hand side.
 __global__ void __launch_bounds__(256) k_ms_flush(BlasLaunch a)
 {
     const int j = blockIdx.y;
@@ -362,6 +364,12 @@ __global__ void __launch_bounds__(256) k_ms_flush(BlasLaunch a)
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     const float4 *r = reinterpret_cast<const float4 *>(a.v[0]) + pd.voff * 3 / 2 + i;
+    if (a.states[j].status == ST_RUNNING) {
+        const float be = (float)a.states[j].beta;
+        float4 *p = reinterpret_cast<float4 *>(a.v[3]) + pd.voff * 3 / 2 + i;
+        const float4 r0 = r[0], p0 = *p;
+        *p = make_float4(r0.x + be * p0.x, r0.y + be * p0.y, r0.z + be * p0.z, r0.w + be * p0.w);
+    }
     const int ns = ms->nshift;
     float4 *xs = reinterpret_cast<float4 *>(a.v[2]) + (long long)j * ns * n + i;
     float4 *ps = reinterpret_cast<float4 *>(a.v[4]) + (long long)j * ns * n + i;

@@ -117,8 +117,8 @@ enum : int {
     BL_MS_RUPDATE = 10,  // multi-shift: r' = r - alpha Ap (next ring slot); partial |r'|^2 (FIN_MS)
     // launch_ms_flush: the pending iterations in turn: x_k += a_k p_k; p_k = z_k r' + b_k p_k
     BL_MS_INIT = 12,     // multi-shift: r = p = b (FP32); p_k = b; x_k = 0; partial |b|^2
-    BL_STATUS_MS = 13,   // after a flush: nothing pending, MS_LAST -> CONVERGED (one thread per problem)
-    BL_MS_PUPDATE = 16,  // multi-shift: p = r + beta p
+    BL_STATUS_MS = 13,   // after a flush: nothing pending, MS_LAST -> CONVERGED (one block per problem)
+    BL_MS_PUPDATE = 16,  // multi-shift: p = r + beta p (the flush does it for a run's last iteration)
     // The CG update with its finishers folded in: every block sums its
     // problem's compact tile sums itself (same order, same bits in every block).
     BL_RUPDATE_F = 14,   // snapshot the state; alpha = rr / sum(p.Ap); r -= alpha Ap; x += alpha p; |r|^2 to red

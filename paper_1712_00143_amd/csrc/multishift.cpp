@@ -7,7 +7,7 @@
 //   alpha_j = rr_j / (p_j, Ap_j)                                 [k_finish]
 //   r_j -= alpha_j Ap_j                                          [k_ms RUPDATE]
 //   beta_j, zeta_{j,k}, alpha_{j,k}, beta_{j,k}                  [k_finish FIN_MS, FP64]
-//   p_j = r_j + beta_j p_j                                       [k_ms PUPDATE]
+//   p_j = r_j + beta_j p_j                                       [k_ms PUPDATE, k_ms_flush]
 // and once per MSRING iterations (fewer if check_every or the memory for their
 // residuals is), for each of them in turn,
 //   x_{j,k} += alpha_{j,k} p_{j,k}; p_{j,k} = zeta_{j,k} r_j + beta_{j,k} p_{j,k}
@@ -220,7 +220,7 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
             return e;
         bl.fin = FIN_NONE;
         bl.slot = bl.slot2;
-        return launch_ms(BL_MS_PUPDATE, bl, ntot, s);
+        return q + 1 == m ? hipSuccess : launch_ms(BL_MS_PUPDATE, bl, ntot, s);   // the last one: in the flush
     };
     // n iterations in runs of `ring`, each followed by its shift updates
     auto iterations = [&](int n) -> hipError_t {
