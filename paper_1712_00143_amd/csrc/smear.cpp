@@ -77,7 +77,9 @@ hisq_status get_work(hisq_lattice lat, int nf, Work &w, size_t extra = 0)
 
 // out (4 planar fields) = fat7(U (4 planar fields)): one pass 1 for every
 // direction, then per output direction one pass 2 (its 5-staple sums) and one
-// pass 3 (their c5 share, the 7-staples and the Lepage term).  T1all: 12 fields (every direction's 3-staples).  Hall: 24
+// pass 3 (their c5 share, the 7-staples and the Lepage term); without 5- and
+// 7-link terms one pass 3 for every direction.  T1all: 12 fields (every
+// direction's 3-staples).  Hall: 24
 // fields for the single-sign 3-staples, needed when cL != 0 (and kept for
 // the adjoint).  keep: T2all holds 12 fields and direction mu's 5-staple
 // sums stay in its fields 3 mu .. 3 mu + 2 (for the adjoint); otherwise
@@ -90,10 +92,14 @@ hipError_t run_fat7(const SmearGeom &g, const double2 *U, double2 *out, double2 
     Pass1Args p1{U, out, need5 ? T1all : nullptr, lep ? Hall : nullptr, c[0], c[1]};
     hipError_t e = launch_smear_pass1(g, p1, s);
     if (e != hipSuccess || !(need5 || lep)) return e;
+    if (!need5) {
+        const Pass3Args p3{U, nullptr, Hall, out, 0.0, 0.0, c[4], 0};
+        return launch_smear_pass3(g, p3, s);
+    }
     for (int mu = 0; mu < 4; mu++) {
-        double2 *T2 = !need5 ? nullptr : keep ? T2all + (size_t)3 * mu * fsz : T2all;
+        double2 *T2 = keep ? T2all + (size_t)3 * mu * fsz : T2all;
         const Pass2Args p2{U, T1all + (size_t)3 * mu * fsz, T2, mu};
-        if (need5 && (e = launch_smear_pass2(g, p2, s)) != hipSuccess) return e;
+        if ((e = launch_smear_pass2(g, p2, s)) != hipSuccess) return e;
         const Pass3Args p3{U, T2, lep ? Hall : nullptr, out + (size_t)mu * fsz, c[2], c[3], c[4], mu};
         if ((e = launch_smear_pass3(g, p3, s)) != hipSuccess) return e;
     }

@@ -40,7 +40,8 @@ inline long long plane_stride(long long V)
 //   pass 2 (mu)  for each k, sig = nu_k and {nu, rho} the other two:
 //                T2_k = staple of T1_nu through rho + staple of T1_rho
 //                through nu (all 5-link staples whose steps avoid sig);
-//   pass 3 (mu)  F_mu += sum over k of c5 T2_k + (the staple through sig of
+//   pass 3 (mu; every mu in one launch without 5- and 7-link terms)
+//                F_mu += sum over k of c5 T2_k + (the staple through sig of
 //                c7 T2_k + cL H+_k on the + side, c7 T2_k + cL H-_k on the
 //                - side): the 7-link staples through sig and the two-step
 //                (Lepage) staples.
@@ -61,9 +62,9 @@ struct Pass3Args {
     const double2 *U;
     const double2 *T2;   // three fields, or null: no 5- and 7-link terms
     const double2 *H;    // the twenty-four H fields of pass 1, or null: no Lepage term
-    double2 *F;          // the field of mu
+    double2 *F;          // the field of mu, without T2 all four
     double c5, c7, cL;
-    int mu;
+    int mu;              // unused without T2
 };
 
 hipError_t launch_smear_pass1(const SmearGeom &g, const Pass1Args &a, hipStream_t s);

@@ -190,6 +190,8 @@ __global__ void __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(1, 2))
 // image).  The staple is linear in what it transports, so one set of products
 // serves both (a Lepage pass of its own took 1.19 ms at 32^4, the two extra
 // fields 0.63 ms here).  T: T2 is read (5- and 7-link terms); H: the Lepage term.
+// Without T2, which holds one output direction at a time, blockIdx.y is mu and
+// one launch serves all four (launch_smear_pass3).
 // The three waves' terms meet in LDS and wave 0 updates F once, adding them in
 // the order of k.
 template <bool T, bool H>
@@ -204,7 +206,7 @@ __global__ void __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(1, 2))
     const bool valid = i0 < g.S[3];
     const int i = valid ? i0 : 0;
     const size_t V = (size_t)g.P;   // plane stride
-    const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), mu = a.mu;
+    const int k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), mu = T ? a.mu : (int)blockIdx.y;
     const int sig = other_dir(k, mu);
     int x[4];
     {
@@ -217,7 +219,7 @@ __global__ void __launch_bounds__(192) __attribute__((amdgpu_waves_per_eu(1, 2))
     const int Sm = pick(g.S, mu), Lm = pick(g.L, mu), Ss = pick(g.S, sig), Ls = pick(g.L, sig);
     const double2 *Us = a.U + (size_t)sig * 9 * V, *T2 = T ? a.T2 + (size_t)k * 9 * V : nullptr;
     const double2 *Hk = H ? a.H + (size_t)(6 * mu + 2 * k) * 9 * V : nullptr;
-    double2 *F = a.F;
+    double2 *F = a.F + (T ? 0 : (size_t)mu * 9 * V);
     __shared__ double2 red[2][9][64];
     // the transported field of sign q (0: +, 1: -) at y
     auto field = [&](int q, int y) {
@@ -435,7 +437,7 @@ hipError_t launch_smear_pass3(const SmearGeom &g, const Pass3Args &a, hipStream_
     const dim3 grid((unsigned)nb), blk(192);
     if (a.T2 && a.H) hipLaunchKernelGGL((k_smear_pass3<true, true>), grid, blk, 0, s, g, a, ntile, tch);
     else if (a.T2) hipLaunchKernelGGL((k_smear_pass3<true, false>), grid, blk, 0, s, g, a, ntile, tch);
-    else if (a.H) hipLaunchKernelGGL((k_smear_pass3<false, true>), grid, blk, 0, s, g, a, ntile, tch);
+    else if (a.H) hipLaunchKernelGGL((k_smear_pass3<false, true>), dim3((unsigned)nb, 4), blk, 0, s, g, a, ntile, tch);
     return hipGetLastError();
 }
 
