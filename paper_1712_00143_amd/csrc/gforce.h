@@ -47,4 +47,18 @@ hipError_t launch_gauge_force(const SmearGeom &g, const GForceArgs &a, int mode,
 // launch_smear_to_planar's split order), for P < BUF_MAX_P.
 hipError_t launch_gauge_force_even(const SmearGeom &g, const GForceArgs &a, hipStream_t s);
 
+// Whether the force comes from launch_gauge_force_even: it does half the
+// direct sum's work (12^4 137 us against 204, 32^4 4.35 ms against 6.64, layout
+// conversions included).  Up to 64 sites per CU, 16384, the direct sum takes the
+// latency of one block, and that is the shorter one where there are rectangles,
+// whose partial products it shares (8^3x18 115 us against 120 and, without
+// parallelograms, 63 against 79; 8^3x32 116 against 128 and 66 against 82;
+// above the line 12^3x10 200 against 135 and 104 against 86).  Without rectangles
+// the line is at 8192 sites (8^3x18 64 us against 51).  From 53.7 million sites
+// on byte offsets overflow (su3.h).
+inline bool gauge_force_even_serves(const SmearGeom &g, double cr)
+{
+    return g.V > (cr == 0.0 ? 8192 : 16384) && g.P < BUF_MAX_P;
+}
+
 }  // namespace hisq

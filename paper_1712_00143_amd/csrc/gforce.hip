@@ -6,9 +6,10 @@
 // the force on U_mu(x) is (beta/3) TA[U_mu(x) B^+], B the weighted sum of
 // the paths from x to x+mu that close each loop through the link.
 //
-// The force comes from k_gauge_force_even (below).  The action, and the force
-// of lattices beyond its 32-bit offsets, from the direct sum: one thread per
-// link, the whole staple sum in registers:
+// The force comes from k_gauge_force_even (below), on small lattices and on
+// those beyond its 32-bit offsets from the direct sum (gauge_force_even_serves),
+// as the action always does: one thread per link, the whole staple sum in
+// registers:
 // 6 signed transverse steps n, each giving the plaquette and the three
 // rectangles (11 products with the shared prefix and suffix factored out),
 // and 24 parallelograms (b, a, mu, -b, -a), summed over b before the common

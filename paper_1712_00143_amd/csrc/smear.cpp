@@ -250,11 +250,7 @@ hisq_status hisq_gauge_force(hisq_lattice lat, const double *U, double beta, con
     Work w;
     if ((st = get_work(lat, 12, w)) != HISQ_OK) return st;   // U 0-3, F 4-7, staging 8-11
     const SmearGeom g = geom_of(lat);
-    // The kernel around even sites does half the work (12^4 137 us against 204
-    // with the direct sum, 32^4 4.35 ms against 6.64, conversions included).  Up
-    // to about 8^4 either takes the latency of one block, 112 us against 110;
-    // from 53.7 million sites on its byte offsets overflow (su3.h).
-    const bool even = g.V > 8192 && g.P < BUF_MAX_P;
+    const bool even = gauge_force_even_serves(g, coef[1]);
     const double2 *src;
     if ((st = stage_in(lat, U, flags, w.field(8), &src)) != HISQ_OK) return st;
     HIPCHK(lat, launch_smear_to_planar(g, src, w.field(0), lat->s, even));

@@ -42,3 +42,32 @@ def test_last_byte_of_the_last_plane_fits_the_resource(tmp_path):
     for v, p in zip(vols, strides):
         fits = 5 * 16 * p <= records
         assert (p < bound) == fits, (v, p)
+
+
+RULE = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "gforce.h"
+int main(int argc, char **argv)
+{
+    for (int k = 1; k < argc; k++) {
+        hisq::SmearGeom g{};
+        g.V = std::atoll(argv[k]);
+        g.P = hisq::plane_stride(g.V);
+        std::printf("%d%d ", hisq::gauge_force_even_serves(g, -0.08), hisq::gauge_force_even_serves(g, 0.0));
+    }
+}
+"""
+
+
+def test_gauge_force_kernel_rule(tmp_path):
+    """Which lattices the kernel around even sites serves, with and without
+    rectangles: not the small ones, nor those beyond its offsets."""
+    src, exe = tmp_path / "rule.cpp", tmp_path / "rule"
+    src.write_text(RULE)
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC, str(src), "-o",
+                    str(exe)], check=True, capture_output=True, text=True)
+    vols = {8192: "00", 8208: "01", 16384: "01", 16400: "11", 32 ** 4: "11", 84 ** 4: "11", 64 ** 3 * 200: "11",
+            64 ** 3 * 208: "00", 88 ** 4: "00", 100 ** 4: "00"}
+    out = subprocess.run([str(exe)] + [str(v) for v in vols], check=True, capture_output=True, text=True).stdout
+    assert out.split() == list(vols.values())

@@ -110,3 +110,17 @@ def test_gauge_force_ragged_even_tiles(dims, coefs):
     F = lat.gauge_force(U, 6.5, coefs)
     check(np.asarray(F).reshape(-1, 9), oracle.gauge_force(dims, U, 6.5, coefs).reshape(-1, 9), 1e-13, (dims, coefs))
     lat.close()
+
+
+@pytest.mark.parametrize("coefs", [(1.0, -0.08, -0.01), (0.0, 1.0, 0.0), (1.0, -0.08, 0.0)])
+@pytest.mark.parametrize("dims", [(8, 8, 16, 16), (6, 14, 14, 14), (34, 4, 4, 32), (10, 12, 12, 12), (20, 6, 10, 14)])
+def test_gauge_force_either_side_of_the_rectangle_line(dims, coefs):
+    """With rectangles the kernel around even sites starts above 16384 sites:
+    the largest lattice that the direct sum takes and, of those above, ragged and
+    whole last tiles of 64 even sites, x extents that do not divide a tile."""
+    H = _hisq()
+    U = synth.thin_links(dims, 0.4, 72)
+    lat = H.Lattice(dims)
+    F = lat.gauge_force(U, 6.5, coefs)
+    check(np.asarray(F).reshape(-1, 9), oracle.gauge_force(dims, U, 6.5, coefs).reshape(-1, 9), 1e-13, (dims, coefs))
+    lat.close()
