@@ -21,9 +21,8 @@ struct GForceArgs {
     int ntile, tch;   // set by the launcher
 };
 
-// Grid of the kernel (and of the smearing's pass 1): ntile tiles of 64
-// x-y-z sites times runs of tch time slices; nblocks (= the number of
-// action partials).
+// Grid of the kernel: ntile tiles of 64 x-y-z sites times runs of tch time
+// slices; nblocks (= the number of action partials).
 void gauge_force_grid(const SmearGeom &g, int *ntile, int *tch, int *nblocks);
 
 // The x-y-z tile a block of that grid takes for its tile index, a

@@ -48,7 +48,7 @@ __device__ __forceinline__ M3 staple_at(const double2 *__restrict__ U, const dou
 
 // Pass 1 of every output direction at once: a block holds 64 sites of one
 // x-y-z slab, one wave per direction mu, and walks a run of tch time slices
-// (the block grid of gauge_force_grid), so that the neighbour links one
+// (launch_smear_pass1), so that the neighbour links one
 // direction's staples fetch serve the other directions from L1 / L2 and the
 // t neighbours are the block's own recent loads.  For each mu, the 3-link
 // staples through the three nu != mu, stored as T1[3 mu + k] when WT (and
@@ -396,8 +396,12 @@ __global__ void __launch_bounds__(256) k_smear_unitarize(SmearGeom g, double2 *_
 hipError_t launch_smear_pass1(const SmearGeom &g, const Pass1Args &a, hipStream_t s)
 {
     if (g.P >= BUF_MAX_P) return hipErrorInvalidValue;
+    // 2048 blocks (32^4: 1.05 ms with the conversions, 1.07 with 512), but runs of
+    // a single time slice reuse nothing: two full loads of the CUs, at one block
+    // each, then (16^3x32 129 us against 141, 16^4 73 against 77)
     int ntile, tch, nb;
-    gauge_force_grid(g, &ntile, &tch, &nb);
+    tile_grid(g, 2048, &ntile, &tch, &nb);
+    if (tch == 1 && nb > 512) tile_grid(g, 512, &ntile, &tch, &nb);
     const dim3 grid((unsigned)nb), blk(256);
     const bool wt = a.T1 != nullptr, wh = a.H != nullptr;
     if (wt && wh) hipLaunchKernelGGL((k_smear_pass1<true, true>), grid, blk, 0, s, g, a, ntile, tch);
@@ -407,7 +411,7 @@ hipError_t launch_smear_pass1(const SmearGeom &g, const Pass1Args &a, hipStream_
     return hipGetLastError();
 }
 
-// The tile grid of gauge_force_grid aimed at `target` blocks: fewer blocks
+// A tile grid aimed at `target` blocks: fewer blocks
 // walk longer runs of time slices.  Passes 2 and 3 take 512 (at 32^4 every
 // block walks the whole time extent: pass 3 310 us against 322 with 2048
 // blocks, pass 2 unchanged).

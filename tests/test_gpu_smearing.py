@@ -166,3 +166,19 @@ def test_singular_level_one_is_reported():
         lat.cg(0.1, synth.gaussian_even(dims, 1))
     assert e.value.status == H.HISQ_ERR_STATE
     lat.close()
+
+
+@pytest.mark.parametrize("dims", [(16, 16, 32, 10), (6, 14, 22, 34)])
+def test_first_pass_in_runs_of_a_few_slices(dims):
+    """Lattices whose tiles would give pass 1 single time slices take longer
+    runs: of 3, 3, 3 and 1 slices, and of 2 with a ragged last tile of 64."""
+    H = _hisq()
+    U = synth.thin_links(dims, 0.4, 57)
+    lat = H.Lattice(dims)
+    for c in ((0.7, -0.3, 0.0, 0.0, 0.0), (0.7, -0.3, 0.0, 0.0, 0.2)):
+        check(_links(lat.fat7(c, U)), _links(oracle.fat7(dims, U, c)), TOL, ("fat7", dims, c))
+    f, l = lat.smear_links(U)
+    fr, lr = oracle.hisq_smear(dims, U)
+    check(_links(f), _links(fr), TOL, ("fat", dims))
+    check(_links(l), _links(lr), TOL, ("long", dims))
+    lat.close()
