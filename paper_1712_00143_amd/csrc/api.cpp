@@ -673,13 +673,23 @@ TuneChoice pick_shape(hisq_lattice lat, int prec, int recon, const ProbDesc *dde
     return best;
 }
 
-TuneChoice pick_shape_mrhs(hisq_lattice lat, int prec, int recon, int nr, bool no_tune)
+// Launch shape of the multi-RHS Dslash for groups of nr right-hand sides,
+// `several` of them in a launch or one.  What is fastest for one group need not
+// be for several, which share the links through L2 (16^3x32, FP32 recon-12: two
+// waves 15.3 us a launch of four against 15.9 with four, but 44 against 38.5 for
+// twelve and 55 against 48.5 for sixteen; recon-18: four and sixteen waves within
+// 3 % for four, 36.6 against 30.4 us for five), so one timing run stores a choice
+// for each, the second from three groups.  A saved choice that knows one group
+// only serves both.
+TuneChoice pick_shape_mrhs(hisq_lattice lat, int prec, int recon, int nr, bool no_tune, bool several)
 {
     TuneChoice def;
     def.W = prec == 0 ? 8 : 4;
     def.remap = 1;
     if (no_tune || Tuner::get().disabled() || nr < 1 || nr > 4) return def;
-    TuneChoice *own = &lat->mrhs_shape[prec * 2 + (recon == 12)][nr - 1];
+    const bool both = nr == 4 && prec != 0;   // the second choice: FP32 vectors only
+    several = several && both;
+    TuneChoice *own = &lat->mrhs_shape[prec * 2 + (recon == 12)][several ? 4 : nr - 1];
     if (own->us > 0) return *own;
     const std::string arch = arch_name(lat->device);
     if (arch.empty()) return def;
@@ -688,65 +698,78 @@ TuneChoice pick_shape_mrhs(hisq_lattice lat, int prec, int recon, int nr, bool n
     std::string key = ks.str();
     for (auto &ch : key)
         if (ch == ' ') ch = '_';
+    const std::string gkey = key + ":several";
     TuneChoice c;
+    if (several && Tuner::get().lookup(gkey, c)) return *own = c;
     if (Tuner::get().lookup(key, c)) return *own = c;
-    DVec in, out;
-    const int vprec = prec == 0 ? 0 : 1;   // FP64 vectors with FP64 links, FP32 otherwise
-    if (dvec_alloc(in, vprec, lat->h * nr) != hipSuccess || dvec_alloc(out, vprec, lat->h * nr) != hipSuccess) {
-        dvec_free(in);
-        dvec_free(out);
-        return def;
-    }
-    (void)hipMemsetAsync(in.p, 0, in.bytes, lat->s);
     hipEvent_t e0, e1;
     (void)hipEventCreate(&e0);
     (void)hipEventCreate(&e1);
-    TuneChoice best = def;
-    best.us = 1e30;
+    // the fastest of `shapes` (waves per block) and tile orders from r0 on, for n
+    // right-hand sides; us 1e30 if the vectors do not fit
+    auto time_shapes = [&](int n, const std::vector<int> &shapes, int r0, const std::string &k) {
+        TuneChoice best = def;
+        best.us = 1e30;
+        DVec in, out;
+        const int vprec = prec == 0 ? 0 : 1;   // FP64 vectors with FP64 links, FP32 otherwise
+        if (dvec_alloc(in, vprec, lat->h * n) == hipSuccess && dvec_alloc(out, vprec, lat->h * n) == hipSuccess) {
+            for (int W : shapes)
+                for (int remap = r0; remap < 2; remap++) {
+                    MrhsLaunch a;
+                    memset(&a, 0, sizeof a);
+                    a.probs = lat->ddesc;
+                    a.desc_stride = 0;
+                    a.remap = remap;
+                    a.lslot = prec * 2 + (recon == 12);
+                    a.nrhs = n;
+                    a.vstride = lat->h;
+                    a.in = in.p;
+                    a.out = out.p;
+                    a.epi = EPI_PLAIN;
+                    bool ok = true;
+                    for (int r = 0; r < 2 && ok; r++)
+                        ok = launch_dslash_mrhs(prec, recon, nr, W, a, lat->ntile, lat->s) == hipSuccess;
+                    if (!ok) continue;
+                    const int reps = 6;
+                    (void)hipEventRecord(e0, lat->s);
+                    for (int r = 0; r < reps; r++)
+                        (void)launch_dslash_mrhs(prec, recon, nr, W, a, lat->ntile, lat->s);
+                    (void)hipEventRecord(e1, lat->s);
+                    (void)hipEventSynchronize(e1);
+                    float ms = 0;
+                    (void)hipEventElapsedTime(&ms, e0, e1);
+                    const double us = 1000.0 * ms / reps;
+                    Tuner::get().note(k, W, remap, 0, us);
+                    if (us < best.us) {
+                        best.us = us;
+                        best.W = W;
+                        best.remap = remap;
+                    }
+                }
+        }
+        dvec_free(in);
+        dvec_free(out);
+        (void)hipGetLastError();
+        return best;
+    };
     // the vector-ALU kernel with 2-16 waves per block, and for groups of four
     // FP32-vector right-hand sides the matrix-core kernel
     std::vector<int> shapes{2, 4, 8, 16};
-    if (nr == 4 && prec != 0) shapes.push_back(MRHS_MFMA);
-    for (int W : shapes) {
-        for (int remap = 0; remap < 2; remap++) {
-            MrhsLaunch a;
-            memset(&a, 0, sizeof a);
-            a.probs = lat->ddesc;
-            a.desc_stride = 0;
-            a.remap = remap;
-            a.lslot = prec * 2 + (recon == 12);
-            a.nrhs = nr;
-            a.vstride = lat->h;
-            a.in = in.p;
-            a.out = out.p;
-            a.epi = EPI_PLAIN;
-            bool ok = true;
-            for (int r = 0; r < 2 && ok; r++) ok = launch_dslash_mrhs(prec, recon, nr, W, a, lat->ntile, lat->s) == hipSuccess;
-            if (!ok) continue;
-            const int reps = 6;
-            (void)hipEventRecord(e0, lat->s);
-            for (int r = 0; r < reps; r++) (void)launch_dslash_mrhs(prec, recon, nr, W, a, lat->ntile, lat->s);
-            (void)hipEventRecord(e1, lat->s);
-            (void)hipEventSynchronize(e1);
-            float ms = 0;
-            (void)hipEventElapsedTime(&ms, e0, e1);
-            const double us = 1000.0 * ms / reps;
-            Tuner::get().note(key, W, remap, 0, us);
-            if (us < best.us) {
-                best.us = us;
-                best.W = W;
-                best.remap = remap;
-            }
-        }
+    if (both) shapes.push_back(MRHS_MFMA);
+    TuneChoice best = time_shapes(nr, shapes, 0, key), bestg = def;
+    if (best.us < 1e29) Tuner::get().store(key, best);
+    else best = def;
+    if (both && best.us > 0) {
+        // neither the tile order nor two waves matter for several groups
+        std::vector<int> gs{4, 8, 16};
+        if (best.W == MRHS_MFMA) gs.push_back(MRHS_MFMA);
+        bestg = time_shapes(3 * nr, gs, 1, gkey);
+        if (bestg.us < 1e29) Tuner::get().store(gkey, bestg);
+        else bestg = best;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    dvec_free(in);
-    dvec_free(out);
-    (void)hipGetLastError();
-    if (best.us < 1e29) Tuner::get().store(key, best);
-    else best = def;
-    return best;
+    return several ? bestg : best;
 }
 
 }  // namespace hisq

@@ -358,14 +358,14 @@ hisq_status run_cg(hisq_lattice lat0, SolveSet &S, const hisq_solver_params &prm
     CgPlan pl{mode, recon, slot, tc.W, tc.remap, tc.cpol, {}};
     if (shared) {
         const int group = S.nprob < 4 ? S.nprob : 4;
-        pl.mrhs[group] = pick_shape_mrhs(lat0, mode, recon, group, (prm.flags & HISQ_NO_TUNE) != 0);
+        pl.mrhs[group] = pick_shape_mrhs(lat0, mode, recon, group, (prm.flags & HISQ_NO_TUNE) != 0, S.nprob > 4);
     }
     if (S.one_lattice) {
         // FP64 updates: up to four problems per link read (a group smaller
         // than four only when it holds the whole set, as the launch requires)
         const bool nt = (prm.flags & HISQ_NO_TUNE) != 0;
         pl.group64 = S.nprob < 4 ? S.nprob : 4;
-        pl.mrhs64 = pick_shape_mrhs(lat0, 0, 18, pl.group64, nt);
+        pl.mrhs64 = pick_shape_mrhs(lat0, 0, 18, pl.group64, nt, S.nprob > 4);
     }
 
     long long *dclock = S.dclock;

@@ -114,7 +114,8 @@ struct hisq_lattice_s {
     hisq::DVec tmp_in, tmp_out, tmp64a, tmp64b;  // host-pointer Dslash staging
     // launch shapes of this lattice's own operator already looked up (us > 0),
     // by link set slot: single RHS (tuned, streamed), multi-RHS by group size
-    hisq::TuneChoice shape[hisq::NLINKSET][2], mrhs_shape[hisq::NLINKSET][4];
+    // (the fifth: several groups of four)
+    hisq::TuneChoice shape[hisq::NLINKSET][2], mrhs_shape[hisq::NLINKSET][5];
     hisq::ProbDesc *ddesc = nullptr;             // this lattice alone
     double *dpart = nullptr;
     void *smear_ws = nullptr;                    // link-smearing workspace

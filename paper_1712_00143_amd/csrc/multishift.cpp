@@ -126,7 +126,7 @@ extern "C" hisq_status hisq_multishift_cg(hisq_lattice lat, double mass, int nsh
 
     // tuned shape of the shared-link kernel (tuning runs before any capture)
     const int group = std::min(4, nrhs);
-    const TuneChoice tcm = pick_shape_mrhs(lat, kprec, recon, group, (prm.flags & HISQ_NO_TUNE) != 0);
+    const TuneChoice tcm = pick_shape_mrhs(lat, kprec, recon, group, (prm.flags & HISQ_NO_TUNE) != 0, nrhs > 4);
 
     // The ring of residuals, after everything that the solve cannot do without:
     // one slot is enough, and no chunk needs more than its iterations.
@@ -359,7 +359,7 @@ hisq_status hisq_dslash_mrhs_impl(hisq_lattice lat, int out_parity, int prec, in
         dout = (char *)tmp + v32;
     }
     const int group = std::min(4, nrhs);
-    const TuneChoice tc = pick_shape_mrhs(lat, prec, recon, group, (flags & HISQ_NO_TUNE) != 0);
+    const TuneChoice tc = pick_shape_mrhs(lat, prec, recon, group, (flags & HISQ_NO_TUNE) != 0, nrhs > 4);
     MrhsLaunch a;
     memset(&a, 0, sizeof a);
     a.probs = lat->ddesc;

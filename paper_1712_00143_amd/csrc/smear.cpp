@@ -334,7 +334,7 @@ hisq_status ff_solutions_odd(hisq_lattice lat, int n, const double2 *X, double2 
 {
     if (n < 1) return HISQ_OK;
     const int group = n < 4 ? n : 4;
-    const TuneChoice tc = pick_shape_mrhs(lat, 0, 18, group, false);
+    const TuneChoice tc = pick_shape_mrhs(lat, 0, 18, group, false, n > group);
     MrhsLaunch a;
     memset(&a, 0, sizeof a);
     a.probs = lat->ddesc;

@@ -21,7 +21,7 @@ TuneChoice pick_shape(hisq_lattice lat, int prec, int recon, const ProbDesc *dde
 TuneChoice lookup_shape(hisq_lattice lat, int prec, int recon, int ntile, int nprob);
 // Tuned launch shape of the multi-right-hand-side Dslash (nr right-hand
 // sides per launch, FP32 vectors) on lattice lat.
-TuneChoice pick_shape_mrhs(hisq_lattice lat, int prec, int recon, int nr, bool no_tune);
+TuneChoice pick_shape_mrhs(hisq_lattice lat, int prec, int recon, int nr, bool no_tune, bool several);
 
 // Describe nprob problems (one per handle) in S: descriptors, tile map,
 // states, partials.  sigma is added to every diagonal (4 m^2 + sigma).

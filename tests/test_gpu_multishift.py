@@ -305,3 +305,60 @@ def test_multishift_deferred_updates_do_not_change_the_solve(graph):
         assert its == want[1], every
         assert np.array_equal(x, want[0]), every
     lat.close()
+
+
+_SEVERAL_GROUPS_CHILD = r"""
+import sys
+import numpy as np
+from paper_1712_00143_amd import hisq as H, synth
+dims = (8, 8, 8, 8)
+fat, lng = synth.make_links(dims, 0.2, 71)
+lat = H.Lattice(dims)
+lat.load_links(fat, lng)
+outs = []
+for p, r in ((1, 12), (2, 12)):
+    lat.prepare_links(p, r)
+    for n in (4, 13):
+        psi = synth.gaussian_even(dims, 80 + n, n)
+        outs.append(lat.dslash(1, p, r, psi, np.zeros_like(psi), nrhs=n))
+np.savez(sys.argv[1], *outs)
+lat.close()
+"""
+
+
+def test_launch_shape_of_several_groups(tmp_path):
+    """The choice for several groups of four is stored beside the one for one
+    group, is never a block of two waves, is used by a later process, and a saved
+    choice for one group alone serves both."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    cache = tmp_path / "tune.txt"
+    env = dict(os.environ, HISQ_TUNE_CACHE=str(cache))
+    env["PYTHONPATH"] = root + os.pathsep + env.get("PYTHONPATH", "")
+
+    def run(name):
+        out = tmp_path / name
+        r = subprocess.run([sys.executable, "-c", _SEVERAL_GROUPS_CHILD, str(out)], cwd=root, env=env,
+                           capture_output=True, text=True, timeout=200)
+        assert r.returncode == 0, r.stdout[-1000:] + r.stderr[-2000:]
+        with np.load(str(out) + ".npz") as z:
+            return [z[k] for k in z.files]
+
+    def lines():
+        return [ln.split() for ln in cache.read_text().splitlines() if ":nr4" in ln]
+
+    first = run("a")
+    got = lines()
+    assert len(got) == 4 and sum(":several" in ln[0] for ln in got) == 2
+    assert all(int(ln[1]) > 2 for ln in got if ":several" in ln[0])
+    again = run("b")
+    assert lines() == got
+    assert all(np.array_equal(u, v) for u, v in zip(first, again))
+    # one group alone known, as an older file has it: nothing is timed again
+    keep = [ln for ln in cache.read_text().splitlines() if ":several" not in ln]
+    cache.write_text("\n".join(keep) + "\n")
+    third = run("c")
+    assert cache.read_text().splitlines() == keep
+    assert all(np.abs(u - v).max() <= 1e-2 * np.abs(u).max() for u, v in zip(first, third))
