@@ -167,7 +167,7 @@ hipError_t run_layer(hisq_lattice lat, int lslot, int prec, int recon, bool w16,
     const int nblk = lat->ntile * (phi - plo + 1);
     a.batch = batch;
     a.bper = batch_chunk(nblk, batch, LAYER_BLOCKS);
-    return launch_ptc_layer(prec, recon, w16, cin, cout, a, nblk, stream);
+    return launch_ptc_layer(prec, recon, w16, cin, cout, a, nblk, lat->V, stream);
 }
 
 // Weight gradient of one layer application, summed over the output parities

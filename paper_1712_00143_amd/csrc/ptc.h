@@ -47,8 +47,9 @@ struct PtcFuse {
     int nt;
 };
 
+// V: sites of the lattice
 hipError_t launch_ptc_layer(int prec, int recon, bool w16, int cin, int cout, const PtcLaunch &a, int nblk,
-                            hipStream_t s);
+                            long long V, hipStream_t s);
 
 // Blocks that a layer launch should have before its batch entries share blocks:
 // one full load of the 256 CUs at the three or four waves per SIMD that the

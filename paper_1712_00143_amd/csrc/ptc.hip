@@ -162,38 +162,57 @@ __device__ __forceinline__ void mix_acc(const float2 w, const Cx<float> v[3], Cx
 // against one entry per block, three waves of three paths and the link
 // unpacked for each entry.  The matrix cores are no help: FP32 4x4x1 products
 // (nine cycles for what takes four multiply-adds) on the mixing gave 62 us.
-template <class LT, int R, class WT, int CIN, int COUT>
-__global__ void __launch_bounds__(256) k_ptc_layer(PtcLaunch a)
+//
+// STREAM (one entry, links beyond the Infinity Cache: see layer_form): memory
+// bounds it, so the blocks take the sites of one parity after the other in plain
+// order (a contiguous eighth per XCD costs 5 % of the rate), and the vectors are
+// requested before the links are unpacked.  W = 1: a wave takes the whole
+// stencil of its sites, two hops at a time, without a join.
+template <class LT, int R, class WT, int CIN, int COUT, int W, bool STREAM>
+__global__ void __launch_bounds__(64 * W) k_ptc_layer(PtcLaunch a)
 {
     if (a.gate && a.gate->status != a.gate_want) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const ProbDesc &pd = a.probs[0];
     const int ntile = pd.ntile;
     const int npar = gridDim.x / ntile;
-    const int unit = xcd_tile(blockIdx.x, gridDim.x, 1);
-    const int par = a.par_lo + unit % npar, tile = unit / npar;
+    const int unit = xcd_tile(blockIdx.x, gridDim.x, !STREAM);
+    const int par = a.par_lo + (STREAM ? unit / ntile : unit % npar), tile = STREAM ? unit % ntile : unit / npar;
     const bool valid = tile * TILE + lane < pd.h;
     const int i = valid ? tile * TILE + lane : pd.h - 1;   // idle lanes repeat the last site
     const long long h = pd.h;
     const LinkSet &ls = pd.ls[a.lslot];
     const Coord co = cb_to_coord_pd(i, par, pd);
     const int lex = 2 * i + (co.x[0] & 1);
-    constexpr int W = 4, G = 8 / W;   // waves, hops of each
-    __shared__ float red[W * COUT * 6 * 64];
+    constexpr int H = 8 / W, G = 2;   // hops of a wave, hops in hand
+    constexpr bool KEEP = H == G;     // the links stay in registers
+    static_assert(KEEP || STREAM, "a block of several entries keeps its links");
+    __shared__ float red[W > 1 ? W * COUT * 6 * 64 : 1];
     const bool hops = path_live(a, par, 1), ident = path_live(a, par, 0);
-    Cx<float> u[G][3][3];
+    const int b0 = blockIdx.y * a.bper, b1 = b0 + a.bper < a.batch ? b0 + a.bper : a.batch;
+    RawLink<LT, R> raw[G];
+    Cx<float> u[G][3][3], sv[G][CIN][3];
     int site[G];
-    if (hops) {
-        RawLink<LT, R> raw[G];
+    auto links = [&](int k0) {
 #pragma unroll
         for (int g = 0; g < G; g++) {
-            site[g] = path_site(pd, i, co, lex, 1 + wave * G + g);
-            path_link<LT, R>(ls, par, i, 1 + wave * G + g, raw[g]);
+            site[g] = path_site(pd, i, co, lex, k0 + g);
+            path_link<LT, R>(ls, par, i, k0 + g, raw[g]);
         }
+    };
+    auto vectors = [&](const float *in_b) {
 #pragma unroll
-        for (int g = 0; g < G; g++) path_matrix<LT, R>(ls, co, 1 + wave * G + g, raw[g], u[g]);
+        for (int g = 0; g < G; g++) load_site<CIN>(in_b, 2, 1 - par, h, site[g], sv[g]);
+    };
+    auto unpack = [&](int k0) {
+#pragma unroll
+        for (int g = 0; g < G; g++) path_matrix<LT, R>(ls, co, k0 + g, raw[g], u[g]);
+    };
+    if (KEEP && hops) {
+        links(1 + wave * G);
+        if (STREAM) vectors(a.in + (size_t)b0 * a.in_bstride);
+        unpack(1 + wave * G);
     }
-    const int b0 = blockIdx.y * a.bper, b1 = b0 + a.bper < a.batch ? b0 + a.bper : a.batch;
     for (int b = b0; b < b1; b++) {
         const float *in_b = a.in + (size_t)b * a.in_bstride;
         Cx<float> acc[COUT][3];
@@ -210,57 +229,62 @@ __global__ void __launch_bounds__(256) k_ptc_layer(PtcLaunch a)
 #pragma unroll
                 for (int c = 0; c < COUT; c++) mix_acc(ldw<WT>(a.w, (c * CIN + cp) * 9), v[0], acc[c]);
             }
-        if (hops) {
-            Cx<float> sv[G][CIN][3];
+        if (hops)
 #pragma unroll
-            for (int g = 0; g < G; g++) load_site<CIN>(in_b, 2, 1 - par, h, site[g], sv[g]);
+            for (int h0 = 0; h0 < H; h0 += G) {
+                if (!KEEP) links(1 + wave * H + h0);
+                if (!(KEEP && STREAM)) vectors(in_b);
+                if (!KEEP) unpack(1 + wave * H + h0);
 #pragma unroll
-            for (int g = 0; g < G; g++) {
-                const int k = 1 + wave * G + g;
-                if constexpr (COUT < CIN) {
+                for (int g = 0; g < G; g++) {
+                    const int k = 1 + wave * H + h0 + g;
+                    if constexpr (COUT < CIN) {
 #pragma unroll
-                    for (int c = 0; c < COUT; c++) {
-                        Cx<float> ph[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+                        for (int c = 0; c < COUT; c++) {
+                            Cx<float> ph[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
 #pragma unroll
-                        for (int cp = 0; cp < CIN; cp++) mix_acc(ldw<WT>(a.w, (c * CIN + cp) * 9 + k), sv[g][cp], ph);
-                        matvec_acc(u[g], ph, acc[c]);
-                    }
-                } else {
+                            for (int cp = 0; cp < CIN; cp++)
+                                mix_acc(ldw<WT>(a.w, (c * CIN + cp) * 9 + k), sv[g][cp], ph);
+                            matvec_acc(u[g], ph, acc[c]);
+                        }
+                    } else {
 #pragma unroll
-                    for (int cp = 0; cp < CIN; cp++) {
-                        Cx<float> t[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
-                        matvec_acc(u[g], sv[g][cp], t);
+                        for (int cp = 0; cp < CIN; cp++) {
+                            Cx<float> t[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+                            matvec_acc(u[g], sv[g][cp], t);
 #pragma unroll
-                        for (int c = 0; c < COUT; c++) mix_acc(ldw<WT>(a.w, (c * CIN + cp) * 9 + k), t, acc[c]);
+                            for (int c = 0; c < COUT; c++) mix_acc(ldw<WT>(a.w, (c * CIN + cp) * 9 + k), t, acc[c]);
+                        }
                     }
                 }
             }
-        }
-        float *mine = red + (size_t)wave * COUT * 6 * 64 + lane;
+        if constexpr (W > 1) {
+            float *mine = red + (size_t)wave * COUT * 6 * 64 + lane;
 #pragma unroll
-        for (int c = 0; c < COUT; c++)
-            if (c % W != wave)
+            for (int c = 0; c < COUT; c++)
+                if (c % W != wave)
 #pragma unroll
-                for (int q = 0; q < 3; q++) {
-                    mine[(6 * c + 2 * q) * 64] = acc[c][q].re;
-                    mine[(6 * c + 2 * q + 1) * 64] = acc[c][q].im;
-                }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < COUT; c++)
-            if (c % W == wave)
-#pragma unroll
-                for (int q = 0; q < 3; q++) {
-                    Cx<float> t = {0.f, 0.f};
-#pragma unroll
-                    for (int w = 0; w < W; w++) {   // the waves in order
-                        const float *o = red + ((size_t)w * COUT + c) * 6 * 64 + lane;
-                        t.re += w == c % W ? acc[c][q].re : o[2 * q * 64];
-                        t.im += w == c % W ? acc[c][q].im : o[(2 * q + 1) * 64];
+                    for (int q = 0; q < 3; q++) {
+                        mine[(6 * c + 2 * q) * 64] = acc[c][q].re;
+                        mine[(6 * c + 2 * q + 1) * 64] = acc[c][q].im;
                     }
-                    acc[c][q] = t;
-                }
-        if (b + 1 < b1) __syncthreads();
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < COUT; c++)
+                if (c % W == wave)
+#pragma unroll
+                    for (int q = 0; q < 3; q++) {
+                        Cx<float> t = {0.f, 0.f};
+#pragma unroll
+                        for (int w = 0; w < W; w++) {   // the waves in order
+                            const float *o = red + ((size_t)w * COUT + c) * 6 * 64 + lane;
+                            t.re += w == c % W ? acc[c][q].re : o[2 * q * 64];
+                            t.im += w == c % W ? acc[c][q].im : o[(2 * q + 1) * 64];
+                        }
+                        acc[c][q] = t;
+                    }
+            if (b + 1 < b1) __syncthreads();
+        }
         double dr = 0.0, di = 0.0;
 #pragma unroll
         for (int c = 0; c < COUT; c++) {
@@ -583,11 +607,52 @@ __global__ void k_adam(PtcNet net, float *m, float *v, const double *g, int step
 
 // ------------------------------------------------------------- launchers
 
+// How a layer is applied: 0 four waves, batch entries sharing the unpacked
+// links; the others for one entry per block on lattices whose fat links stream
+// past the Infinity Cache (FP32 recon-18: 576 bytes a site, FP16 recon-12: 192):
+// 1 four waves, 2 one wave, both in plain order.  One layer in us by form 0 / 1 /
+// 2:
+//             1 -> 1            2 -> 2            4 -> 4            8 -> 1
+//   FP32 24^4     33 / 38 / 40     41 / 46 / 47    56 / 64 / 69    59 / 73 / 86
+//        24^3x48  82 / 78 / 82     94 / 88 / 94   122 / 117 / 132  134 / 162 / 167
+//        28^4     80 / 75 / 77     91 / 88 / 93   116 / 119 / 129  118 / 164 / 174
+//        32^4    134 / 127 / 125  150 / 146 / 142 200 / 197 / 205  267 / 261 / 246
+//   FP16 24^3x48  33 / 39 / 36     47 / 51 / 49    90 / 98 / 100   89 / 124 / 121
+//        32^4     51 / 54 / 51     81 / 80 / 72   148 / 158 / 158 154 / 200 / 174
+//        32^3x64 114 / 120 / 104  165 / 174 / 145 298 / 309 / 321 336 / 397 / 363
+// Where four or more channels are gathered for fewer, the vectors count for more
+// than the links, and form 0 keeps their neighbours in an XCD's L2.
+static int layer_form(int prec, int cin, int cout, long long V, int bper)
+{
+    if (bper > 1 || cin * cout >= 64 || (cin > 2 && cin > cout)) return 0;
+    if (prec == 2) return V >= 1 << 20 && cin <= 2 ? 2 : 0;
+    if (V <= 1 << 19) return 0;
+    return V >= 1 << 20 && (cin == 1 || cout == 1) ? 2 : 1;
+}
+
+template <class LT, int R, class WT, int I, int O>
+static hipError_t layer_f(int form, const PtcLaunch &a, dim3 g, hipStream_t s)
+{
+    if constexpr (I * O < 64) {
+        if (form == 2) {
+            hipLaunchKernelGGL((k_ptc_layer<LT, R, WT, I, O, 1, true>), g, dim3(64), 0, s, a);
+            return hipGetLastError();
+        }
+        if constexpr (sizeof(LT) == 4)
+            if (form == 1) {
+                hipLaunchKernelGGL((k_ptc_layer<LT, R, WT, I, O, 4, true>), g, dim3(256), 0, s, a);
+                return hipGetLastError();
+            }
+    }
+    hipLaunchKernelGGL((k_ptc_layer<LT, R, WT, I, O, 4, false>), g, dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 template <class LT, int R, class WT>
-static hipError_t layer_c(int cin, int cout, const PtcLaunch &a, dim3 g, hipStream_t s)
+static hipError_t layer_c(int form, int cin, int cout, const PtcLaunch &a, dim3 g, hipStream_t s)
 {
 #define PTC_CASE(I, O) \
-    if (cin == I && cout == O) { hipLaunchKernelGGL((k_ptc_layer<LT, R, WT, I, O>), g, dim3(256), 0, s, a); return hipGetLastError(); }
+    if (cin == I && cout == O) return layer_f<LT, R, WT, I, O>(form, a, g, s);
     PTC_CASE(1, 1) PTC_CASE(1, 4) PTC_CASE(4, 4) PTC_CASE(4, 1) PTC_CASE(1, 2) PTC_CASE(2, 2) PTC_CASE(2, 1)
     PTC_CASE(2, 4) PTC_CASE(4, 2) PTC_CASE(1, 8) PTC_CASE(8, 8) PTC_CASE(8, 1)
 #undef PTC_CASE
@@ -595,13 +660,14 @@ static hipError_t layer_c(int cin, int cout, const PtcLaunch &a, dim3 g, hipStre
 }
 
 hipError_t launch_ptc_layer(int prec, int recon, bool w16, int cin, int cout, const PtcLaunch &a, int nblk,
-                            hipStream_t s)
+                            long long V, hipStream_t s)
 {
     dim3 g(nblk, (a.batch + a.bper - 1) / a.bper);
+    const int f = layer_form(prec, cin, cout, V, a.bper);
     if (prec == 1 && recon == 18)
-        return w16 ? layer_c<float, 18, __half>(cin, cout, a, g, s) : layer_c<float, 18, float>(cin, cout, a, g, s);
+        return w16 ? layer_c<float, 18, __half>(f, cin, cout, a, g, s) : layer_c<float, 18, float>(f, cin, cout, a, g, s);
     if (prec == 2 && recon == 12)
-        return w16 ? layer_c<__half, 12, __half>(cin, cout, a, g, s) : layer_c<__half, 12, float>(cin, cout, a, g, s);
+        return w16 ? layer_c<__half, 12, __half>(f, cin, cout, a, g, s) : layer_c<__half, 12, float>(f, cin, cout, a, g, s);
     return hipErrorInvalidValue;
 }
 
