@@ -188,8 +188,9 @@ hipError_t run_wgrad(hisq_ptc_s *n, hisq_lattice lat, int cin, int cout, const f
     a.batch = batch;
     a.bper = batch_chunk(tiles, batch, WGRAD_UNITS);
     const long long units = tiles * ((batch + a.bper - 1) / a.bper);
-    const int nrow = (int)(units < WGRAD_ROWS ? units : WGRAD_ROWS);
-    hipError_t e = launch_ptc_wgrad(n->tprec, n->trecon, cin, cout, a, g_pstride, nrow, s);
+    const bool nine = wgrad_nine(cin, cout, lat->V, a.bper);
+    const int nrow = (int)std::min<long long>(units, nine ? WGRAD_NINE_ROWS : WGRAD_ROWS);
+    hipError_t e = launch_ptc_wgrad(n->tprec, n->trecon, nine, cin, cout, a, g_pstride, nrow, s);
     if (e != hipSuccess) return e;
     return launch_ptc_wsum(n->part, nrow, cin, cout, gw, mode, s);
 }

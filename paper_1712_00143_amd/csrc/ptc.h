@@ -87,11 +87,20 @@ hipError_t launch_ptc_infer(int prec, int recon, int cin, int cout, int ik, int 
 // Units wanted before batch entries share one: the rows that take one unit more
 // than others then cost at most a tenth.
 constexpr int WGRAD_ROWS = 336, WGRAD_UNITS = 10 * WGRAD_ROWS;
+// Rows of nine-wave blocks, a path each, for a single entry on lattices beyond
+// the caches and few channels (32^4, FP16 links, layer_backward: 1 -> 1 115 us
+// with WGRAD_ROWS rows of four-wave blocks, 94 so; 2 -> 2 143 and 125, 8 -> 1 in
+// FP32 303 and 292; 4 -> 4 216 and 258; at 24^4 55 and 53, 62 and 62).
+constexpr int WGRAD_NINE_ROWS = 1024;
+inline bool wgrad_nine(int cin, int cout, long long V, int bper)
+{
+    return bper == 1 && V > 1 << 19 && (cin == 1 || cout == 1 || cin * cout <= 4);
+}
 
 // Weight-gradient partials of npar output parities x a.batch entries, reduced
 // into nrow rows of [9][cout][cin] complex FP64.
-hipError_t launch_ptc_wgrad(int prec, int recon, int cin, int cout, const PtcLaunch &a, int npar, int nrow,
-                           hipStream_t s);
+hipError_t launch_ptc_wgrad(int prec, int recon, bool nine, int cin, int cout, const PtcLaunch &a, int npar, int nrow,
+                            hipStream_t s);
 enum : int { WSUM_SET = 0, WSUM_ADD = 1, WSUM_ADJOINT = 2 };
 hipError_t launch_ptc_wsum(const double *partials, long long nrow, int cin, int cout, double *gw, int mode,
                            hipStream_t s);

@@ -336,12 +336,16 @@ __global__ void __launch_bounds__(64 * W) k_ptc_layer(PtcLaunch a)
 // (T_k in)^+ g = in^+ (T_k^+ g).  16^4, 8 entries: 4 -> 4 110 -> 73 us, 4 -> 1
 // 53 -> 42 us, 1 -> 4 40 -> 38 us, against blocks of nine waves, a path each
 // (two or three on a SIMD), that unpacked the link for every entry.
-template <class LT, int R, int CIN, int COUT>
-__global__ void __launch_bounds__(256) k_ptc_wgrad(PtcLaunch a, int npar, int nrow)
+//
+// W = 9: those blocks, for one entry per unit on lattices that stream from
+// memory (wgrad_nine): a row's nine waves read the same vectors at the same time,
+// which blocks of their own would fetch again.
+template <class LT, int R, int CIN, int COUT, int W>
+__global__ void __launch_bounds__(64 * W) k_ptc_wgrad(PtcLaunch a, int npar, int nrow)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int k = blockIdx.y < 2 ? 1 + 4 * blockIdx.y + wave : 0;
-    const int row = blockIdx.y < 2 ? blockIdx.x : 4 * blockIdx.x + wave;
+    const int k = W == 9 ? wave : blockIdx.y < 2 ? 1 + 4 * blockIdx.y + wave : 0;
+    const int row = W == 9 || blockIdx.y < 2 ? blockIdx.x : 4 * blockIdx.x + wave;
     if (row >= nrow) return;
     const ProbDesc &pd = a.probs[0];
     const int ntile = pd.ntile;
@@ -365,12 +369,15 @@ __global__ void __launch_bounds__(256) k_ptc_wgrad(PtcLaunch a, int npar, int nr
         const int site = path_site(pd, i, co, 2 * i + (co.x[0] & 1), k);
         RawLink<LT, R> raw;
         path_link<LT, R>(ls, par, i, k, raw);
-        Cx<float> m[3][3];
-        if (k != 0) path_matrix<LT, R>(ls, co, k, raw, m);
-        for (int b = b0; b < b1; b++) {
-            Cx<float> v[CIN][3], g[COUT][3];
+        Cx<float> m[3][3], v[CIN][3], g[COUT][3];
+        auto vectors = [&](int b) {
             load_site<CIN>(a.in + (size_t)b * a.in_bstride, 2, k == 0 ? par : 1 - par, h, site, v);
             load_site<COUT>(a.g + (size_t)b * a.g_bstride, a.g_pstride, par - a.g_par0, h, i, g);
+        };
+        if (W == 9) vectors(b0);   // its only entry, requested before the link is unpacked
+        if (k != 0) path_matrix<LT, R>(ls, co, k, raw, m);
+        for (int b = b0; b < b1; b++) {
+            if (W != 9) vectors(b);
             if (k != 0) {
                 if constexpr (COUT < CIN) {
 #pragma unroll
@@ -671,12 +678,23 @@ hipError_t launch_ptc_layer(int prec, int recon, bool w16, int cin, int cout, co
     return hipErrorInvalidValue;
 }
 
-template <class LT, int R>
-static hipError_t wgrad_c(int cin, int cout, const PtcLaunch &a, int npar, int nrow, hipStream_t s)
+template <class LT, int R, int I, int O>
+static hipError_t wgrad_w(bool nine, const PtcLaunch &a, int npar, int nrow, hipStream_t s)
 {
-    const dim3 g(nrow, 3), b(256);
+    if constexpr (I == 1 || O == 1 || I * O <= 4)
+        if (nine) {
+            hipLaunchKernelGGL((k_ptc_wgrad<LT, R, I, O, 9>), dim3(nrow), dim3(576), 0, s, a, npar, nrow);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((k_ptc_wgrad<LT, R, I, O, 4>), dim3(nrow, 3), dim3(256), 0, s, a, npar, nrow);
+    return hipGetLastError();
+}
+
+template <class LT, int R>
+static hipError_t wgrad_c(bool nine, int cin, int cout, const PtcLaunch &a, int npar, int nrow, hipStream_t s)
+{
 #define WG_CASE(I, O) \
-    if (cin == I && cout == O) { hipLaunchKernelGGL((k_ptc_wgrad<LT, R, I, O>), g, b, 0, s, a, npar, nrow); return hipGetLastError(); }
+    if (cin == I && cout == O) return wgrad_w<LT, R, I, O>(nine, a, npar, nrow, s);
     WG_CASE(1, 1) WG_CASE(1, 4) WG_CASE(4, 4) WG_CASE(4, 1) WG_CASE(1, 2) WG_CASE(2, 2) WG_CASE(2, 1)
     WG_CASE(2, 4) WG_CASE(4, 2) WG_CASE(1, 8) WG_CASE(8, 8) WG_CASE(8, 1)
 #undef WG_CASE
@@ -684,11 +702,11 @@ static hipError_t wgrad_c(int cin, int cout, const PtcLaunch &a, int npar, int n
 }
 
 // transports on FP32 recon-18 (prec 1) or FP16 recon-12 (prec 2) fat links
-hipError_t launch_ptc_wgrad(int prec, int recon, int cin, int cout, const PtcLaunch &a, int npar, int nrow,
+hipError_t launch_ptc_wgrad(int prec, int recon, bool nine, int cin, int cout, const PtcLaunch &a, int npar, int nrow,
                             hipStream_t s)
 {
-    if (prec == 1 && recon == 18) return wgrad_c<float, 18>(cin, cout, a, npar, nrow, s);
-    if (prec == 2 && recon == 12) return wgrad_c<__half, 12>(cin, cout, a, npar, nrow, s);
+    if (prec == 1 && recon == 18) return wgrad_c<float, 18>(nine, cin, cout, a, npar, nrow, s);
+    if (prec == 2 && recon == 12) return wgrad_c<__half, 12>(nine, cin, cout, a, npar, nrow, s);
     return hipErrorInvalidValue;
 }
 
