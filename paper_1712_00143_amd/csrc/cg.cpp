@@ -61,7 +61,8 @@ hisq_status build_set(hisq_lattice lat0, SolveSet &S, const std::vector<hisq_lat
         ntile += hd[k].ntile;
         nsite += hd[k].h;
     }
-    bool same = S.nprob == n && S.ntile == ntile && S.nsite == nsite && S.ddesc;
+    // dred: the last one allocated, so that a set that was refused some memory is built again
+    bool same = S.nprob == n && S.ntile == ntile && S.nsite == nsite && S.dred;
     if (!same) {
         S.release();
         S.nprob = n;

@@ -127,6 +127,32 @@ PtcLaunch base_launch(hisq_lattice lat, int lslot)
     return a;
 }
 
+// New device memory in the place of *p; *p is null if it is refused.
+hipError_t renew(void **p, size_t bytes)
+{
+    if (*p) (void)hipFree(*p);
+    *p = nullptr;
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) *p = nullptr;
+    return e;
+}
+
+// At least `doubles` of partial sums.
+hipError_t need_partials(hisq_ptc_s *n, size_t doubles)
+{
+    if (n->part_n >= doubles) return hipSuccess;
+    n->part_n = 0;
+    const hipError_t e = renew((void **)&n->part, doubles * 8);
+    if (e == hipSuccess) n->part_n = doubles;
+    return e;
+}
+
+// Weight-gradient rows at most: one per work unit (tile, parity, entry).
+size_t wgrad_rows(long long ntile, int batch)
+{
+    return (size_t)std::min<long long>(2 * ntile * batch, std::max(WGRAD_ROWS, WGRAD_NINE_ROWS));
+}
+
 // Batch entries per block or unit: all of them where the nblk blocks of one
 // entry fill the device by themselves (want of them), else as few as do.
 int batch_chunk(long long nblk, int batch, long long want)
@@ -401,8 +427,8 @@ hipError_t ptc_apply_internal(hisq_ptc n, hisq_lattice lat, int lslot, int prec,
     if (n->aprec == HISQ_F16) return apply_net_infer16(n, lat, lslot, prec, recon, r, z, lat->s, fz);
     const long long need = (long long)cmax(n) * 2 * lat->h * 6 * 2;
     if (n->infV < need) {
-        if (n->inf) (void)hipFree(n->inf);
-        hipError_t e = hipMalloc(&n->inf, need * 4);
+        n->infV = 0;
+        hipError_t e = renew((void **)&n->inf, need * 4);
         if (e != hipSuccess) return e;
         n->infV = need;
     }
@@ -663,12 +689,7 @@ hisq_status hisq_ptc_layer_backward(hisq_ptc n, int layer, const void *in, const
         HIPCHK(lat, run_layer(lat, n->tslot(), n->tprec, n->trecon, false, n->wa32 + 2 * n->woff[layer], cout, cin, (const float *)gout, 0,
                               -1, (float *)gin, 0, 2, 0, 1, 1, s));
     if (gw) {
-        const size_t need = ((size_t)2 * lat->ntile + 256) * 9 * cin * cout * 2;
-        if (n->part_n < need) {
-            if (n->part) (void)hipFree(n->part);
-            HIPCHK(lat, hipMalloc(&n->part, need * 8));
-            n->part_n = need;
-        }
+        HIPCHK(lat, need_partials(n, wgrad_rows(lat->ntile, 1) * 9 * cin * cout * 2));
         HIPCHK(lat, run_wgrad(n, lat, cin, cout, (const float *)in, 0, -1, (const float *)gout, 0, 2, 1, n->gtmp, WSUM_SET, s));
         HIPCHK(lat, hipMemcpyAsync(gw, n->gtmp, sizeof(double) * 2 * 9 * cin * cout, hipMemcpyDeviceToHost, s));
     }
@@ -987,24 +1008,17 @@ hisq_status hisq_ptc_train(hisq_ptc n, int steps, int batch, double lr, unsigned
     const size_t nbuf = (size_t)(2 * nl + 1);
     const size_t need = (size_t)batch * (actf * nbuf + h * 6 * 6);
     if (n->wsB != batch || n->wsV != V) {
-        if (n->act) (void)hipFree(n->act);
-        if (n->dee) (void)hipFree(n->dee);
-        n->act = nullptr;
-        n->dee = nullptr;
-        HIPCHK(lat0, hipMalloc(&n->act, need * 4));
-        HIPCHK(lat0, hipMalloc(&n->dee, sizeof(double) * batch));
+        n->wsB = 0;   // nothing to use if one of the two is refused
+        HIPCHK(lat0, renew((void **)&n->act, need * 4));
+        HIPCHK(lat0, renew((void **)&n->dee, sizeof(double) * batch));
         n->wsB = batch;
         n->wsV = V;
     }
     const size_t ntl = (size_t)((h + 63) / 64);
-    // weight-gradient rows plus the second-pass rows of the sum
-    const size_t pneed = ((size_t)batch * 2 * ntl + 256) * 9 * C * C * 2 + 64;
+    // weight-gradient rows, and the sums of the loss
+    const size_t pneed = wgrad_rows((long long)ntl, batch) * 9 * C * C * 2;
     const size_t lneed = (size_t)batch * ntl * NPART + 4 * (size_t)batch + 4;
-    if (n->part_n < std::max(pneed, lneed)) {
-        if (n->part) (void)hipFree(n->part);
-        n->part_n = std::max(pneed, lneed);
-        HIPCHK(lat0, hipMalloc(&n->part, n->part_n * 8));
-    }
+    HIPCHK(lat0, need_partials(n, std::max(pneed, lneed)));
     float *A = n->act;
     auto full = [&](size_t k) { return A + (size_t)batch * actf * k; };
     std::vector<float *> acts(nl + 1), bs(nl + 1);
