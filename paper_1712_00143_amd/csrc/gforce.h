@@ -29,8 +29,9 @@ void gauge_force_grid(const SmearGeom &g, int *ntile, int *tch, int *nblocks);
 // permutation of [0, ntile): when a tile is two whole x rows (L0 = 32) and
 // L1, L2 are multiples of 8, each run of 32 consecutive tiles covers 8 y rows
 // by 8 z planes instead of two whole z planes, so that the blocks an XCD
-// holds at once read fewer neighbour planes of other blocks; otherwise the
-// identity.
+// holds at once read fewer neighbour planes of other blocks (32^4: smearing
+// 9.8 ms against 10.25 in plain order, the fermion force 33.6 against 35.1, the
+// direct sum of the gauge action the same); otherwise the identity.
 __device__ __forceinline__ int brick_tile(int tile, const SmearGeom &g)
 {
     if (g.L[0] != 32 || (g.L[1] & 7) || (g.L[2] & 7)) return tile;

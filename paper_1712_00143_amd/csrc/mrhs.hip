@@ -163,9 +163,9 @@ __global__ void __launch_bounds__(64 * W) k_dslash_mrhs(MrhsLaunch a)
     // epilogue of NR right-hand sides runs in NR waves side by side instead
     // of in wave 0 while the others wait.  At 24^3x48, FP32 recon-18, with the
     // wide branch-free gathers: four right-hand sides 105 -> 93-98 us (PLAIN)
-    // and 139 -> 113 us (AX); 48 of them 660 -> 569 us and 989 -> 736 us, the
-    // FP64 residual of 48 976 -> 760 us.  What is left is memory-side traffic
-    // (3.6 GB a launch of 48, vectors refetched across the t hops).
+    // and 139 -> 113 us (AX); 48 of them 938 -> 805 us (PLAIN).  What is left is
+    // memory-side traffic (3.6 GB a launch of 48, vectors refetched across the t
+    // hops).
     constexpr int PW = NR == 1 ? 1 : W < 4 ? W : NR == 2 ? 2 : 4;
     if constexpr (W > 1) {
         constexpr int FOLD = W / 2 >= PW ? W / 2 : 0;   // waves written per folding round, at most

@@ -158,7 +158,7 @@ __device__ __forceinline__ void mix_acc(const float2 w, const Cx<float> v[3], Cx
 // transported (the transport is linear).  The waves' outputs are joined
 // through LDS, channel c by wave c mod 4.
 //
-// 16^4, 8 entries, FP16 recon-12 links: 4 -> 4 70 -> 55 us, 4 -> 1 49 -> 29 us,
+// 16^4, 8 entries, FP16 recon-12 links: 4 -> 4 70 -> 57 us, 4 -> 1 49 -> 29 us,
 // against one entry per block, three waves of three paths and the link
 // unpacked for each entry.  The matrix cores are no help: FP32 4x4x1 products
 // (nine cycles for what takes four multiply-adds) on the mixing gave 62 us.
@@ -333,7 +333,7 @@ __global__ void __launch_bounds__(64 * W) k_ptc_layer(PtcLaunch a)
 // The vector ALU bounds it (4 -> 4: 144 transport, 192 product and 64
 // conversion or FP64 instructions per site, path and entry); with fewer
 // outputs than inputs the gradient is transported instead,
-// (T_k in)^+ g = in^+ (T_k^+ g).  16^4, 8 entries: 4 -> 4 110 -> 73 us, 4 -> 1
+// (T_k in)^+ g = in^+ (T_k^+ g).  16^4, 8 entries: 4 -> 4 110 -> 75 us, 4 -> 1
 // 53 -> 42 us, 1 -> 4 40 -> 38 us, against blocks of nine waves, a path each
 // (two or three on a SIMD), that unpacked the link for every entry.
 //

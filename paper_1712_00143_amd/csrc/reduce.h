@@ -47,8 +47,7 @@ __device__ __forceinline__ void publish_partials(double mine[NV], double *partia
 // Sum of v[0..NV) over the block's first wavefront, for kernels whose epilogue
 // runs in that wavefront alone (call it there only; result in lane 0).  The
 // same bits as block_sum with zeros in the other wavefronts, without their
-// shuffles and the three barriers (16^3x32 mixed CG 14.77 -> 14.54 ms on one
-// machine, 14.58 both ways on others, where the tuner takes two-wave blocks).
+// shuffles and the three barriers (no more than the spread of a solve).
 template <int NV>
 __device__ __forceinline__ void first_wave_sum(double v[NV])
 {
