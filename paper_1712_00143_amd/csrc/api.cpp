@@ -142,6 +142,20 @@ bool Tuner::lookup(const std::string &key, TuneChoice &c)
     return true;
 }
 
+bool Tuner::recall(const TuneChoice &kept, TuneChoice &c)
+{
+    std::lock_guard<std::mutex> g(mu_);
+    if (!(kept.us > 0)) return false;
+    c = kept;
+    return true;
+}
+
+TuneChoice Tuner::keep(TuneChoice &kept, const TuneChoice &c)
+{
+    std::lock_guard<std::mutex> g(mu_);
+    return kept = c;
+}
+
 void Tuner::store(const std::string &key, const TuneChoice &c)
 {
     std::lock_guard<std::mutex> g(mu_);
@@ -506,16 +520,13 @@ TuneChoice pick_shape(hisq_lattice lat, int prec, int recon, const ProbDesc *dde
     if (no_tune || Tuner::get().disabled()) return def;
     // the lattice's own operator: the choice this handle already looked up
     TuneChoice *own = nprob == 1 && ntile == lat->ntile ? &lat->shape[prec * 2 + (recon == 12)][streamed] : nullptr;
-    if (own && own->us > 0) return *own;
+    TuneChoice c;
+    if (own && Tuner::get().recall(*own, c)) return c;
     const std::string arch = arch_name(lat->device);
     if (arch.empty()) return def;
     std::string key = dslash_tune_key(arch, prec, recon, ntile, nprob);
     const std::string skey = dslash_tune_key(arch, prec, recon, ntile, nprob, true);
-    TuneChoice c;
-    if (Tuner::get().lookup(streamed ? skey : key, c)) {
-        if (own) *own = c;
-        return c;
-    }
+    if (Tuner::get().lookup(streamed ? skey : key, c)) return own ? Tuner::get().keep(*own, c) : c;
     DVec in, out;
     if (dvec_alloc(in, prec, nsite) != hipSuccess || dvec_alloc(out, prec, nsite) != hipSuccess) {
         dvec_free(in);
@@ -690,7 +701,8 @@ TuneChoice pick_shape_mrhs(hisq_lattice lat, int prec, int recon, int nr, bool n
     const bool both = nr == 4 && prec != 0;   // the second choice: FP32 vectors only
     several = several && both;
     TuneChoice *own = &lat->mrhs_shape[prec * 2 + (recon == 12)][several ? 4 : nr - 1];
-    if (own->us > 0) return *own;
+    TuneChoice c;
+    if (Tuner::get().recall(*own, c)) return c;
     const std::string arch = arch_name(lat->device);
     if (arch.empty()) return def;
     std::ostringstream ks;
@@ -699,9 +711,8 @@ TuneChoice pick_shape_mrhs(hisq_lattice lat, int prec, int recon, int nr, bool n
     for (auto &ch : key)
         if (ch == ' ') ch = '_';
     const std::string gkey = key + ":several";
-    TuneChoice c;
-    if (several && Tuner::get().lookup(gkey, c)) return *own = c;
-    if (Tuner::get().lookup(key, c)) return *own = c;
+    if (several && Tuner::get().lookup(gkey, c)) return Tuner::get().keep(*own, c);
+    if (Tuner::get().lookup(key, c)) return Tuner::get().keep(*own, c);
     hipEvent_t e0, e1;
     (void)hipEventCreate(&e0);
     (void)hipEventCreate(&e1);

@@ -78,6 +78,10 @@ class Tuner {
     static Tuner &get();
     bool lookup(const std::string &key, TuneChoice &c);
     void store(const std::string &key, const TuneChoice &c);
+    // A choice that a handle keeps (us > 0 once known), without its key's
+    // strings; under the cache's lock, as several threads may use a handle.
+    bool recall(const TuneChoice &kept, TuneChoice &c);
+    TuneChoice keep(TuneChoice &kept, const TuneChoice &c);
     // HISQ_TUNE=0 in the environment: every launch takes its default shape
     bool disabled() const { return disabled_; }
     // HISQ_TUNE_VERBOSE=1: every timed candidate is printed to stderr

@@ -130,3 +130,48 @@ def test_weight_gradient_units_of_several_entries(chans):
         w = got
     net.close()
     lat.close()
+
+
+def test_one_handle_used_by_several_threads():
+    """Eight threads apply one lattice's operator, single and in groups, with the
+    launch shapes not yet known to the handle."""
+    import threading
+
+    import torch
+    from paper_1712_00143_amd import hisq as H
+    dims = (8, 6, 4, 10)
+    h = synth.volume(dims) // 2
+    fat, lng = synth.make_links(dims, 0.25, seed=4031)
+    psi = [synth.gaussian_even(dims, 4600 + k, 6) for k in range(8)]
+    ins = [torch.from_numpy(np.ascontiguousarray(p.astype(np.complex64)).view(np.float32).ravel()).cuda() for p in psi]
+    torch.cuda.synchronize()
+    lat = H.Lattice(dims)
+    lat.load_links(fat, lng)
+    lat.prepare_links(H.HISQ_F32, 18)
+    want = None
+    for _ in range(2):
+        outs = [torch.zeros_like(v) for v in ins]
+        torch.cuda.synchronize()
+        failed = []
+
+        def work(k):
+            try:
+                n = 6 if k % 2 else 1
+                for _ in range(20):
+                    lat.dslash(H.HISQ_ODD, H.HISQ_F32, 18, ins[k], outs[k], nrhs=n)
+            except Exception as e:  # noqa: BLE001
+                failed.append((k, e))
+
+        ts = [threading.Thread(target=work, args=(k,)) for k in range(8)]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+        torch.cuda.synchronize()
+        assert not failed, failed
+        for k in range(8):
+            got = outs[k].cpu().numpy().view(np.complex64).reshape(6, h, 3)
+            for j in range(6 if k % 2 else 1):
+                ref = oracle.dslash_half(dims, fat, lng, 1, psi[k][j])
+                assert np.linalg.norm(got[j] - ref) <= 5e-6 * np.linalg.norm(ref), (k, j)
+    lat.close()
